@@ -1023,7 +1023,8 @@ wf_status wf_init(void) {
   WF_HIP(load_fast_kernels(), "loading the token-skim kernels");
   WF_HIP(load_scan_kernels(), "loading the scan kernels");
   WF_HIP(load_attn_kernels(), "loading the attention kernels");
-  WF_HIP(load_skim_kernels(), "loading the DWT and skim kernels");
+  WF_HIP(load_skim_kernels(), "loading the skim kernels");
+  WF_HIP(load_dwt_kernels(), "loading the DWT kernels");
   void* scratch_ptr = nullptr;  // this file's code object and its scratch array
   WF_TRY(scratch_of_current_device(&scratch_ptr));
   return ok();

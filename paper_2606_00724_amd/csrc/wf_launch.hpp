@@ -194,6 +194,7 @@ hipError_t load_fast_kernels();
 hipError_t load_scan_kernels();
 hipError_t load_attn_kernels();
 hipError_t load_skim_kernels();
+hipError_t load_dwt_kernels();
 hipError_t launch_attn_combine(const wf_params& p, long nrows,
                                const float* part, const float* pstat, void* O,
                                hipStream_t s);

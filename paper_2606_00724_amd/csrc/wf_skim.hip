@@ -1,572 +1,17 @@
-// DWT of the cached prompt keys (eqs. 5-6) and the skim: perception weights
-// of the query block over the level-J approximation (eq. 7), their column
-// sums W (eq. 8) and the top-S coarse regions (eq. 9).
+// The skim: perception weights of the query block over the level-J
+// approximation of the keys (eq. 7), their column sums W (eq. 8) and the
+// top-S coarse regions (eq. 9).
 //
 // Layout: one unit = one (batch, head) pair; K is [U][L][D] with channels
-// contiguous.  The DWT runs along the sequence independently per channel.
-//
-//  * Haar in the fused path: the level-J approximation of block j is
-//    2^{-J/2} times the sum of its 2^J rows (the orthonormal pyramid
-//    collapses to a block sum), so a wave streams rows with 16-byte loads,
-//    accumulates in fp32 registers and finishes the block with cross-lane
-//    butterflies.
-//  * Daubechies-2 (and the staged transform that also returns details):
-//    every lane owns two channels and runs the filter-bank cascade along the
-//    sequence, level by level, with three samples of state per level; the
-//    half-sample symmetric extension is applied per level at the true end.
-//  * The skim epilogue multiplies the fp32 coefficient tile (in LDS) with
-//    the query block on fp32 MFMA (v_mfma_f32_16x16x4_f32), then writes the
-//    logits and per-tile row max / row sum of exponentials.  A per-unit
-//    kernel merges the tiles' row statistics, forms W and selects.
-#include <mutex>
+// contiguous.  A tile's coefficients (wf_dwt.hpp) stay in LDS: the epilogue
+// multiplies them with the query block on MFMA, then writes the logits and
+// per-tile row max / row sum of exponentials.  A per-unit kernel merges the
+// tiles' row statistics, forms W and selects.
 #include <vector>
 
-#include "wf_device.hpp"
-#include "wf_kernels.hpp"
-#include "wf_launch.hpp"
+#include "wf_dwt.hpp"
 
 namespace wf {
-
-struct Taps {
-  float g[4];
-  float h[4];
-  float inv_norm;  // 2^{-J/2}, for the Haar block sum
-};
-
-struct F2 {
-  float x, y;
-};
-
-__device__ __forceinline__ F2 load_pair(const bf16_t* p) {
-  uint32_t w = *reinterpret_cast<const uint32_t*>(p);
-  return F2{bf16_lo(w), bf16_hi(w)};
-}
-__device__ __forceinline__ F2 load_pair(const float* p) {
-  u32x2 w = *reinterpret_cast<const u32x2*>(p);
-  return F2{__uint_as_float(w[0]), __uint_as_float(w[1])};
-}
-
-// ------------------------------------------------------------ cascade
-
-// Filter-bank cascade over one stream of rows for one channel pair.  Level j
-// (1..J) consumes samples y^{j-1}[i] in increasing i and, after every odd i,
-// emits y^j[n] = sum_m g_m y^{j-1}[2n+m] (and the detail with h), with
-// n = (i - (M-1)) / 2.  Samples pushed before the stream's first aligned
-// coefficient produce emissions with smaller indices, which sinks ignore.
-template <int M, int J, bool DET>
-struct Cascade {
-  F2 s1[J + 1], s2[J + 1], s3[J + 1];  // y[i-1], y[i-2], y[i-3] per level
-  float g0, g1, g2, g3, h0, h1, h2, h3;
-  long L;
-  bool symmetric;
-
-  __device__ void init(const Taps& t, long L_, bool sym) {
-    g0 = t.g[0]; g1 = t.g[1]; g2 = t.g[2]; g3 = t.g[3];
-    h0 = t.h[0]; h1 = t.h[1]; h2 = t.h[2]; h3 = t.h[3];
-    L = L_;
-    symmetric = sym;
-#pragma unroll
-    for (int j = 0; j <= J; ++j) {
-      s1[j] = F2{0.f, 0.f};
-      s2[j] = F2{0.f, 0.f};
-      s3[j] = F2{0.f, 0.f};
-    }
-  }
-
-  template <int j, class Sink>
-  __device__ __forceinline__ void feed(long i, F2 v, Sink& sink) {
-    if (i & 1) {
-      long n;
-      F2 a, d;
-      if constexpr (M == 2) {
-        n = (i - 1) >> 1;
-        a.x = g0 * s1[j].x + g1 * v.x;
-        a.y = g0 * s1[j].y + g1 * v.y;
-        if constexpr (DET) {
-          d.x = h0 * s1[j].x + h1 * v.x;
-          d.y = h0 * s1[j].y + h1 * v.y;
-        }
-      } else {
-        n = (i - 3) >> 1;
-        a.x = g0 * s3[j].x + g1 * s2[j].x + g2 * s1[j].x + g3 * v.x;
-        a.y = g0 * s3[j].y + g1 * s2[j].y + g2 * s1[j].y + g3 * v.y;
-        if constexpr (DET) {
-          d.x = h0 * s3[j].x + h1 * s2[j].x + h2 * s1[j].x + h3 * v.x;
-          d.y = h0 * s3[j].y + h1 * s2[j].y + h2 * s1[j].y + h3 * v.y;
-        }
-      }
-      if constexpr (DET) sink.detail(j, n, d);
-      if constexpr (j < J) {
-        push<j + 1>(n, a, sink);
-      } else {
-        sink.approx(n, a);
-      }
-    }
-    s3[j] = s2[j];
-    s2[j] = s1[j];
-    s1[j] = v;
-  }
-
-  // Pushes y^{j-1}[i].  After the last sample of a level (i = N - 1) the
-  // symmetric mode continues with y[N] = y[N-1] and y[N+1] = y[N-2]
-  // (half-sample symmetric extension); a loop keeps one copy of the deeper
-  // levels' code.
-  template <int j, class Sink>
-  __device__ __forceinline__ void push(long i, F2 v, Sink& sink) {
-    int reps = 1;
-    const F2 prev = s1[j];
-    if constexpr (M == 4) {
-      if (symmetric && i == (L >> (j - 1)) - 1) reps = 3;
-    }
-#pragma unroll 1
-    for (int r = 0; r < reps; ++r) {
-      const F2 x = (r == 2) ? prev : v;
-      feed<j>(i + r, x, sink);
-    }
-  }
-};
-
-// Rows a stream reads past its own 2^J-aligned range: level-J coefficient n
-// of a 4-tap bank depends on rows 2^J n .. 2^J n + 3 (2^J - 1), so the last
-// owned coefficient needs 2^{J+1} - 2 extra rows; a 2-tap bank needs none.
-__host__ __device__ constexpr long cascade_halo(int M, int J) {
-  return M == 4 ? (2L << J) - 2 : 0;
-}
-
-// Row t of the sequence a tile transforms: the unit's key row t, or on a
-// refinement scale of the recursion row t of the gathered kept blocks
-// (parent [npar] ids of 2^shift rows each; ids are clamped into the unit).
-struct RowsIdentity {
-  __device__ __forceinline__ long operator()(long t) const { return t; }
-};
-struct RowsGathered {
-  const int32_t* par;
-  int shift;
-  long last;
-  __device__ __forceinline__ long operator()(long t) const {
-    const long r = ((long)par[t >> shift] << shift) | (t & ((1L << shift) - 1));
-    return min(max(r, 0L), last);
-  }
-};
-
-// Streams rows [t0, t_stop) of one unit into the cascade (periodic extension
-// reads row t mod L), 16 loads in flight per lane.
-template <int M, int J, bool DET, typename T, class Sink, class RowMap = RowsIdentity>
-__device__ void run_stream(Cascade<M, J, DET>& cas, const T* Kunit, int D,
-                           int cp, long t0, long t_stop, long L, Sink& sink,
-                           const RowMap& map = RowMap{}) {
-  constexpr int U = 16;
-  for (long t = t0; t < t_stop; t += U) {
-    F2 v[U];
-#pragma unroll
-    for (int k = 0; k < U; ++k) {
-      long tt = t + k;
-      if (tt < t_stop) {
-        long row = tt < L ? tt : tt % L;
-        v[k] = load_pair(Kunit + map(row) * D + 2 * cp);
-      } else {
-        v[k] = F2{0.f, 0.f};
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < U; ++k) {
-      if (t + k < t_stop) cas.template push<1>(t + k, v[k], sink);
-    }
-  }
-}
-
-struct GlobalSink {
-  float* aout;     // approximation, unit base + 2 cp
-  float* dout;     // details, unit base + 2 cp, nullable
-  long n0, n1;     // level-J rows owned by the stream
-  long L;
-  int J, D;
-  __device__ __forceinline__ void store2(float* p, F2 a) {
-    *reinterpret_cast<float2*>(p) = make_float2(a.x, a.y);
-  }
-  __device__ __forceinline__ void approx(long n, F2 a) {
-    if (n >= n0 && n < n1) store2(aout + n * D, a);
-  }
-  __device__ __forceinline__ void detail(int j, long n, F2 d) {
-    const long lo = n0 << (J - j), hi = n1 << (J - j);
-    if (dout && n >= lo && n < hi) {
-      const long row = (L - (L >> (j - 1))) + n;  // D_1 rows come first
-      store2(dout + row * D, d);
-    }
-  }
-};
-
-struct LdsSink {
-  float* coef;  // tile base + 2 cp
-  long nbase;   // coefficient index of tile row 0
-  long n0, n1;  // rows owned by the stream
-  int stride;
-  __device__ __forceinline__ void approx(long n, F2 a) {
-    if (n >= n0 && n < n1) {
-      float* p = coef + (n - nbase) * stride;
-      p[0] = a.x;
-      p[1] = a.y;
-    }
-  }
-  __device__ __forceinline__ void detail(int, long, F2) {}
-};
-
-// ------------------------------------------------------------ staged DWT
-
-template <int M, int J, typename T>
-__global__ __launch_bounds__(kBlock) void dwt_kernel(DwtArgs a, Taps taps) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int lps = a.D / 2;             // lanes per stream
-  const int spw = kWave / lps;         // streams per wave
-  const int cp = lane % lps;
-  const int sid = wave * spw + lane / lps;
-  const int u = blockIdx.x / a.ntiles;
-  const int tile = blockIdx.x % a.ntiles;
-  const long n0 = ((long)tile * a.streams + sid) * a.cps;
-  if (u >= a.U || n0 >= a.nJ) return;  // no barrier in this kernel
-  const long n1 = min(n0 + (long)a.cps, (long)a.nJ);
-  const T* Kunit = reinterpret_cast<const T*>(a.K) + (long)u * a.Ls * a.D;
-  GlobalSink sink;
-  sink.aout = a.approx + (long)u * a.nJ * a.D + 2 * cp;
-  sink.dout = a.details ? a.details + (long)u * (a.L - a.nJ) * a.D + 2 * cp
-                        : nullptr;
-  sink.n0 = n0;
-  sink.n1 = n1;
-  sink.L = a.L;
-  sink.J = J;
-  sink.D = a.D;
-  Cascade<M, J, true> cas;
-  const bool sym = (M == 4) && a.boundary == 0;
-  cas.init(taps, a.L, sym);
-  const long t0 = n0 << J;
-  long t_stop = (n1 << J) + cascade_halo(M, J);
-  if (sym || M == 2) t_stop = min(t_stop, (long)a.L);
-  run_stream<M, J, true, T>(cas, Kunit, a.D, cp, t0, t_stop, a.L, sink);
-}
-
-// ------------------------------------------------------------ skim tiles
-
-// Haar level-J approximation of tile rows [n0, n0 + ncoef) into LDS.
-// Coefficient n covers tokens bid(n) 2^J .. bid(n) 2^J + 2^J - 1.  A wave
-// sums groups of G = max(2^J, RPL) rows (RPL rows per 16-byte wave load):
-// one coefficient per group, or RPL / 2^J of them reduced across lanes.
-// LOADS = G / RPL loads per group (8 stands for 8 or more); small groups
-// are taken 8 / LOADS at a time so that a lane always has 8 loads in flight.
-template <typename T, int D, int LOADS, class BlockId>
-__device__ void haar_sum_tile_groups(const T* Kunit, long n0, int ncoef, int J,
-                                     float inv_norm, float* coef, const BlockId& bid) {
-  constexpr int CPL = 16 / sizeof(T);  // channels per lane (16-byte load)
-  constexpr int LPR = D / CPL;         // lanes per row
-  constexpr int RPL = kWave / LPR;     // rows per wave load
-  constexpr int STRIDE = D + kCoefPad;
-  constexpr int NW = kBlock / kWave;
-  constexpr int GPI = LOADS >= 8 ? 1 : 8 / LOADS;  // groups per iteration
-  constexpr int LPI = LOADS >= 8 ? 8 : LOADS;      // loads per group and batch
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int rsub = lane / LPR, csub = lane % LPR;
-  const int blk = 1 << J;
-  const int G = blk > RPL ? blk : RPL;
-  const int cpg = G / blk;                // coefficients per group
-  const int red = blk < RPL ? blk : RPL;  // rows reduced across lanes
-  const long rows = (long)ncoef << J;     // tile rows, in coefficient order
-  const int ngroups = (int)((rows + G - 1) / G);
-  const int nloads = LOADS >= 8 ? G / RPL : 1;  // batches of LPI loads per group
-  for (int gb = wave; gb < ngroups; gb += NW * GPI) {
-    float acc[GPI][CPL];
-#pragma unroll
-    for (int gi = 0; gi < GPI; ++gi)
-#pragma unroll
-      for (int e = 0; e < CPL; ++e) acc[gi][e] = 0.f;
-    for (int i0 = 0; i0 < nloads; i0 += LPI) {
-      u32x4 v[GPI][LPI];
-#pragma unroll
-      for (int gi = 0; gi < GPI; ++gi)
-#pragma unroll
-        for (int li = 0; li < LPI; ++li) {
-          const int grp = gb + gi * NW;
-          const long r = (long)grp * G + rsub + (long)(i0 + li) * RPL;
-          if (grp < ngroups && r < rows) {
-            const long t = ((long)bid(n0 + (r >> J)) << J) + (r & (blk - 1));
-            v[gi][li] = *reinterpret_cast<const u32x4*>(Kunit + t * D + csub * CPL);
-          } else {
-            v[gi][li] = u32x4{0u, 0u, 0u, 0u};
-          }
-        }
-#pragma unroll
-      for (int gi = 0; gi < GPI; ++gi)
-#pragma unroll
-        for (int li = 0; li < LPI; ++li) {
-          if constexpr (sizeof(T) == 2) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              acc[gi][2 * e] += bf16_lo(v[gi][li][e]);
-              acc[gi][2 * e + 1] += bf16_hi(v[gi][li][e]);
-            }
-          } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[gi][e] += __uint_as_float(v[gi][li][e]);
-          }
-        }
-    }
-#pragma unroll
-    for (int gi = 0; gi < GPI; ++gi) {
-      // the red rows of a coefficient sit LPR, 2 LPR, ... lanes apart (LDS
-      // permutes: with many waves resident their latency hides, where the
-      // VALU lane swaps would take issue slots)
-#pragma unroll
-      for (int sh = 1; sh < red; sh <<= 1) {
-#pragma unroll
-        for (int e = 0; e < CPL; ++e) acc[gi][e] += __shfl_xor(acc[gi][e], LPR * sh);
-      }
-      const int grp = gb + gi * NW;
-      if (grp < ngroups && rsub % red == 0) {
-        const int c = grp * cpg + rsub / blk;
-        if (c < ncoef) {
-          float* dst = coef + c * STRIDE + csub * CPL;
-#pragma unroll
-          for (int e = 0; e < CPL; ++e) dst[e] = acc[gi][e] * inv_norm;
-        }
-      }
-    }
-  }
-}
-
-template <typename T, int D, class BlockId>
-__device__ void haar_sum_tile(const T* Kunit, long n0, int ncoef, int J, float inv_norm,
-                              float* coef, const BlockId& bid) {
-  constexpr int RPL = kWave / (D / (16 / (int)sizeof(T)));
-  const int blk = 1 << J;
-  const int loads = (blk > RPL ? blk : RPL) / RPL;
-  switch (loads) {
-    case 1: haar_sum_tile_groups<T, D, 1>(Kunit, n0, ncoef, J, inv_norm, coef, bid); break;
-    case 2: haar_sum_tile_groups<T, D, 2>(Kunit, n0, ncoef, J, inv_norm, coef, bid); break;
-    case 4: haar_sum_tile_groups<T, D, 4>(Kunit, n0, ncoef, J, inv_norm, coef, bid); break;
-    default: haar_sum_tile_groups<T, D, 8>(Kunit, n0, ncoef, J, inv_norm, coef, bid); break;
-  }
-}
-
-// Cascade level-J approximation of tile rows [n0, n0 + ncoef) into LDS.
-// The tile is split into one stream per half/whole wave.
-template <int M, int J, typename T, int D, class RowMap>
-__device__ void cascade_tile(const T* Kunit, long L, long n0, int ncoef,
-                             int cpt, bool sym, const Taps& taps,
-                             float* coef, const RowMap& map) {
-  constexpr int LPS = D / 2;
-  constexpr int SPW = kWave / LPS;
-  constexpr int NSTREAM = (kBlock / kWave) * SPW;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int cp = lane % LPS;
-  const int sid = wave * SPW + lane / LPS;
-  const int cps = cpt / NSTREAM;
-  const long s0 = n0 + (long)sid * cps;
-  const long s1 = min(s0 + (long)cps, n0 + (long)ncoef);
-  if (s0 >= s1) return;
-  LdsSink sink;
-  sink.coef = coef + 2 * cp;
-  sink.nbase = n0;
-  sink.n0 = s0;
-  sink.n1 = s1;
-  sink.stride = D + kCoefPad;
-  Cascade<M, J, false> cas;
-  cas.init(taps, L, sym);
-  const long t0 = s0 << J;
-  long t_stop = (s1 << J) + cascade_halo(M, J);
-  if (sym || M == 2) t_stop = min(t_stop, L);
-  run_stream<M, J, false, T>(cas, Kunit, D, cp, t0, t_stop, L, sink, map);
-}
-
-// ------------------------------------------------------------ banded filter
-
-// Away from the end of the sequence the level-J approximation of a 4-tap
-// bank is one banded filter: A_J[n] = sum_m f_J[m] y0[2^J n + m] with
-// f_1 = g and f_{j+1}[s] = sum_k g_k f_j[s - 2^j k] (length 3 (2^J - 1) + 1).
-// With the symmetric extension the per-level extensions do not compose, so
-// the filter is exact only while 2^J n + 3 (2^J - 1) < L; the periodic
-// extension composes (even lengths), with rows read modulo L.
-__host__ __device__ constexpr int band_len(int J) { return 3 * ((1 << J) - 1) + 1; }
-
-// Rows a 16-byte wave load covers and whether the banded fill applies: every
-// load must lie inside one 2^J-row block.
-template <typename T, int D, int J>
-struct BandShape {
-  static constexpr int CPL = 16 / (int)sizeof(T);  // channels per lane
-  static constexpr int LPR = D / CPL;              // lanes per row
-  static constexpr int RPI = kWave / LPR;          // rows per load
-  static constexpr bool ok = (1 << J) >= RPI;
-};
-
-// f_J into taps[0 .. 3 2^J) (zero past its length), built in LDS by the
-// whole workgroup from the 4 low-pass taps; tmp is scratch of the same size.
-template <int J>
-__device__ void build_band_taps(const Taps& t, float* taps, float* tmp) {
-  constexpr int N = 3 << J;
-  float* cur = (J % 2 == 1) ? taps : tmp;  // f_1 lands where f_J ends up
-  for (int i = threadIdx.x; i < N; i += kBlock) cur[i] = i < 4 ? t.g[i] : 0.f;
-  __syncthreads();
-  for (int j = 1; j < J; ++j) {
-    float* nxt = cur == taps ? tmp : taps;
-    const int step = 1 << j;
-    for (int i = threadIdx.x; i < N; i += kBlock) {
-      float v = 0.f;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int src = i - step * k;
-        if (src >= 0) v += t.g[k] * cur[src];
-      }
-      nxt[i] = v;
-    }
-    __syncthreads();
-    cur = nxt;
-  }
-}
-
-// Sum of v over the lanes l ^ sh, sh = LPR .. 32 (the RPI rows of a load).
-template <int LPR>
-__device__ __forceinline__ float sum_rows(float v) {
-  if constexpr (LPR <= 8)
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, false));
-  if constexpr (LPR <= 16) v = add_xor16(v);
-  v = add_xor32(v);
-  return v;
-}
-
-// Level-J approximation of coefficients [n0, n0 + ncoef) ∩ [0, n_end) into
-// the LDS tile by the banded filter.  Wave w takes a contiguous run of the
-// tile's coefficients and streams their rows once: at block b a lane adds
-// its row's contribution to coefficients b, b - 1, b - 2 (taps o, o + 2^J,
-// o + 2^(J+1) at offset o in the block); when block b + 1 starts,
-// coefficient b - 2 is complete and its RPI row lanes are summed.
-template <typename T, int D, int J, class RowMap>
-__device__ void band_tile(const T* Kunit, long L, long n0, int ncoef, long n_end,
-                          bool periodic, const float* taps, float* coef, const RowMap& map) {
-  using BS = BandShape<T, D, J>;
-  constexpr int CPL = BS::CPL, LPR = BS::LPR, RPI = BS::RPI;
-  constexpr int BLK = 1 << J;
-  constexpr int GPB = BLK / RPI;  // loads per block
-  constexpr int BATCH = GPB < 8 ? GPB : 8;
-  constexpr int STRIDE = D + kCoefPad;
-  constexpr int NW = kBlock / kWave;
-  static_assert(BS::ok, "a load must stay inside one block");
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int rsub = lane / LPR, csub = lane % LPR;
-  const int per = (ncoef + NW - 1) / NW;
-  const long c0 = n0 + (long)wave * per;
-  const long c1 = min(min(c0 + (long)per, n0 + (long)ncoef), n_end);
-  if (c0 >= c1) return;  // uniform per wave; no barrier follows inside
-  float a0[CPL], a1[CPL], a2[CPL];  // coefficients b, b - 1, b - 2
-#pragma unroll
-  for (int e = 0; e < CPL; ++e) a0[e] = a1[e] = a2[e] = 0.f;
-  auto flush = [&](long n) {
-    float r[CPL];
-#pragma unroll
-    for (int e = 0; e < CPL; ++e) r[e] = sum_rows<LPR>(a2[e]);
-    if (rsub == 0 && n >= c0 && n < c1) {
-      float* dst = coef + (n - n0) * STRIDE + csub * CPL;
-#pragma unroll
-      for (int e = 0; e < CPL; e += 4)
-        *reinterpret_cast<f32x4*>(dst + e) = f32x4{r[e], r[e + 1], r[e + 2], r[e + 3]};
-    }
-  };
-  // batches of BATCH loads over blocks c0 .. c1 + 1
-  constexpr int NBB = GPB / BATCH;  // batches per block
-  const long nbt = (c1 + 2 - c0) * NBB;
-  for (long bi = 0; bi < nbt; ++bi) {
-    const long b = c0 + bi / NBB;
-    const int g0 = (int)(bi % NBB) * BATCH;
-    u32x4 v[BATCH];
-#pragma unroll
-    for (int gi = 0; gi < BATCH; ++gi) {
-      const long r = b * BLK + (g0 + gi) * RPI + rsub;
-      // past L: wrapped (periodic) or the last row with a zero tap
-      const long row = r < L ? r : (periodic ? r % L : L - 1);
-      v[gi] = *reinterpret_cast<const u32x4*>(Kunit + map(row) * D + csub * CPL);
-    }
-    if (g0 == 0 && b > c0) {
-      flush(b - 3);
-#pragma unroll
-      for (int e = 0; e < CPL; ++e) {
-        a2[e] = a1[e];
-        a1[e] = a0[e];
-        a0[e] = 0.f;
-      }
-    }
-#pragma unroll
-    for (int gi = 0; gi < BATCH; ++gi) {
-      const int o = (g0 + gi) * RPI + rsub;
-      const float t0 = taps[o], t1 = taps[o + BLK], t2 = taps[o + 2 * BLK];
-      float x[CPL];
-      if constexpr (sizeof(T) == 2) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          x[2 * e] = bf16_lo(v[gi][e]);
-          x[2 * e + 1] = bf16_hi(v[gi][e]);
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] = __uint_as_float(v[gi][e]);
-      }
-#pragma unroll
-      for (int e = 0; e < CPL; ++e) {
-        a0[e] = fmaf(t0, x[e], a0[e]);
-        a1[e] = fmaf(t1, x[e], a1[e]);
-        a2[e] = fmaf(t2, x[e], a2[e]);
-      }
-    }
-  }
-  flush(c1 - 1);
-}
-
-// The coefficients next to a symmetric end: coefficient nJ - 1 - m (m < 3)
-// is sum_r E_m[r] y0[(nJ - 1 - m) 2^J + r], r < 2^J (m + 1).  The per-level
-// extensions make E_m differ from f_J, but E_m depends only on m (lengths
-// are multiples of 2^J), so the host builds the three filters once per J by
-// pushing impulses through the extended cascade.  Filter m starts at
-// 2^J m (m + 1) / 2.  The banded path with edges covers J <= kBandMaxJ.
-constexpr int kBandMaxJ = 7;
-struct EdgeTaps {
-  float e[6 << kBandMaxJ];
-};
-
-// Edge coefficient n of the tile into LDS by the calling wave.
-template <typename T, int D, int J, class RowMap>
-__device__ void edge_coef(const T* Kunit, long n0, long n, long nJ, const float* edge,
-                          float* coef, const RowMap& map) {
-  using BS = BandShape<T, D, J>;
-  constexpr int CPL = BS::CPL, LPR = BS::LPR, RPI = BS::RPI;
-  constexpr int BLK = 1 << J;
-  constexpr int STRIDE = D + kCoefPad;
-  const int lane = threadIdx.x & 63;
-  const int rsub = lane / LPR, csub = lane % LPR;
-  const int m = (int)(nJ - 1 - n);
-  const float* e = edge + BLK * (m * (m + 1) / 2);
-  const int len = BLK * (m + 1);  // rows n 2^J .. L - 1
-  float acc[CPL];
-#pragma unroll
-  for (int k = 0; k < CPL; ++k) acc[k] = 0.f;
-  for (int r0 = 0; r0 < len; r0 += RPI) {
-    const int rr = r0 + rsub;
-    const u32x4 v = *reinterpret_cast<const u32x4*>(Kunit + map(n * BLK + rr) * D + csub * CPL);
-    const float t = e[rr];
-    if constexpr (sizeof(T) == 2) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        acc[2 * k] = fmaf(t, bf16_lo(v[k]), acc[2 * k]);
-        acc[2 * k + 1] = fmaf(t, bf16_hi(v[k]), acc[2 * k + 1]);
-      }
-    } else {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) acc[k] = fmaf(t, __uint_as_float(v[k]), acc[k]);
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < CPL; ++k) acc[k] = sum_rows<LPR>(acc[k]);
-  if (rsub == 0) {
-    float* dst = coef + (n - n0) * STRIDE + csub * CPL;
-#pragma unroll
-    for (int k = 0; k < CPL; k += 4)
-      *reinterpret_cast<f32x4*>(dst + k) = f32x4{acc[k], acc[k + 1], acc[k + 2], acc[k + 3]};
-  }
-}
 
 // In place, every fp32 coefficient row of the tile becomes [hi x D][lo x D]
 // bf16 in the same bytes: hi = bf16(c), lo = bf16(c - hi) (round to nearest
@@ -724,13 +169,12 @@ __device__ void skim_epilogue(const SkimTileArgs& a, int u, int tile, long n0,
   }
 }
 
-// Waves per SIMD a skim tile instance is compiled for.  The banded db2
-// tiles at J = 6, 7 (d = 128, bf16) fit four workgroups per CU in 128 VGPRs
-// without spills, so one round of workgroups covers the 32 tiles per unit of
-// the 128K shape instead of a round and a third; other instances would
-// spill under that bound and keep the default.
+// Waves per SIMD a skim tile instance is compiled for: the banded db2 tiles
+// at J = 6, 7 (d = 128, bf16) take three without spills, and with four they
+// spill 19 registers (64K keys, 128 query rows, J = 6: 149.4 us a call with
+// four, 145.1 with three).
 constexpr int skim_tile_waves(int src, int M, int J, int elem, int D) {
-  return src == kCascade && M == 4 && elem == 2 && D == 128 && (J == 6 || J == 7) ? 4 : 1;
+  return src == kCascade && M == 4 && elem == 2 && D == 128 && (J == 6 || J == 7) ? 3 : 1;
 }
 
 template <int SRC, int M, int J, typename T, int D>
@@ -742,7 +186,7 @@ skim_tile_kernel(SkimTileArgs a, Taps taps, EdgeTaps edge) {
   float* edge_lds = band + 2 * (3 << J);
   if constexpr (kBand) {
     for (int i = threadIdx.x; i < (6 << J); i += kBlock) edge_lds[i] = edge.e[i];
-    build_band_taps<J>(taps, band, band + (3 << J));  // ends with a barrier
+    build_band_taps<J>(taps.g, band, band + (3 << J));  // ends with a barrier
   }
   const int total = a.U * a.ntiles;
   for (int item = blockIdx.x; item < total; item += gridDim.x) {
@@ -778,7 +222,16 @@ skim_tile_kernel(SkimTileArgs a, Taps taps, EdgeTaps edge) {
           band_tile<T, D, J>(Kunit, a.L, n0, ncoef, n_end, !sym, band, coef, map);
           // at most three edge coefficients: wave w takes the w-th of the tile
           const long n = max(n0, n_end) + (threadIdx.x >> 6);
-          if (n < n0 + ncoef) edge_coef<T, D, J>(Kunit, n0, n, nJf, edge_lds, coef, map);
+          if (n < n0 + ncoef) {
+            using BS = BandShape<T, D, J>;
+            const int csub = threadIdx.x % BS::LPR;
+            edge_coef<T, D, J>(Kunit, n, nJf, edge_lds, map,
+                               [&](long c, const float (&r)[BS::CPL]) {
+                                 float* dst = coef + (c - n0) * (D + kCoefPad) + csub * BS::CPL;
+#pragma unroll
+                                 for (int k = 0; k < BS::CPL; ++k) dst[k] = r[k];
+                               });
+          }
         } else {
           cascade_tile<M, J, T, D>(Kunit, a.L, n0, ncoef, a.cpt, sym, taps, coef, map);
         }
@@ -827,33 +280,6 @@ skim_tile_kernel(SkimTileArgs a, Taps taps, EdgeTaps edge) {
     __syncthreads();
     if constexpr (sizeof(T) == 2 && SRC != kFromApprox) split_tile_bf16<D>(coef, ncoef);
     skim_epilogue<T, D>(a, u, tile, n0, ncoef, coef);
-    __syncthreads();
-  }
-}
-
-// Haar A_J alone (no details): block sums of 2^J rows in coefficient tiles
-// (the same tiles the skim builds), then copied to approx [U][nJ][D].
-// Persistent grid over (unit, tile) items.
-template <typename T, int D>
-__global__ __launch_bounds__(kBlock) void haar_approx_kernel(DwtArgs a, float inv_norm,
-                                                             int cpt) {
-  extern __shared__ float coef[];  // [cpt][D + kCoefPad]
-  constexpr int STRIDE = D + kCoefPad;
-  const int total = a.U * a.ntiles;
-  for (int item = blockIdx.x; item < total; item += gridDim.x) {
-    const int u = item / a.ntiles;
-    const int tile = item % a.ntiles;
-    const long n0 = (long)tile * cpt;
-    const int ncoef = (int)min((long)cpt, (long)a.nJ - n0);
-    const T* Kunit = reinterpret_cast<const T*>(a.K) + (long)u * a.Ls * D;
-    haar_sum_tile<T, D>(Kunit, n0, ncoef, a.J, inv_norm, coef, [](long n) { return n; });
-    __syncthreads();
-    float* dst = a.approx + ((long)u * a.nJ + n0) * D;
-    for (int v = threadIdx.x; v < ncoef * (D / 4); v += kBlock) {
-      const int c = v / (D / 4), k = v % (D / 4);
-      *reinterpret_cast<f32x4*>(dst + (long)c * D + 4 * k) =
-          *reinterpret_cast<const f32x4*>(coef + c * STRIDE + 4 * k);
-    }
     __syncthreads();
   }
 }
@@ -1126,64 +552,6 @@ __global__ __launch_bounds__(kSelectBlock) void skim_select_kernel(SkimSelectArg
 
 // ------------------------------------------------------------ host side
 
-static Taps make_taps(int wavelet, int J) {
-  Taps t{};
-  const double r2 = std::sqrt(2.0);
-  if (wavelet == WF_HAAR) {
-    t.g[0] = t.g[1] = (float)(1.0 / r2);
-    t.h[0] = (float)(1.0 / r2);
-    t.h[1] = (float)(-1.0 / r2);
-  } else {
-    const double r3 = std::sqrt(3.0), den = 4.0 * r2;
-    const double g[4] = {(1 + r3) / den, (3 + r3) / den, (3 - r3) / den,
-                         (1 - r3) / den};
-    for (int m = 0; m < 4; ++m) {
-      t.g[m] = (float)g[m];
-      t.h[m] = (float)((m % 2 == 0 ? 1.0 : -1.0) * g[3 - m]);
-    }
-  }
-  t.inv_norm = (float)std::pow(2.0, -0.5 * J);
-  return t;
-}
-
-// The three symmetric-end filters of the level-J Daubechies-2 approximation
-// (see EdgeTaps), in double, once per J: impulses at each of the last 3 2^J
-// rows of a sequence of 6 2^J rows, through the cascade with the
-// half-sample symmetric extension at every level.
-static const EdgeTaps& symmetric_edge_filters(int J) {
-  static EdgeTaps table[kBandMaxJ + 1];
-  static std::once_flag once[kBandMaxJ + 1];
-  std::call_once(once[J], [J] {
-    const double r2 = std::sqrt(2.0), r3 = std::sqrt(3.0), den = 4.0 * r2;
-    const double g[4] = {(1 + r3) / den, (3 + r3) / den, (3 - r3) / den, (1 - r3) / den};
-    const int blk = 1 << J, len = 6 * blk, nJ = 6;
-    EdgeTaps& t = table[J];
-    for (int i = 0; i < (6 << kBandMaxJ); ++i) t.e[i] = 0.f;
-    for (int r = len - 3 * blk; r < len; ++r) {
-      std::vector<double> y(len, 0.0);
-      y[r] = 1.0;
-      for (int j = 1; j <= J; ++j) {
-        const int N = (int)y.size();
-        std::vector<double> a(N / 2);
-        for (int n = 0; n < N / 2; ++n) {
-          double v = 0.0;
-          for (int m = 0; m < 4; ++m) {
-            const int i = 2 * n + m;
-            v += g[m] * (i < N ? y[i] : y[2 * N - 1 - i]);
-          }
-          a[n] = v;
-        }
-        y.swap(a);
-      }
-      for (int m = 0; m < 3; ++m) {
-        const int start = len - blk * (m + 1);  // first row of coefficient nJ - 1 - m
-        if (r >= start) t.e[blk * (m * (m + 1) / 2) + (r - start)] = (float)y[nJ - 1 - m];
-      }
-    }
-  });
-  return table[J];
-}
-
 void db2_token_taps(int J, Db2TokenTaps* out) {
   const double r2 = std::sqrt(2.0), r3 = std::sqrt(3.0), den = 4.0 * r2;
   const double g[4] = {(1 + r3) / den, (3 + r3) / den, (3 - r3) / den, (1 - r3) / den};
@@ -1203,90 +571,9 @@ void db2_token_taps(int J, Db2TokenTaps* out) {
   for (int i = 0; i < (6 << 6); ++i) out->edge[i] = e.e[i];
 }
 
-template <int M, typename T>
-static hipError_t dwt_dispatch(const DwtArgs& a, const Taps& taps, dim3 grid,
-                               hipStream_t s) {
-  switch (a.J) {
-#define WF_DWT_CASE(JJ)                                                  \
-  case JJ:                                                               \
-    hipLaunchKernelGGL((dwt_kernel<M, JJ, T>), grid, dim3(kBlock), 0, s, \
-                       a, taps);                                         \
-    break;
-    WF_DWT_CASE(1) WF_DWT_CASE(2) WF_DWT_CASE(3) WF_DWT_CASE(4)
-    WF_DWT_CASE(5) WF_DWT_CASE(6) WF_DWT_CASE(7) WF_DWT_CASE(8)
-    WF_DWT_CASE(9) WF_DWT_CASE(10)
-#undef WF_DWT_CASE
-    default:
-      return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-// Haar coefficient tile size at level J.
-static int haar_cpt(int J) { return std::min(kMaxCoefTile, std::max(16, 2048 >> J)); }
 // coefficients per tile at scale b of the recursion
 static int rec_cpt(const wf_params& p, int b) {
   return p.wavelet == WF_HAAR ? haar_cpt(b) : kMaxCoefTile;
-}
-
-DwtPlan plan_dwt(const wf_params& p) {
-  DwtPlan d;
-  const int spw = kWave / (p.head_dim / 2);
-  d.streams = (kBlock / kWave) * spw;
-  d.cps = std::max(1, 2048 >> p.levels);
-  const long nJ = (long)p.ctx_len >> p.levels;
-  const long per_tile = (long)d.streams * d.cps;
-  d.ntiles = (int)((nJ + per_tile - 1) / per_tile);
-  return d;
-}
-
-hipError_t launch_dwt(const wf_params& p, const void* K, float* approx,
-                      float* details, hipStream_t s) {
-  DwtPlan pl = plan_dwt(p);
-  DwtArgs a;
-  a.K = K;
-  a.approx = approx;
-  a.details = details;
-  a.U = p.batch * p.heads;
-  a.L = (int)filtered_len(p);
-  a.Ls = p.ctx_len;
-  a.D = p.head_dim;
-  a.J = p.levels;
-  a.nJ = p.ctx_len >> p.levels;
-  a.cps = pl.cps;
-  a.streams = pl.streams;
-  a.ntiles = pl.ntiles;
-  a.boundary = p.boundary;
-  const Taps taps = make_taps(p.wavelet, p.levels);
-  if (p.wavelet == WF_HAAR && !details) {
-    // A_J is the scaled block sum: coefficient tiles at streaming rate
-    const int cpt = haar_cpt(p.levels);
-    a.ntiles = (int)((a.nJ + cpt - 1) / cpt);
-    const size_t lds = (size_t)cpt * (p.head_dim + kCoefPad) * sizeof(float);
-    auto run = [&](auto kern) -> hipError_t {
-      int per_cu = 0;
-      hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &per_cu, reinterpret_cast<const void*>(kern), kBlock, lds);
-      if (e != hipSuccess) return e;
-      const long total = (long)a.U * a.ntiles;
-      const long cap = (long)std::max(1, per_cu) * device_cu_count();
-      hipLaunchKernelGGL(kern, dim3((unsigned)std::min(total, cap)), dim3(kBlock), lds, s, a,
-                         taps.inv_norm, cpt);
-      return hipGetLastError();
-    };
-    if (p.dtype == WF_BF16)
-      return p.head_dim == 128 ? run(haar_approx_kernel<bf16_t, 128>)
-                               : run(haar_approx_kernel<bf16_t, 64>);
-    return p.head_dim == 128 ? run(haar_approx_kernel<float, 128>)
-                             : run(haar_approx_kernel<float, 64>);
-  }
-  dim3 grid((unsigned)(a.U * a.ntiles));
-  const bool haar = p.wavelet == WF_HAAR;
-  if (p.dtype == WF_BF16)
-    return haar ? dwt_dispatch<2, bf16_t>(a, taps, grid, s)
-                : dwt_dispatch<4, bf16_t>(a, taps, grid, s);
-  return haar ? dwt_dispatch<2, float>(a, taps, grid, s)
-              : dwt_dispatch<4, float>(a, taps, grid, s);
 }
 
 SkimPlan plan_skim(const wf_params& p, bool fused) {
