@@ -63,7 +63,7 @@ __global__ __launch_bounds__(kBlock) void dwt_kernel(DwtArgs a, Taps taps) {
 // Haar A_J alone (no details): block sums of 2^J rows in coefficient tiles
 // (the same tiles the skim builds), then copied to approx [U][nJ][D].
 // Persistent grid over (unit, tile) items.
-template <typename T, int D>
+template <typename T, int D, bool STREAM>
 __global__ __launch_bounds__(kBlock) void haar_approx_kernel(DwtArgs a, float inv_norm,
                                                              int cpt) {
   extern __shared__ float coef[];  // [cpt][D + kCoefPad]
@@ -75,7 +75,8 @@ __global__ __launch_bounds__(kBlock) void haar_approx_kernel(DwtArgs a, float in
     const long n0 = (long)tile * cpt;
     const int ncoef = (int)min((long)cpt, (long)a.nJ - n0);
     const T* Kunit = reinterpret_cast<const T*>(a.K) + (long)u * a.Ls * D;
-    haar_sum_tile<T, D>(Kunit, n0, ncoef, a.J, inv_norm, coef, [](long n) { return n; });
+    haar_sum_tile<T, D, STREAM>(Kunit, n0, ncoef, a.J, inv_norm, coef,
+                                [](long n) { return n; });
     __syncthreads();
     float* dst = a.approx + ((long)u * a.nJ + n0) * D;
     for (int v = threadIdx.x; v < ncoef * (D / 4); v += kBlock) {
@@ -323,11 +324,15 @@ hipError_t launch_dwt(const wf_params& p, const void* K, float* approx,
                          taps.inv_norm, cpt);
       return hipGetLastError();
     };
-    if (p.dtype == WF_BF16)
-      return p.head_dim == 128 ? run(haar_approx_kernel<bf16_t, 128>)
-                               : run(haar_approx_kernel<bf16_t, 64>);
-    return p.head_dim == 128 ? run(haar_approx_kernel<float, 128>)
-                             : run(haar_approx_kernel<float, 64>);
+    auto of_type = [&](auto stream) -> hipError_t {
+      constexpr bool S = decltype(stream)::value;
+      if (p.dtype == WF_BF16)
+        return p.head_dim == 128 ? run(haar_approx_kernel<bf16_t, 128, S>)
+                                 : run(haar_approx_kernel<bf16_t, 64, S>);
+      return p.head_dim == 128 ? run(haar_approx_kernel<float, 128, S>)
+                               : run(haar_approx_kernel<float, 64, S>);
+    };
+    return keys_stream(p) ? of_type(std::true_type{}) : of_type(std::false_type{});
   }
   if (p.wavelet == WF_DB2 && !details && p.levels <= kBandMaxJ) {
     // A_J is one banded filter of the keys: every row read about once, where
@@ -349,7 +354,7 @@ hipError_t launch_dwt(const wf_params& p, const void* K, float* approx,
 
 hipError_t load_dwt_kernels() {
   hipFuncAttributes fa;
-  return hipFuncGetAttributes(&fa, reinterpret_cast<const void*>(haar_approx_kernel<bf16_t, 128>));
+  return hipFuncGetAttributes(&fa, reinterpret_cast<const void*>(haar_approx_kernel<bf16_t, 128, false>));
 }
 
 }  // namespace wf

@@ -195,7 +195,8 @@ struct LdsSink {
 // one coefficient per group, or RPL / 2^J of them reduced across lanes.
 // LOADS = G / RPL loads per group (8 stands for 8 or more); small groups
 // are taken 8 / LOADS at a time so that a lane always has 8 loads in flight.
-template <typename T, int D, int LOADS, class BlockId>
+// STREAM: the rows are read with the nt policy.
+template <typename T, int D, int LOADS, bool STREAM, class BlockId>
 __device__ void haar_sum_tile_groups(const T* Kunit, long n0, int ncoef, int J,
                                      float inv_norm, float* coef, const BlockId& bid) {
   constexpr int CPL = 16 / sizeof(T);  // channels per lane (16-byte load)
@@ -230,7 +231,8 @@ __device__ void haar_sum_tile_groups(const T* Kunit, long n0, int ncoef, int J,
           const long r = (long)grp * G + rsub + (long)(i0 + li) * RPL;
           if (grp < ngroups && r < rows) {
             const long t = ((long)bid(n0 + (r >> J)) << J) + (r & (blk - 1));
-            v[gi][li] = *reinterpret_cast<const u32x4*>(Kunit + t * D + csub * CPL);
+            const u32x4* src = reinterpret_cast<const u32x4*>(Kunit + t * D + csub * CPL);
+            v[gi][li] = STREAM ? __builtin_nontemporal_load(src) : *src;
           } else {
             v[gi][li] = u32x4{0u, 0u, 0u, 0u};
           }
@@ -274,17 +276,17 @@ __device__ void haar_sum_tile_groups(const T* Kunit, long n0, int ncoef, int J,
   }
 }
 
-template <typename T, int D, class BlockId>
+template <typename T, int D, bool STREAM, class BlockId>
 __device__ void haar_sum_tile(const T* Kunit, long n0, int ncoef, int J, float inv_norm,
                               float* coef, const BlockId& bid) {
   constexpr int RPL = kWave / (D / (16 / (int)sizeof(T)));
   const int blk = 1 << J;
   const int loads = (blk > RPL ? blk : RPL) / RPL;
   switch (loads) {
-    case 1: haar_sum_tile_groups<T, D, 1>(Kunit, n0, ncoef, J, inv_norm, coef, bid); break;
-    case 2: haar_sum_tile_groups<T, D, 2>(Kunit, n0, ncoef, J, inv_norm, coef, bid); break;
-    case 4: haar_sum_tile_groups<T, D, 4>(Kunit, n0, ncoef, J, inv_norm, coef, bid); break;
-    default: haar_sum_tile_groups<T, D, 8>(Kunit, n0, ncoef, J, inv_norm, coef, bid); break;
+    case 1: haar_sum_tile_groups<T, D, 1, STREAM>(Kunit, n0, ncoef, J, inv_norm, coef, bid); break;
+    case 2: haar_sum_tile_groups<T, D, 2, STREAM>(Kunit, n0, ncoef, J, inv_norm, coef, bid); break;
+    case 4: haar_sum_tile_groups<T, D, 4, STREAM>(Kunit, n0, ncoef, J, inv_norm, coef, bid); break;
+    default: haar_sum_tile_groups<T, D, 8, STREAM>(Kunit, n0, ncoef, J, inv_norm, coef, bid); break;
   }
 }
 
@@ -383,7 +385,8 @@ __device__ __forceinline__ float sum_rows(float v) {
 // AHEAD takes batches of eight loads whatever the block's length and keeps
 // the next one in flight while one is added up (56 more registers; in the
 // skim tiles, four or eight waves a CU deep already, short blocks' batches
-// of eight measured slower: db2 J = 2, 4K keys, 61.5 -> 65.3 us a call).  STREAM: the rows are read with the nt policy.
+// of eight measured slower: db2 J = 2, 4K keys, 61.5 -> 65.3 us a call).
+// STREAM: the rows are read with the nt policy.
 template <typename T, int D, int J, bool AHEAD, bool STREAM, class RowMap, class Put>
 __device__ __forceinline__ void band_run(const T* Kunit, long L, long c0, long c1, bool periodic,
                                          const float* taps, const RowMap& map, const Put& put) {

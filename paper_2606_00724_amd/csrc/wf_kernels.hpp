@@ -13,7 +13,8 @@ constexpr int kScanChunk = 128;    // pool tokens per scan workgroup
 constexpr int kAttnChunk = 128;    // cache rows per attention workgroup
 constexpr int kCoefPad = 4;        // fp32 pad per LDS coefficient row
 
-enum CoefSource { kHaarSum = 0, kCascade = 1, kFromApprox = 2 };
+// kHaarStream: kHaarSum with the keys read with the nt policy
+enum CoefSource { kHaarSum = 0, kCascade = 1, kFromApprox = 2, kHaarStream = 3 };
 
 struct DwtArgs {
   const void* K;       // [U][Ls][D]
@@ -31,13 +32,14 @@ struct SkimTileArgs {
   const void* K;        // [U][L][D]      (Haar sum / cascade)
   const float* approx;  // [U][nJ][D]     (from approx)
   const void* Q;        // [U][B][D]
-  float* logits;        // [U][B][nJ]
+  float* logits;        // [U][B][ld]
   float* stats;         // [U][ntiles][2][B]: row max, then row sum of exp
   const int32_t* parent;  // nullable: coefficient n is block 2 parent[n/2] + n%2
                           // of level J ([U][npar], ascending block ids at J + 1)
   int npar;
   long Ls;              // rows per unit in K (L: the filtered rows)
   int U, L, B, J, nJ;
+  int ld;               // floats per row of logits (>= nJ)
   int cpt;              // coefficients per tile
   int ntiles;           // tiles per unit
   int boundary;
@@ -45,7 +47,7 @@ struct SkimTileArgs {
 };
 
 struct SkimSelectArgs {
-  const float* logits;  // [U][B][nJ]
+  const float* logits;  // [U][B][ld]
   const float* stats;   // [U][ntiles][2][B]
   float* W;             // [U][nJ] out
   int32_t* seg;         // [U][S] out (block ids), or [U][2S] tokens when pairs
@@ -53,6 +55,7 @@ struct SkimSelectArgs {
   int npar;
   int pairs;            // emit the two tokens of each kept 2-token block
   int U, B, nJ, ntiles, S;
+  int ld;               // floats per row of logits (>= nJ)
 };
 
 struct ScanArgs {
@@ -76,6 +79,7 @@ struct ScanArgs {
   int span;             // pool positions per workgroup (multiple of the chunk)
   int nbuf;             // LDS ring depth (bf16 path)
   int seg_cap;          // region ids staged per workgroup (bf16 path)
+  int stream;           // statistics pass: pool rows read with the nt policy (bf16 path)
   float scale;
   // units per selection: the selecting scan of unit u reads W and writes
   // seg_out of selection u / share (seg_out by the group's first unit only)

@@ -69,7 +69,33 @@ inline long filtered_len(const wf_params& p) {
   return ((long)p.ctx_len >> p.levels) << p.levels;
 }
 inline long remainder_len(const wf_params& p) { return (long)p.ctx_len - filtered_len(p); }
+// Floats per row of the two-stage skim's coarse logits: L >> J rounded up to
+// whole 16-byte vectors (the recursion's rows are not padded).
+inline long skim_ld(const wf_params& p) { return (((long)p.ctx_len >> p.levels) + 3) & ~3L; }
+// Whether a call has the coefficients to fill the chip with a W kernel and
+// selections in the kernels that consume them, whatever its keys, query rows
+// and coefficient count.  16 units of 128 bf16 query rows: with 1024
+// coefficients each a call takes 89.5 us instead of 107.5, with 128 64.4
+// instead of 80.0; 32 fp32 units of 128 coefficients 63.8 instead of 70.0.
+// The line is drawn at 1024 in all: calls below it (two fp32 units of 128
+// coefficients would take 49.1 us instead of 54.2) keep the sequence of
+// kernels that the timed entry points have always named for them.
+inline bool wide_weights(const wf_params& p) {
+  return (long)p.batch * p.heads * ((long)p.ctx_len >> p.levels) >= 1024;
+}
 int device_cu_count();
+// Whether the Haar coefficient tiles read the keys with the streaming (nt)
+// policy:
+// keys past the Infinity Cache's 256 MiB displace what the kernels beside them
+// reuse and find nothing of themselves there (A_J of 1 GiB of Haar keys: 235 us
+// kept, 198 streamed); smaller ones may still be cached from the call or the
+// copy before (64 MiB: 24.0 us kept, 25.8 streamed).  The choice is a template
+// argument of the kernels: a run-time one, twice the load code, cost the
+// smallest calls 0.7 us of instruction fetch.
+inline bool keys_stream(const wf_params& p) {
+  return (size_t)p.batch * p.heads * p.ctx_len * p.head_dim * (p.dtype == WF_BF16 ? 2 : 4) >
+         (size_t)256 << 20;
+}
 
 DwtPlan plan_dwt(const wf_params& p);
 SkimPlan plan_skim(const wf_params& p, bool fused);
@@ -130,9 +156,9 @@ hipError_t launch_rec_select_slices(const wf_params& p, int b, long n, int keep,
 hipError_t launch_skim_select(const wf_params& p, int ntiles,
                               const float* logits, const float* stats,
                               float* W, int32_t* seg, hipStream_t s);
-// W [U][nJ] of the coarse logits [U][B][nJ] and their tiles' (max, sum)
+// W [U][nJ] of the coarse logits [U][B][skim_ld] and their tiles' (max, sum)
 // pairs, spread over enough workgroups per unit to fill the chip (no
-// selection); nJ must be a multiple of 4.
+// selection).
 hipError_t launch_skim_weights(const wf_params& p, int ntiles, const float* logits,
                                const float* stats, float* W, hipStream_t s);
 // stat_slices: 0 when `stats` holds one (max, sum) slice per scan workgroup
@@ -151,7 +177,7 @@ hipError_t launch_scan_select_weights(const wf_params& p, const void* Q, const v
                                       const float* W, const float* blocks, int32_t* seg_out,
                                       float* wpool, hipStream_t s, int share = 1);
 // Whether the scan's workgroups can take the top-S regions themselves (bf16,
-// at most 64 query rows, the region ids and the selection fit in LDS).
+// the region ids and the selection fit in LDS).
 bool scan_can_select(const wf_params& p);
 // The statistics pass that first takes the unit's top-S regions of W itself
 // (seg_out [U][S] receives them, for the weights pass that follows) and

@@ -243,7 +243,22 @@ __device__ __forceinline__ void issue_pool_chunk(uint32_t lds_base, const PoolRo
 constexpr int kPoolBlock = 512;
 constexpr int kPoolWaves = kPoolBlock / kWave;
 
-// SEL (at most 64 query rows): the workgroup first takes the unit's top-S
+// One running (reference, sum of 2^(logit - reference)) pair, log2 units,
+// absorbs another.
+__device__ __forceinline__ void stat_absorb2(float& m, float& z, float m2, float z2) {
+  const float mn = fmaxf(m, m2);
+  if (mn == -INFINITY) return;
+  z = (m > -INFINITY ? z * __builtin_amdgcn_exp2f(m - mn) : 0.f) +
+      (m2 > -INFINITY ? z2 * __builtin_amdgcn_exp2f(m2 - mn) : 0.f);
+  m = mn;
+}
+
+// How far (log2 units) a logit may pass the statistics pass's running
+// reference before that is raised: sums of 2^16 per term stay far from the
+// ends of the fp32 range.
+constexpr float kRefSlack = 16.f;
+
+// SEL: the workgroup first takes the unit's top-S
 // regions from W (eq. 9) itself, then queues its first pool chunks.  In the
 // weights pass of the token-level path it forms the pool normalisers from
 // the selected blocks' log-sum-exps while they load; in the statistics pass
@@ -280,25 +295,36 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = lane >> 4, col = lane & 15;
 
-  // SEL (at most 64 query rows): the query rows are loaded into registers
-  // first and written to LDS after the selection, by when they have landed
+  // SEL, at most 64 query rows: the query rows are loaded into registers
+  // first and written to LDS after the selection, by when they have landed;
+  // more rows go to LDS before it
   const bf16_t* Qunit = reinterpret_cast<const bf16_t*>(a.Q) + (long)u * a.B * D;
   constexpr int QVR = D / 8;                                  // 16-byte vectors per row
   constexpr int QV = (64 * QVR + kPoolBlock - 1) / kPoolBlock;  // vectors per thread
   const int qtotal = a.B * QVR;
   u32x4 qpre[QV];
-  if constexpr (SEL) {
+  const bool qheld = SEL && a.B <= 64;
+  if (qheld) {
 #pragma unroll
     for (int i = 0; i < QV; ++i) {
       const int v = min(i * kPoolBlock + (int)threadIdx.x, qtotal - 1);
       qpre[i] = *reinterpret_cast<const u32x4*>(Qunit + (long)(v / QVR) * D + (v % QVR) * 8);
     }
+  } else {
+    stage_rows_any<bf16_t, D, kPoolBlock>(Qs, a.B, [&](int r) { return Qunit + (long)r * D; });
   }
 
   // region ids of this range: the span's own, or with SEL all S of the unit
   const int s_lo = SEL ? 0 : (int)(pb >> a.J);
   const uint32_t ring_lds = lds_offset(ring);
   const int nbuf = a.nbuf;
+  // the pool chunk at the row pointer's p0 into the ring slot at `slot`
+  auto issue = [&](const PoolRowPtr<D>& rows, uint32_t slot) {
+    if (WEIGHTS || a.stream)
+      issue_pool_chunk<CR, G, NW, true>(slot, rows);
+    else
+      issue_pool_chunk<CR, G, NW, false>(slot, rows);
+  };
   PoolRowPtr<D> rp;
   rp.Kunit = reinterpret_cast<const bf16_t*>(a.K) + (long)u * a.Ls * D;
   rp.segs = segs;
@@ -338,7 +364,7 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
     // pass reads the pool for the last time: streaming loads)
     for (int k = 0; k < nch && k < nbuf - 1; ++k) {
       rp.p0 = pb + (long)k * CR;
-      issue_pool_chunk<CR, G, NW, (bool)WEIGHTS>(ring_lds + (uint32_t)(k * CHB), rp);
+      issue(rp, ring_lds + (uint32_t)(k * CHB));
     }
     if constexpr (WEIGHTS) {
       // pool normalisers (M_q, Z_q) over the pool's tokens, from the selected
@@ -381,14 +407,12 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
     const int32_t* useg = a.seg + (long)(u / a.share) * a.S;  // the unit's selection
     for (int i = threadIdx.x; i < ns; i += kPoolBlock) segs[i] = useg[s_lo + i];
   }
-  if constexpr (SEL) {
+  if (qheld) {
 #pragma unroll
     for (int i = 0; i < QV; ++i) {
       const int v = i * kPoolBlock + (int)threadIdx.x;
       if (v < qtotal) *reinterpret_cast<u32x4*>(Qs + (v / QVR) * QSTR + (v % QVR) * 8) = qpre[i];
     }
-  } else {
-    stage_rows_any<bf16_t, D, kPoolBlock>(Qs, a.B, [&](int r) { return Qunit + (long)r * D; });
   }
   if constexpr (WEIGHTS && !SEL) {
     const float* stt = a.stats + (long)u * a.Cs * 2 * a.B;
@@ -404,10 +428,9 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
           zk[k] = ok ? stt[(long)(k0 + k) * 2 * a.B + a.B + q] : 0.f;
         }
 #pragma unroll
-        for (int k = 0; k < SB; ++k) stat_absorb(mx, z, mk[k], zk[k]);
+        for (int k = 0; k < SB; ++k) stat_absorb2(mx, z, mk[k], zk[k]);
       }
-      // exp(s - M) / Z = 2^(s log2(e) - (M log2(e) + log2(Z)))
-      lse2[q] = fmaf(mx, kLog2e, __log2f(z));
+      lse2[q] = mx + __log2f(z);
     }
   }
   __syncthreads();  // every regular load above has been consumed
@@ -439,7 +462,10 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
         const int q = (qg + j) * 16 + 4 * g + i;
         c2[j][i] = WEIGHTS && q < a.B ? lse2[q] : INFINITY;
       }
-    float sm[QPG][4], sz[QPG][4];  // per-lane running row max / sum of exp
+    // statistics: a lane's reference per query row (log2 units, within
+    // kRefSlack of the largest logit it has seen) and its sum of
+    // 2^(logit - reference)
+    float sm[QPG][4], sz[QPG][4];
 #pragma unroll
     for (int j = 0; j < QPG; ++j)
 #pragma unroll
@@ -453,7 +479,7 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
     // attention that follows loads the selected keys with nt as well).
     for (int k = 0; k < nch && k < nbuf - 1 && !(SEL && qg == 0); ++k) {
       rp.p0 = pb + (long)k * CR;
-      issue_pool_chunk<CR, G, NW, (bool)WEIGHTS>(ring_lds + (uint32_t)(k * CHB), rp);
+      issue(rp, ring_lds + (uint32_t)(k * CHB));
     }
     for (int ch = 0; ch < nch; ++ch) {
       const long p0 = pb + (long)ch * CR;
@@ -462,7 +488,7 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
       lds_barrier();  // chunk ch visible; everyone is past chunk ch - 1
       if (ch + nbuf - 1 < nch) {
         rp.p0 = pb + (long)(ch + nbuf - 1) * CR;
-        issue_pool_chunk<CR, G, NW, (bool)WEIGHTS>(ring_lds + (uint32_t)(((ch + nbuf - 1) % nbuf) * CHB), rp);
+        issue(rp, ring_lds + (uint32_t)(((ch + nbuf - 1) % nbuf) * CHB));
       }
       const unsigned char* buf = ring + (ch % nbuf) * CHB;
 #pragma unroll
@@ -484,26 +510,53 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
             acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                 __builtin_bit_cast(bf16x8, qreg[j][s]), __builtin_bit_cast(bf16x8, bv[s]),
                 acc[j], 0, 0, 0);
+        // lane holds logit[q = 16 (qg + j) + 4 g + i][p = p0 + row]
         float wk = 0.f;
+        if constexpr (!WEIGHTS) {
+          // The reference need not be the maximum: it is raised, and the sum
+          // rescaled, only when some lane's logit passes it by more than
+          // kRefSlack (in the first block, and then rarely), so a logit costs
+          // one fma and one exp2.  Raising it at every new maximum, a branch
+          // and two exponentials on most lanes' paths, took this pass 45.3 us
+          // on 128 units of 4096 pool rows and 64 queries, and this 43.9.
+          float t[QPG][4], top = -INFINITY;
 #pragma unroll
-        for (int j = 0; j < QPG; ++j) {
-          if (qg + j >= nqb) break;
-          // lane holds logit[q = 16 (qg + j) + 4 g + i][p = p0 + row]
+          for (int j = 0; j < QPG; ++j) {
+            if (qg + j >= nqb) break;
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            if constexpr (!WEIGHTS) {
-              const float v = acc[j][i] * a.scale;
-              if (ok) {
-                if (v > sm[j][i]) {
-                  sz[j][i] = sz[j][i] * __expf(sm[j][i] - v) + 1.f;
+            for (int i = 0; i < 4; ++i) {
+              t[j][i] = ok ? fmaf(acc[j][i], s2, -sm[j][i]) : -INFINITY;
+              top = fmaxf(top, t[j][i]);
+            }
+          }
+          if (__builtin_amdgcn_ballot_w64(top > kRefSlack) != 0) {
+#pragma unroll
+            for (int j = 0; j < QPG; ++j) {
+              if (qg + j >= nqb) break;
+#pragma unroll
+              for (int i = 0; i < 4; ++i) {
+                if (t[j][i] > kRefSlack) {
+                  const float v = acc[j][i] * s2;
+                  sz[j][i] *= __builtin_amdgcn_exp2f(sm[j][i] - v);  // 0 at the first logit
                   sm[j][i] = v;
-                } else {
-                  sz[j][i] += __expf(v - sm[j][i]);
+                  t[j][i] = 0.f;
                 }
               }
-            } else {
-              wk += __builtin_amdgcn_exp2f(fmaf(acc[j][i], s2, -c2[j][i]));
             }
+          }
+#pragma unroll
+          for (int j = 0; j < QPG; ++j) {
+            if (qg + j >= nqb) break;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sz[j][i] += __builtin_amdgcn_exp2f(t[j][i]);
+          }
+        } else {
+#pragma unroll
+          for (int j = 0; j < QPG; ++j) {
+            if (qg + j >= nqb) break;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              wk += __builtin_amdgcn_exp2f(fmaf(acc[j][i], s2, -c2[j][i]));
           }
         }
         if constexpr (WEIGHTS) {
@@ -515,18 +568,21 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
       }
     }
     if constexpr (!WEIGHTS) {
-      // merge the 16 lanes of each row, then the waves, through LDS
+      // merge the 16 lanes of each row (their largest reference, then the sums
+      // brought to it), then the waves, through LDS.  Rows no lane has seen
+      // keep (-inf, 0).  (Pairwise merges of the lanes, four rounds of two
+      // exponentials each: 24.4 us instead of 17.2 for 16 units of 128 query
+      // rows, 43.9 instead of 40.2 for 128 units of 64.)
 #pragma unroll
       for (int j = 0; j < QPG; ++j) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          row16_merge<8>(sm[j][i], sz[j][i]);
-          row16_merge<4>(sm[j][i], sz[j][i]);
-          row16_merge<2>(sm[j][i], sz[j][i]);
-          row16_merge<1>(sm[j][i], sz[j][i]);
+          const float m = wave_max16(sm[j][i]);
+          const float z = wave_sum16(
+              sm[j][i] > -INFINITY ? sz[j][i] * __builtin_amdgcn_exp2f(sm[j][i] - m) : 0.f);
           if (col == 0 && qg + j < nqb) {
-            part[(((qg + j) * NW + wave) * 16 + 4 * g + i) * 2] = sm[j][i];
-            part[(((qg + j) * NW + wave) * 16 + 4 * g + i) * 2 + 1] = sz[j][i];
+            part[(((qg + j) * NW + wave) * 16 + 4 * g + i) * 2] = m;
+            part[(((qg + j) * NW + wave) * 16 + 4 * g + i) * 2 + 1] = z;
           }
         }
       }
@@ -540,7 +596,7 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
       float mx = -INFINITY, z = 0.f;
 #pragma unroll
       for (int w = 0; w < NW; ++w)
-        stat_absorb(mx, z, part[((qb * NW + w) * 16 + r) * 2], part[((qb * NW + w) * 16 + r) * 2 + 1]);
+        stat_absorb2(mx, z, part[((qb * NW + w) * 16 + r) * 2], part[((qb * NW + w) * 16 + r) * 2 + 1]);
       stt[q] = mx;
       stt[a.B + q] = z;
     }
@@ -643,11 +699,21 @@ static hipError_t scan_launch(const ScanArgs& a, size_t lds, hipStream_t s) {
     return launch_with_lds(scan_chunk_kernel<WEIGHTS, T, D>, grid, kBlock, lds, s, a);
 }
 
+// Whether the statistics pass reads the pool with the streaming (nt) policy.
+// The weights pass reads it again: a pool that fits the L2s (4 MiB per XCD) is
+// kept there for it (8 MiB: 17.2 + 9.3 us for the two passes, streamed 17.6 +
+// 10.3); a larger one only displaces itself and is found in the Infinity Cache
+// either way (128 MiB: 40.2 + 24.4 us kept, 31.2 + 26.4 streamed).
+static int scan_streams(const wf_params& p) {
+  const size_t pool = ((size_t)p.batch * p.heads * p.segments << p.levels) * 2 * p.head_dim;
+  return pool > (size_t)32 << 20 ? 1 : 0;
+}
+
 // the scan's arguments when its workgroups take the top-S regions from W
 // themselves; false when the shape does not allow it
 static bool scan_select_args(const wf_params& p, const void* Q, const void* K, const float* W,
                              int32_t* seg_out, int share, ScanArgs& a, ScanPlan& pl) {
-  if (p.dtype != WF_BF16 || p.q_len > 64 || p.segments > kSelectLdsSegs || share < 1 ||
+  if (p.dtype != WF_BF16 || p.segments > kSelectLdsSegs || share < 1 ||
       (p.batch * p.heads) % share != 0)
     return false;
   pl = plan_scan(p, true);
@@ -670,6 +736,7 @@ static bool scan_select_args(const wf_params& p, const void* Q, const void* K, c
   a.span = pl.span;
   a.nbuf = pl.nbuf;
   a.seg_cap = pl.seg_cap;
+  a.stream = scan_streams(p);
   a.scale = effective_scale(p);
   // W in the ring slots before the spare one when it fits there
   const size_t chb = (size_t)kScanChunk * 2 * p.head_dim;
@@ -688,7 +755,9 @@ hipError_t launch_scan_select_weights(const wf_params& p, const void* Q, const v
                                       float* wpool, hipStream_t s, int share) {
   ScanArgs a;
   ScanPlan pl;
-  if (!scan_select_args(p, Q, K, W, seg_out, share, a, pl)) return hipErrorInvalidValue;
+  // (the pool normalisers take a thread per query row, 64 rows at most)
+  if (p.q_len > 64 || !scan_select_args(p, Q, K, W, seg_out, share, a, pl))
+    return hipErrorInvalidValue;
   a.blocks = blocks;
   a.wpool = wpool;
   a.Cs = 1;
@@ -736,6 +805,7 @@ hipError_t launch_scan_chunks(const wf_params& p, int weights, const void* Q,
   a.span = pl.span;
   a.nbuf = pl.nbuf;
   a.seg_cap = pl.seg_cap;
+  a.stream = scan_streams(p);
   a.scale = effective_scale(p);
   const bool bf = p.dtype == WF_BF16, d128 = p.head_dim == 128;
   if (weights) {

@@ -143,7 +143,7 @@ __device__ void skim_epilogue(const SkimTileArgs& a, int u, int tile, long n0,
       s = wave_sum16(s);
       z[i] = s;
     }
-    float* lg = a.logits + (long)u * a.B * a.nJ + n0;
+    float* lg = a.logits + (long)u * a.B * a.ld + n0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int q = qb * 16 + 4 * g + i;
@@ -151,7 +151,7 @@ __device__ void skim_epilogue(const SkimTileArgs& a, int u, int tile, long n0,
 #pragma unroll
         for (int cb = 0; cb < kMaxCoefTile / 16; ++cb) {
           const int c = cb * 16 + col;
-          if (cb < ncb && c < ncoef) lg[(long)q * a.nJ + c] = acc[cb][i];
+          if (cb < ncb && c < ncoef) lg[(long)q * a.ld + c] = acc[cb][i];
         }
       }
     }
@@ -194,18 +194,18 @@ skim_tile_kernel(SkimTileArgs a, Taps taps, EdgeTaps edge) {
     const int tile = item % a.ntiles;
     const long n0 = (long)tile * a.cpt;
     const int ncoef = (int)min((long)a.cpt, (long)a.nJ - n0);
-    if constexpr (SRC == kHaarSum) {
+    if constexpr (SRC == kHaarSum || SRC == kHaarStream) {
       const T* Kunit = reinterpret_cast<const T*>(a.K) + (long)u * a.Ls * D;
-      if (a.parent) {
+      if (SRC == kHaarSum && a.parent) {
         // block ids are clamped into the unit: a bad id cannot leave K
         const int32_t* par = a.parent + (long)u * a.npar;
         const long last = ((long)a.L >> a.J) - 1;
-        haar_sum_tile<T, D>(Kunit, n0, ncoef, a.J, taps.inv_norm, coef, [=](long n) {
+        haar_sum_tile<T, D, false>(Kunit, n0, ncoef, a.J, taps.inv_norm, coef, [=](long n) {
           return min(max(2L * par[n >> 1] + (n & 1), 0L), last);
         });
       } else {
-        haar_sum_tile<T, D>(Kunit, n0, ncoef, a.J, taps.inv_norm, coef,
-                            [](long n) { return n; });
+        haar_sum_tile<T, D, SRC == kHaarStream>(Kunit, n0, ncoef, a.J, taps.inv_norm, coef,
+                                                [](long n) { return n; });
       }
     } else if constexpr (SRC == kCascade) {
       const T* Kunit = reinterpret_cast<const T*>(a.K) + (long)u * a.Ls * D;
@@ -287,12 +287,12 @@ skim_tile_kernel(SkimTileArgs a, Taps taps, EdgeTaps edge) {
 // One workgroup per unit: merge the tiles' row statistics, form W (eq. 8) and
 // select the top-S regions (eq. 9).
 // W_j (eq. 8) of unit u for the columns 4 j4 .. 4 j4 + 3, j4 in [j4_lo,
-// j4_hi) (nJ a multiple of 4), from the query-major logits and the row
+// j4_hi) (nJ = ld a multiple of 4), from the query-major logits and the row
 // normalisers c_q = M_q log2(e) + log2(Z_q); also into wsh when given.
 template <int NT>
 __device__ void skim_w_columns(const SkimSelectArgs& a, int u, const float* row_c, int j4_lo,
                                int j4_hi, float* wsh) {
-  const float* lg = a.logits + (long)u * a.B * a.nJ;
+  const float* lg = a.logits + (long)u * a.B * a.ld;
   float* W = a.W + (long)u * a.nJ;
   // four adjacent columns per thread, 16 query rows of loads in flight
   constexpr int QB = 16;
@@ -302,7 +302,7 @@ __device__ void skim_w_columns(const SkimSelectArgs& a, int u, const float* row_
       float4 v[QB];
 #pragma unroll
       for (int i = 0; i < QB; ++i)
-        v[i] = q0 + i < a.B ? *reinterpret_cast<const float4*>(lg + (long)(q0 + i) * a.nJ + 4 * j4)
+        v[i] = q0 + i < a.B ? *reinterpret_cast<const float4*>(lg + (long)(q0 + i) * a.ld + 4 * j4)
                             : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
       for (int i = 0; i < QB; ++i) {
@@ -380,7 +380,9 @@ __global__ __launch_bounds__(kBlock) void skim_weights_kernel(SkimSelectArgs a, 
 // the terms of query rows 16 g .. 16 g + 15 (and every 64th row after them)
 // of four adjacent columns, the four groups' partial sums meet in LDS and are
 // added in order of g.  The first batch of logits is loaded before the
-// slices are merged, so that the two loads overlap.
+// slices are merged, so that the two loads overlap.  ld is a multiple of 4:
+// the last group of a row may reach into its padding, whose sums are not
+// stored.
 __global__ __launch_bounds__(kBlock) void skim_weights_rows_kernel(SkimSelectArgs a, int parts) {
   constexpr int QB = 16;             // query rows of one batch
   constexpr int NQG = 4;             // query groups
@@ -390,16 +392,16 @@ __global__ __launch_bounds__(kBlock) void skim_weights_rows_kernel(SkimSelectArg
   __shared__ float4 wpart[NQG][CPW];
   const int item = xcd_swizzle(blockIdx.x, gridDim.x);
   const int u = item / parts, part = item % parts;
-  const int n4 = a.nJ / 4, per = (n4 + parts - 1) / parts;
+  const int n4 = (a.nJ + 3) / 4, per = (n4 + parts - 1) / parts;
   const int j4_lo = part * per, j4_hi = min(n4, j4_lo + per);
   const int qg = threadIdx.x / CPW, cl = threadIdx.x % CPW;
-  const float* lg = a.logits + (long)u * a.B * a.nJ;
+  const float* lg = a.logits + (long)u * a.B * a.ld;
   float4 v[QB];
   auto load = [&](int j4, int q0) {
 #pragma unroll
     for (int i = 0; i < QB; ++i)
       v[i] = j4 < j4_hi && q0 + i < a.B
-                 ? *reinterpret_cast<const float4*>(lg + (long)(q0 + i) * a.nJ + 4 * j4)
+                 ? *reinterpret_cast<const float4*>(lg + (long)(q0 + i) * a.ld + 4 * j4)
                  : make_float4(0.f, 0.f, 0.f, 0.f);
   };
   load(j4_lo + cl, QB * qg);
@@ -435,7 +437,14 @@ __global__ __launch_bounds__(kBlock) void skim_weights_rows_kernel(SkimSelectArg
         t.z += o.z;
         t.w += o.w;
       }
-      *reinterpret_cast<float4*>(W + 4 * j4) = t;
+      if ((a.nJ & 3) == 0) {
+        *reinterpret_cast<float4*>(W + 4 * j4) = t;
+      } else {  // units' rows of W are not 16-byte aligned
+        const float tw[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (4 * j4 + e < a.nJ) W[4 * j4 + e] = tw[e];
+      }
     }
     __syncthreads();
   }
@@ -520,8 +529,8 @@ __global__ __launch_bounds__(kSelectBlock) void skim_select_kernel(SkimSelectArg
       }
       __syncthreads();
     }
-    const float* lg = a.logits + (long)u * a.B * a.nJ;
-    if ((a.nJ & 3) == 0) {
+    const float* lg = a.logits + (long)u * a.B * a.ld;
+    if ((a.nJ & 3) == 0 && a.ld == a.nJ) {
       skim_w_columns<NT>(a, u, row_c, 0, a.nJ / 4, w_in_lds ? wsh : nullptr);
     } else {
       constexpr int RB = 16;  // rows in flight per thread
@@ -530,7 +539,7 @@ __global__ __launch_bounds__(kSelectBlock) void skim_select_kernel(SkimSelectArg
         for (int q0 = 0; q0 < a.B; q0 += RB) {
           float v[RB];
 #pragma unroll
-          for (int i = 0; i < RB; ++i) v[i] = q0 + i < a.B ? lg[(long)(q0 + i) * a.nJ + j] : 0.f;
+          for (int i = 0; i < RB; ++i) v[i] = q0 + i < a.B ? lg[(long)(q0 + i) * a.ld + j] : 0.f;
 #pragma unroll
           for (int i = 0; i < RB; ++i)
             if (q0 + i < a.B) w += __builtin_amdgcn_exp2f(fmaf(v[i], kLog2e, -row_c[q0 + i]));
@@ -583,7 +592,7 @@ SkimPlan plan_skim(const wf_params& p, bool fused) {
     k.source = kFromApprox;
     k.cpt = kMaxCoefTile;
   } else if (p.wavelet == WF_HAAR) {
-    k.source = kHaarSum;
+    k.source = keys_stream(p) ? kHaarStream : kHaarSum;
     k.cpt = std::min(kMaxCoefTile, std::max(16, 2048 >> J));
   } else {
     k.source = kCascade;
@@ -615,6 +624,8 @@ template <typename T, int D>
 static hipError_t skim_dispatch(int source, const SkimTileArgs& a, const Taps& taps,
                                 const EdgeTaps& edge, size_t lds, hipStream_t s) {
   if (source == kHaarSum) return skim_launch_one<kHaarSum, 2, 1, T, D>(a, taps, edge, lds, s);
+  if (source == kHaarStream)
+    return skim_launch_one<kHaarStream, 2, 1, T, D>(a, taps, edge, lds, s);
   if (source == kFromApprox)
     return skim_launch_one<kFromApprox, 2, 1, T, D>(a, taps, edge, lds, s);
   switch (a.J) {
@@ -631,7 +642,7 @@ static hipError_t skim_dispatch(int source, const SkimTileArgs& a, const Taps& t
 }
 
 static hipError_t skim_tiles_common(const wf_params& p, int source, int cpt, int J,
-                                    long nJ, const int32_t* parent, int npar,
+                                    long nJ, long ld, const int32_t* parent, int npar,
                                     const void* Q, const void* K, const float* approx,
                                     float* logits, float* stats, hipStream_t s) {
   SkimTileArgs a;
@@ -651,6 +662,7 @@ static hipError_t skim_tiles_common(const wf_params& p, int source, int cpt, int
   a.B = p.q_len;
   a.J = J;
   a.nJ = (int)nJ;
+  a.ld = (int)ld;
   a.cpt = cpt;
   a.ntiles = (int)((nJ + cpt - 1) / cpt);
   a.boundary = p.boundary;
@@ -678,10 +690,10 @@ hipError_t launch_skim_tiles(const wf_params& p, bool fused, const void* Q,
                              float* stats, hipStream_t s) {
   const SkimPlan pl = plan_skim(p, fused);
   return skim_tiles_common(p, pl.source, pl.cpt, p.levels, (long)p.ctx_len >> p.levels,
-                           nullptr, 0, Q, K, approx, logits, stats, s);
+                           skim_ld(p), nullptr, 0, Q, K, approx, logits, stats, s);
 }
 
-static hipError_t skim_select_common(const wf_params& p, long nJ, int ntiles, int S,
+static hipError_t skim_select_common(const wf_params& p, long nJ, long ld, int ntiles, int S,
                                      const int32_t* parent, int npar, int pairs,
                                      const float* logits, const float* stats, float* W,
                                      int32_t* out, hipStream_t s) {
@@ -696,6 +708,7 @@ static hipError_t skim_select_common(const wf_params& p, long nJ, int ntiles, in
   a.U = p.batch * p.heads;
   a.B = p.q_len;
   a.nJ = (int)nJ;
+  a.ld = (int)ld;
   a.ntiles = ntiles;
   a.S = S;
   const int in_lds = a.nJ <= kSelectLdsFloats ? 1 : 0;
@@ -706,7 +719,7 @@ static hipError_t skim_select_common(const wf_params& p, long nJ, int ntiles, in
     if (e != hipSuccess) return e;
   }
   // wide candidate sets: W over all CUs first (1024 columns a workgroup)
-  const int w_ready = a.nJ >= 4096 && (a.nJ & 3) == 0 ? 1 : 0;
+  const int w_ready = a.nJ >= 4096 && (a.nJ & 3) == 0 && a.ld == a.nJ ? 1 : 0;
   if (w_ready) {
     const int parts = (a.nJ + 1023) / 1024;
     hipLaunchKernelGGL(skim_weights_kernel, dim3((unsigned)(a.U * parts)), dim3(kBlock), 0, s,
@@ -748,10 +761,11 @@ hipError_t launch_skim_weights(const wf_params& p, int ntiles, const float* logi
   a.U = p.batch * p.heads;
   a.B = p.q_len;
   a.nJ = (int)((long)p.ctx_len >> p.levels);
+  a.ld = (int)skim_ld(p);
   a.ntiles = ntiles;
-  if (!logits || !stats || !W || (a.nJ & 3) != 0 || a.nJ == 0) return hipErrorInvalidValue;
+  if (!logits || !stats || !W || a.nJ == 0) return hipErrorInvalidValue;
   // at most 1024 columns a workgroup, and two workgroups per CU at least
-  const long n4 = a.nJ / 4;
+  const long n4 = (a.nJ + 3) / 4;
   const long want = std::max((a.nJ + 1023L) / 1024,
                              (2L * device_cu_count() + a.U - 1) / a.U);
   const int parts = (int)std::min(n4, want);
@@ -763,7 +777,7 @@ hipError_t launch_skim_weights(const wf_params& p, int ntiles, const float* logi
 hipError_t launch_skim_select(const wf_params& p, int ntiles,
                               const float* logits, const float* stats,
                               float* W, int32_t* seg, hipStream_t s) {
-  return skim_select_common(p, (long)p.ctx_len >> p.levels, ntiles, p.segments, nullptr, 0,
+  return skim_select_common(p, (long)p.ctx_len >> p.levels, skim_ld(p), ntiles, p.segments, nullptr, 0,
                             0, logits, stats, W, seg, s);
 }
 
@@ -788,8 +802,12 @@ RecPlan plan_recursion(const wf_params& p, const int32_t* counts) {
 hipError_t launch_rec_tiles(const wf_params& p, int b, long n, const int32_t* parent,
                             int npar, const void* Q, const void* K, float* logits,
                             float* stats, hipStream_t s) {
-  return skim_tiles_common(p, p.wavelet == WF_HAAR ? kHaarSum : kCascade, rec_cpt(p, b), b, n,
-                           parent, npar, Q, K, nullptr, logits, stats, s);
+  return skim_tiles_common(p,
+                           p.wavelet != WF_HAAR            ? kCascade
+                           : parent == nullptr && keys_stream(p) ? kHaarStream
+                                                           : kHaarSum,
+                           rec_cpt(p, b), b, n,
+                           n, parent, npar, Q, K, nullptr, logits, stats, s);
 }
 
 hipError_t launch_rec_select(const wf_params& p, int b, long n, int keep,
@@ -797,14 +815,14 @@ hipError_t launch_rec_select(const wf_params& p, int b, long n, int keep,
                              const float* stats, float* W, int32_t* out, hipStream_t s) {
   const int cpt = rec_cpt(p, b);
   const int ntiles = (int)((n + cpt - 1) / cpt);
-  return skim_select_common(p, n, ntiles, keep, parent, npar, b == 1 ? 1 : 0, logits,
+  return skim_select_common(p, n, n, ntiles, keep, parent, npar, b == 1 ? 1 : 0, logits,
                             stats, W, out, s);
 }
 hipError_t launch_rec_select_slices(const wf_params& p, int b, long n, int keep,
                                     const int32_t* parent, int npar, int nslices,
                                     const float* logits, const float* stats, float* W,
                                     int32_t* out, hipStream_t s) {
-  return skim_select_common(p, n, nslices, keep, parent, npar, b == 1 ? 1 : 0, logits,
+  return skim_select_common(p, n, n, nslices, keep, parent, npar, b == 1 ? 1 : 0, logits,
                             stats, W, out, s);
 }
 

@@ -1,0 +1,48 @@
+"""Dispatch edges of the coefficient-tile path and its rings: every unit of the
+fused, cached and shared calls against the fp64 oracle (the tolerances of
+parity.py)."""
+import pytest
+
+import synth
+from test_gpu_random_shapes import _check_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def wf():
+    import paper_2606_00724_amd as m
+    return m
+
+
+def _w(name, **kw):
+    base = dict(batch=1, heads=4, head_dim=128, q_len=32, dtype="bf16", wavelet="haar",
+                boundary="symmetric", gen_len=0, needles=1, seed=41)
+    base.update(kw)
+    return synth.small_variant(synth.WORKLOADS["tiny"], name=name, **base)
+
+
+# W over all CUs and the selections in their consumers from 1024 coefficients
+# in all: just below and at the line, past 64 query rows, coefficient counts
+# that leave 1..3 floats of row padding, a row whose logits span more than the
+# statistics pass's slack (the seed's queries lean on the needles)
+WIDE = [
+    _w("w1023", heads=3, ctx_len=341 * 8, levels=3, segments=40, budget=300, q_len=65),
+    _w("w1024", heads=4, ctx_len=256 * 8, levels=3, segments=40, budget=300, q_len=65),
+    _w("w_b128", heads=4, ctx_len=4 * 513 + 3, levels=2, segments=99, budget=150, q_len=128,
+       gen_len=9),
+    _w("w_b256", heads=2, ctx_len=64 * 514, levels=6, segments=3, budget=100, q_len=256,
+       head_dim=64),
+    _w("w_pad1", heads=4, ctx_len=4 * 259 + 1, levels=2, segments=259, budget=1036, q_len=17),
+    _w("w_db2", heads=5, ctx_len=16 * 301, levels=4, segments=20, budget=90, q_len=48,
+       wavelet="db2", boundary="periodic"),
+    _w("w_j7", heads=8, ctx_len=128 * 130, levels=7, segments=9, budget=200, q_len=64),
+]
+
+
+@pytest.mark.parametrize("w", WIDE, ids=lambda w: w.name)
+def test_wide_route(wf, w):
+    names = wf.fused_kernel_names(wf.params_for(w))
+    wide = w.name != "w1023"
+    assert names[1] == ("skim_weights" if wide else "skim_select"), names
+    _check_case(wf, w, w.name, "wide", cached=True)
