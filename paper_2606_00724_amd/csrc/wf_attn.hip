@@ -1,7 +1,7 @@
 // Sparse cache and attention over it (Section 3.2, last paragraph; the
 // cached-attention form of eq. 3, bidirectional: no mask).
 //
-// The cache rows of a unit are split into chunks of kAttnChunk rows, one
+// The cache rows of a unit are split into ranges of whole chunks, one
 // workgroup each (split-KV); each workgroup writes its unnormalised partial
 // output with the per-row max and sum of exp, and a combine kernel merges the
 // splits.  In the fused path the rows are read in place: row r < k_eff is
@@ -11,364 +11,37 @@
 // The two 16-row MFMA tiles of a sub-block take rows 8(m/4) + m%4 and
 // 8(m/4) + 4 + m%4, so that lane group g ends up holding the scores of rows
 // 8g .. 8g+7 for query l%16 -- exactly the A operand of O = P V for the same
-// instruction.  V sits transposed in LDS so that its B operand is one 16-byte
-// read.  Online softmax (running max / sum per query row) spans the
+// instruction.  Online softmax (running max / sum per query row) spans the
 // sub-blocks.  fp32 uses v_mfma_f32_16x16x4_f32 on 16-row sub-blocks.
-#include <type_traits>
-
 #include "wf_device.hpp"
 #include "wf_kernels.hpp"
 #include "wf_launch.hpp"
 
 namespace wf {
 
-// Absolute cache row rr of unit u: K[tok[rr]] for rr < nsel, then the tail
-// rows; contiguous rows when tok is null.  Rows outside [r_lo, r_hi) of the
-// current chunk are zero.
-template <typename T, int D>
-struct CacheRows {
-  const T* base;
-  const T* tail;
-  const int32_t* tok;   // unit's token list or null
-  long unit_rows;       // rows per unit in `base` (L, or nrows when contiguous)
-  long Lf;              // rows Lf .. Lf + R - 1 of `base` follow the token list
-  int u, nsel, G, R;
-  long r0;
-  int nr;
-  __device__ __forceinline__ const T* operator()(int r) const {
-    if (r >= nr) return nullptr;
-    const long rr = r0 + r;
-    if (tok) {
-      if (rr < nsel)
-        return base + ((long)u * unit_rows + min(max((long)tok[rr], 0L), unit_rows - 1)) * D;
-      if (rr < nsel + R) return base + ((long)u * unit_rows + Lf + (rr - nsel)) * D;
-      return tail + ((long)u * G + (rr - nsel - R)) * D;
-    }
-    return base + ((long)u * unit_rows + rr) * D;
-  }
-};
-
-// bf16 V chunk in token-pair layout: dword [m][c] holds channel c of rows
-// 2m (low half) and 2m+1 (high half), so the PV operand of rows 8g .. 8g+7
-// is four dword reads.  Thread t stages pairs of 8-channel vectors.
-template <int D, int NT>
-struct VPairStager {
-  static constexpr int VPR = D / 8;                       // vectors per row
-  static constexpr int ITEMS = (kAttnChunk / 2) * VPR;    // (pair, vector)
-  static constexpr int PER_THREAD = (ITEMS + NT - 1) / NT;
-  static constexpr int VPS = D + 4;                       // dwords per pair row
-  u32x4 lo[PER_THREAD], hi[PER_THREAD];
-
-  template <class Src>
-  __device__ __forceinline__ void load(const Src& src) {
-    const bf16_t* pa[PER_THREAD];
-    const bf16_t* pb[PER_THREAD];
-#pragma unroll
-    for (int i = 0; i < PER_THREAD; ++i) {
-      const int v = i * NT + threadIdx.x;
-      const int m = v / VPR;
-      pa[i] = v < ITEMS ? src(2 * m) : nullptr;
-      pb[i] = v < ITEMS ? src(2 * m + 1) : nullptr;
-    }
-#pragma unroll
-    for (int i = 0; i < PER_THREAD; ++i) {
-      const int k = (i * NT + threadIdx.x) % VPR;
-      lo[i] = pa[i] ? *reinterpret_cast<const u32x4*>(pa[i] + 8 * k) : u32x4{0u, 0u, 0u, 0u};
-      hi[i] = pb[i] ? *reinterpret_cast<const u32x4*>(pb[i] + 8 * k) : u32x4{0u, 0u, 0u, 0u};
-    }
-  }
-
-  __device__ __forceinline__ void store(uint32_t* dst) const {
-#pragma unroll
-    for (int i = 0; i < PER_THREAD; ++i) {
-      const int v = i * NT + threadIdx.x;
-      if (v < ITEMS) {
-        const int m = v / VPR, k = v % VPR;
-        u32x4 w0, w1;
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          w0[2 * e] = (lo[i][e] & 0xffffu) | (hi[i][e] << 16);
-          w0[2 * e + 1] = (lo[i][e] >> 16) | (hi[i][e] & 0xffff0000u);
-          w1[2 * e] = (lo[i][e + 2] & 0xffffu) | (hi[i][e + 2] << 16);
-          w1[2 * e + 1] = (lo[i][e + 2] >> 16) | (hi[i][e + 2] & 0xffff0000u);
-        }
-        uint32_t* row = dst + m * VPS + 8 * k;
-        *reinterpret_cast<u32x4*>(row) = w0;
-        *reinterpret_cast<u32x4*>(row + 4) = w1;
-      }
-    }
-  }
-};
-
-template <typename T, int D>
-__global__ __launch_bounds__(kBlock) void attn_kernel(AttnArgs a) {
-  constexpr int NW = kBlock / kWave;
-  constexpr bool BF = sizeof(T) == 2;
-  using KStager = RowStager<T, D, kAttnChunk, kBlock>;
-  constexpr int KSTR = KStager::STRIDE;
-  using VStage = typename std::conditional<BF, VPairStager<D, kBlock>,
-                                           RowStager<T, D, kAttnChunk, kBlock>>::type;
-  // fp32 V is row-major with stride D + 4 floats; bf16 V is the pair layout
-  constexpr int VPS = D + 4;
-  extern __shared__ __align__(16) unsigned char smem[];
-  T* Ks = reinterpret_cast<T*>(smem);
-  uint32_t* Vl = reinterpret_cast<uint32_t*>(Ks + kAttnChunk * KSTR);
-
-  const int item = xcd_swizzle(blockIdx.x, gridDim.x);
-  const int u = item / a.NS, sp = item % a.NS;
-  const long rb0 = (long)sp * a.rps;
-  const long re0 = min(rb0 + (long)a.rps, (long)a.nrows);
-  const int nchunks = (int)((re0 - rb0 + kAttnChunk - 1) / kAttnChunk);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int g = lane >> 4, col = lane & 15;
-
-  CacheRows<T, D> ksrc, vsrc;
-  ksrc.base = reinterpret_cast<const T*>(a.K);
-  vsrc.base = reinterpret_cast<const T*>(a.V);
-  ksrc.tail = reinterpret_cast<const T*>(a.Kg);
-  vsrc.tail = reinterpret_cast<const T*>(a.Vg);
-  ksrc.tok = vsrc.tok = a.tok ? a.tok + (long)(u / a.share) * a.nsel : nullptr;
-  ksrc.unit_rows = vsrc.unit_rows = a.tok ? (long)a.L : (long)a.nrows;
-  ksrc.u = vsrc.u = u;
-  ksrc.nsel = vsrc.nsel = a.nsel;
-  ksrc.G = vsrc.G = a.G;
-  ksrc.R = vsrc.R = a.R;
-  ksrc.Lf = vsrc.Lf = a.Lf;
-
-  const int nqb = (a.B + 15) / 16;
-  const int tsplit = nqb == 1 ? 4 : (nqb == 2 ? 2 : 1);
-  const int qpg = NW / tsplit;                 // query blocks per group
-  const int ngroups = (nqb + qpg - 1) / qpg;
-  const int part = wave % tsplit;
-  const int R = kAttnChunk / tsplit;           // chunk rows per wave
-  const T* Qunit = reinterpret_cast<const T*>(a.Q) + (long)u * a.B * D;
-  float* po_base = a.part + ((long)u * a.NS + sp) * a.B * D;
-  float* ps_base = a.pstat + ((long)u * a.NS + sp) * 2 * a.B;
-
-  KStager kst;
-  VStage vst;
-  for (int grp = 0; grp < ngroups; ++grp) {
-    const int qb = grp * qpg + wave / tsplit;
-    const bool active = qb < nqb;
-    const T* qrow = Qunit + (long)min(qb * 16 + col, a.B - 1) * D;
-    f32x4 O[D / 16];
-#pragma unroll
-    for (int cb = 0; cb < D / 16; ++cb) O[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float m_run = -INFINITY, l_run = 0.f;
-    u32x4 qreg[BF ? D / 32 : 1];
-    if constexpr (BF) {
-#pragma unroll
-      for (int s = 0; s < D / 32; ++s)
-        qreg[s] = *reinterpret_cast<const u32x4*>(qrow + 32 * s + 8 * g);
-    }
-    ksrc.r0 = vsrc.r0 = rb0;
-    ksrc.nr = vsrc.nr = (int)min((long)kAttnChunk, re0 - rb0);
-    kst.load(ksrc);
-    vst.load(vsrc);
-    for (int ch = 0; ch < nchunks; ++ch) {
-      const int nr = (int)min((long)kAttnChunk, re0 - (rb0 + (long)ch * kAttnChunk));
-      __syncthreads();  // previous chunk (or group) done with the LDS
-      kst.store(Ks);
-      if constexpr (BF) vst.store(Vl);
-      else vst.store(reinterpret_cast<T*>(Vl));
-      __syncthreads();
-      if (ch + 1 < nchunks) {
-        ksrc.r0 = vsrc.r0 = rb0 + (long)(ch + 1) * kAttnChunk;
-        ksrc.nr = vsrc.nr = (int)min((long)kAttnChunk, re0 - ksrc.r0);
-        kst.load(ksrc);
-        vst.load(vsrc);
-      }
-      if (!active) continue;
-      const int rb = part * R;
-      const int re = min(rb + R, nr);
-      if constexpr (BF) {
-        for (int sb = rb; sb < re; sb += 32) {
-          const int rx = sb + 8 * (col >> 2) + (col & 3);
-          f32x4 ax = {0.f, 0.f, 0.f, 0.f}, ay = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int s = 0; s < D / 32; ++s) {
-            u32x4 kx = *reinterpret_cast<const u32x4*>(Ks + rx * KSTR + 32 * s + 8 * g);
-            u32x4 ky = *reinterpret_cast<const u32x4*>(Ks + (rx + 4) * KSTR + 32 * s + 8 * g);
-            ax = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                __builtin_bit_cast(bf16x8, kx), __builtin_bit_cast(bf16x8, qreg[s]), ax, 0, 0, 0);
-            ay = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                __builtin_bit_cast(bf16x8, ky), __builtin_bit_cast(bf16x8, qreg[s]), ay, 0, 0, 0);
-          }
-          // lane holds scores of rows sb + 8g + e (e < 8) for query col
-          float sv[8];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            sv[i] = (sb + 8 * g + i < re) ? ax[i] * a.scale : -INFINITY;
-            sv[4 + i] = (sb + 8 * g + 4 + i < re) ? ay[i] * a.scale : -INFINITY;
-          }
-          float mb = sv[0];
-#pragma unroll
-          for (int e = 1; e < 8; ++e) mb = fmaxf(mb, sv[e]);
-          mb = fmaxf(mb, __shfl_xor(mb, 16));
-          mb = fmaxf(mb, __shfl_xor(mb, 32));
-          const float m_new = fmaxf(m_run, mb);
-          const float alpha = __expf(m_run - m_new);
-          float pv[8], ps = 0.f;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            pv[e] = sv[e] > -INFINITY ? __expf(sv[e] - m_new) : 0.f;
-            ps += pv[e];
-          }
-          ps += __shfl_xor(ps, 16);
-          ps += __shfl_xor(ps, 32);
-          l_run = l_run * alpha + ps;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float ai = __shfl(alpha, 4 * g + i);
-#pragma unroll
-            for (int cb = 0; cb < D / 16; ++cb) O[cb][i] *= ai;
-          }
-          u32x4 pp = {pack_bf16x2(pv[0], pv[1]), pack_bf16x2(pv[2], pv[3]),
-                      pack_bf16x2(pv[4], pv[5]), pack_bf16x2(pv[6], pv[7])};
-          const uint32_t* vrow = Vl + ((sb >> 1) + 4 * g) * VPS + col;
-#pragma unroll
-          for (int cb = 0; cb < D / 16; ++cb) {
-            u32x4 vb = {vrow[cb * 16], vrow[VPS + cb * 16], vrow[2 * VPS + cb * 16],
-                        vrow[3 * VPS + cb * 16]};
-            O[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                __builtin_bit_cast(bf16x8, pp), __builtin_bit_cast(bf16x8, vb), O[cb], 0, 0, 0);
-          }
-          m_run = m_new;
-        }
-      } else {
-        const float* Kf = reinterpret_cast<const float*>(Ks);
-        const float* Vf = reinterpret_cast<const float*>(Vl);
-        for (int sb = rb; sb < re; sb += 16) {
-          f32x4 acc = tile_dot_f32<D>(Kf + (sb + col) * KSTR,
-                                      reinterpret_cast<const float*>(qrow),
-                                      f32x4{0.f, 0.f, 0.f, 0.f});
-          // lane holds scores of rows sb + 4g + i for query col
-          float sv[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) sv[i] = (sb + 4 * g + i < re) ? acc[i] * a.scale : -INFINITY;
-          float mb = fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]));
-          mb = fmaxf(mb, __shfl_xor(mb, 16));
-          mb = fmaxf(mb, __shfl_xor(mb, 32));
-          const float m_new = fmaxf(m_run, mb);
-          const float alpha = __expf(m_run - m_new);
-          float pv[4], ps = 0.f;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            pv[i] = sv[i] > -INFINITY ? __expf(sv[i] - m_new) : 0.f;
-            ps += pv[i];
-          }
-          ps += __shfl_xor(ps, 16);
-          ps += __shfl_xor(ps, 32);
-          l_run = l_run * alpha + ps;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float ai = __shfl(alpha, 4 * g + i);
-#pragma unroll
-            for (int cb = 0; cb < D / 16; ++cb) O[cb][i] *= ai;
-          }
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-#pragma unroll
-            for (int cb = 0; cb < D / 16; ++cb) {
-              const float vb = Vf[(sb + 4 * g + i) * VPS + cb * 16 + col];
-              O[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(pv[i], vb, O[cb], 0, 0, 0);
-            }
-          }
-          m_run = m_new;
-        }
-      }
-    }
-
-    if (tsplit == 1) {
-      if (active) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int q = qb * 16 + 4 * g + i;
-          if (q < a.B) {
-#pragma unroll
-            for (int cb = 0; cb < D / 16; ++cb) po_base[(long)q * D + cb * 16 + col] = O[cb][i];
-          }
-        }
-        const int q = qb * 16 + col;
-        if (g == 0 && q < a.B) {
-          ps_base[q] = m_run;
-          ps_base[a.B + q] = l_run;
-        }
-      }
-    } else {
-      // one group; the tsplit waves of a query block merge their row parts
-      __syncthreads();
-      float* cO = reinterpret_cast<float*>(smem);  // [NW][16][D]
-      float* cm = cO + NW * 16 * D;                 // [NW][16]
-      float* cl = cm + NW * 16;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-#pragma unroll
-        for (int cb = 0; cb < D / 16; ++cb)
-          cO[(wave * 16 + 4 * g + i) * D + cb * 16 + col] = O[cb][i];
-      }
-      if (g == 0) {
-        cm[wave * 16 + col] = m_run;
-        cl[wave * 16 + col] = l_run;
-      }
-      __syncthreads();
-      if (part == 0 && active) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int rr = 4 * g + i;
-          const int q = qb * 16 + rr;
-          float M = -INFINITY;
-          for (int pp = 0; pp < tsplit; ++pp) M = fmaxf(M, cm[(wave + pp) * 16 + rr]);
-          float lsum = 0.f;
-          float wgt[4];
-#pragma unroll
-          for (int pp = 0; pp < 4; ++pp) {
-            const float mp = pp < tsplit ? cm[(wave + pp) * 16 + rr] : -INFINITY;
-            wgt[pp] = mp > -INFINITY ? __expf(mp - M) : 0.f;
-            if (pp < tsplit) lsum += wgt[pp] * cl[(wave + pp) * 16 + rr];
-          }
-          if (q < a.B) {
-#pragma unroll
-            for (int cb = 0; cb < D / 16; ++cb) {
-              float o = 0.f;
-              for (int pp = 0; pp < tsplit; ++pp)
-                o += wgt[pp] * cO[((wave + pp) * 16 + rr) * D + cb * 16 + col];
-              po_base[(long)q * D + cb * 16 + col] = o;
-            }
-            if (col == 0) {
-              ps_base[q] = M;
-              ps_base[a.B + q] = lsum;
-            }
-          }
-        }
-      }
-    }
-  }
-}
-
-// ------------------------------------------------------------ bf16 ring path
-//
 // Chunks of kRingRows cache rows (K and V) stream into an LDS ring through
 // direct global->LDS loads; rows stay in their natural row-major form with
-// swizzled 16-byte granules.  The PV B operand (8 consecutive rows of one
-// channel per lane) comes from two ds_read_b64_tr_b16: in each 16-lane group,
-// lane i points at row t0 + i/4, channels c0 + 4(i%4) .. +3, and receives
-// rows t0 .. t0+3 of channel c0 + i.
+// swizzled 16-byte granules.  bf16: the PV B operand (8 consecutive rows of
+// one channel per lane) comes from two ds_read_b64_tr_b16: in each 16-lane
+// group, lane i points at row t0 + i/4, channels c0 + 4(i%4) .. +3, and
+// receives rows t0 .. t0+3 of channel c0 + i.  fp32: it is four dword reads,
+// whose 64 lanes (rows 4g + i, channels c0 + col) fall on 64 banks by the
+// granule swizzle.
 constexpr int kRingRows = 64;
 
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 
-template <int D>
+template <typename T, int D>
 struct RingRowPtr {
-  const bf16_t* base;
-  const bf16_t* tail;
+  const T* base;
+  const T* tail;
   const int32_t* toks;  // LDS: token ids of the split's selected rows, or null
   long unit_rows;       // rows per unit in `base`
   long r0, rlast;       // absolute first row of the chunk, last valid row
   long split_r0;        // first row of the split (toks[0])
   long Lf;              // rows Lf .. Lf + R - 1 of `base` follow the token list
   int u, nsel, G, R;
-  __device__ __forceinline__ const bf16_t* operator()(int r) const {
+  __device__ __forceinline__ const T* operator()(int r) const {
     const long rr = min(r0 + r, rlast);
     if (toks) {
       // token ids are clamped into the unit: a bad id cannot leave K / V
@@ -383,20 +56,22 @@ struct RingRowPtr {
 };
 
 // 8 waves, two per SIMD, so that one wave's MFMA, exp and LDS latencies
-// overlap the other's work; with up to four query blocks each block's rows
-// are split over two waves.
+// overlap the other's work; with few query blocks each block's rows are
+// split over two waves (bf16, 32-row products) or up to four (fp32, 16-row).
 constexpr int kAttnRingBlock = 512;
 
 // SEL (token-level path): the workgroup first takes the unit's top-nsel
 // tokens of the scan weights itself (eq. 9 over the pool; ties to the lower
 // pool position, which is the lower token) and keeps the ascending ids of
 // its split; tok_out (nullable) receives them.
-template <int D, bool SEL = false>
+template <typename T, int D, bool SEL = false>
 __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
+  constexpr bool BF = sizeof(T) == 2;
   constexpr int NW = kAttnRingBlock / kWave;
   constexpr int CR = kRingRows;
-  constexpr int G = D / 8;
-  constexpr int CHB = CR * 2 * D;            // bytes of one K (or V) chunk
+  constexpr int ES = (int)sizeof(T), EPV = 16 / ES;  // element size, elements per granule
+  constexpr int G = D / EPV;
+  constexpr int CHB = CR * ES * D;           // bytes of one K (or V) chunk
   constexpr int IPW = CR * G / (64 * NW);    // loads per wave per matrix
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned char* ring = smem;                                       // [nbuf][K, V]
@@ -451,11 +126,11 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
   }
   __syncthreads();
 
-  RingRowPtr<D> kp, vp;
-  kp.base = reinterpret_cast<const bf16_t*>(a.K);
-  vp.base = reinterpret_cast<const bf16_t*>(a.V);
-  kp.tail = reinterpret_cast<const bf16_t*>(a.Kg);
-  vp.tail = reinterpret_cast<const bf16_t*>(a.Vg);
+  RingRowPtr<T, D> kp, vp;
+  kp.base = reinterpret_cast<const T*>(a.K);
+  vp.base = reinterpret_cast<const T*>(a.V);
+  kp.tail = reinterpret_cast<const T*>(a.Kg);
+  vp.tail = reinterpret_cast<const T*>(a.Vg);
   const bool indexed = SEL || a.tok != nullptr;
   kp.toks = vp.toks = indexed ? toks : nullptr;
   kp.unit_rows = vp.unit_rows = indexed ? (long)a.L : (long)a.nrows;
@@ -468,12 +143,13 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
   kp.Lf = vp.Lf = a.Lf;
 
   const int nqb = (a.B + 15) / 16;
-  const int tsplit = 2 * nqb <= NW ? 2 : 1;  // row halves per query block
+  // row parts per query block (bf16: two or one)
+  const int tsplit = !BF && 4 * nqb <= NW ? 4 : 2 * nqb <= NW ? 2 : 1;
   const int qpg = NW / tsplit;
   const int ngroups = (nqb + qpg - 1) / qpg;
   const int part = wave % tsplit;
   const int R = CR / tsplit;
-  const bf16_t* Qunit = reinterpret_cast<const bf16_t*>(a.Q) + (long)u * a.B * D;
+  const T* Qunit = reinterpret_cast<const T*>(a.Q) + (long)u * a.B * D;
   float* po_base = a.part + ((long)u * a.NS + sp) * a.B * D;
   float* ps_base = a.pstat + ((long)u * a.NS + sp) * 2 * a.B;
   const uint32_t ring_lds = lds_offset(ring);
@@ -484,8 +160,8 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
   // rows are all selected tokens (rows past the split repeat its last row)
   // takes one token id and one address per row for both loads; any other
   // chunk goes through the general row map.
-  const bf16_t* kunit = kp.base + (long)u * kp.unit_rows * D;
-  const bf16_t* vunit = vp.base + (long)u * vp.unit_rows * D;
+  const T* kunit = kp.base + (long)u * kp.unit_rows * D;
+  const T* vunit = vp.base + (long)u * vp.unit_rows * D;
   const int split_last = (int)(re0 - 1 - rb0);
   auto issue_kv = [&](int c, uint32_t slot) {
     const long r0 = rb0 + (long)c * CR;
@@ -500,7 +176,7 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
         const int k = (lane % G) ^ granule_swz<G>(r);
         // token ids are clamped into the unit: a bad id cannot leave K / V
         const int t = min(max(toks[min((int)(r0 - rb0) + r, split_last)], 0), a.L - 1);
-        off[i] = (long)t * D + 8 * k;
+        off[i] = (long)t * D + EPV * k;
       }
 #pragma unroll
       for (int i = 0; i < IPW; ++i) {
@@ -518,12 +194,14 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
   // LDS byte offsets of the lane's operands inside a 32-row block: the
   // granule swizzle depends only on the row mod 32 and every block starts at
   // a multiple of 32 rows, so one set serves all blocks
-  int koff[D / 32], kyoff[D / 32], vlo[D / 16], vhi[D / 16];
-  {
+  // (fp32: inside a 16-row block, the first or second of 32 rows)
+  constexpr int KS = G / 4;  // granules of a row per lane group
+  int koff[KS], kyoff[KS], vlo[D / 16], vhi[D / 16];
+  if constexpr (BF) {
     const int rx0 = 8 * (col >> 2) + (col & 3);  // QK rows rx0 and rx0 + 4
     const int t00 = 8 * g + (col >> 2);          // PV rows t00 and t00 + 4
 #pragma unroll
-    for (int s = 0; s < D / 32; ++s) {
+    for (int s = 0; s < KS; ++s) {
       koff[s] = granule_offset<G>(rx0, 4 * s + g);
       kyoff[s] = granule_offset<G>(rx0 + 4, 4 * s + g);
     }
@@ -539,11 +217,11 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
   for (int grp = 0; grp < ngroups; ++grp) {
     const int qb = grp * qpg + wave / tsplit;
     const bool active = qb < nqb;
-    const bf16_t* qrow = Qunit + (long)min(qb * 16 + col, a.B - 1) * D;
-    u32x4 qreg[D / 32];
+    const T* qrow = Qunit + (long)min(qb * 16 + col, a.B - 1) * D;
+    u32x4 qreg[KS];
 #pragma unroll
-    for (int s = 0; s < D / 32; ++s)
-      qreg[s] = *reinterpret_cast<const u32x4*>(qrow + 32 * s + 8 * g);
+    for (int s = 0; s < KS; ++s)
+      qreg[s] = *reinterpret_cast<const u32x4*>(qrow + EPV * (4 * s + g));
     f32x4 O[D / 16];
 #pragma unroll
     for (int cb = 0; cb < D / 16; ++cb) O[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -551,7 +229,7 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
     // consume the q operand before async loads are queued, so that the
     // compiler's own wait for it sits here and not inside the loop below
 #pragma unroll
-    for (int s = 0; s < D / 32; ++s) asm volatile("" ::"v"(qreg[s]));
+    for (int s = 0; s < KS; ++s) asm volatile("" ::"v"(qreg[s]));
     // ring of nbuf slots, nbuf - 1 chunks in flight ahead of the one consumed
     for (int k = 0; k < nch && k < nbuf - 1; ++k)
       issue_kv(k, ring_lds + (uint32_t)(k * 2 * CHB));
@@ -566,12 +244,67 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
       if (active) {
         const int rb = part * R;
         const int re = min(rb + R, nr);
-        for (int sb = rb; sb < re; sb += 32) {
+        if constexpr (!BF) {
+          for (int sb = rb; sb < re; sb += 16) {
+            const unsigned char* kblk = Kb + sb * (16 * G);
+            const unsigned char* vblk = Vb + sb * (16 * G);
+            const int h = sb & 16;  // the block's place in its 32 rows
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+              const f32x4 kv = *reinterpret_cast<const f32x4*>(
+                  kblk + granule_offset<G>(h + col, 4 * s + g) - h * (16 * G));
+              const f32x4 qv = __builtin_bit_cast(f32x4, qreg[s]);
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[e], qv[e], acc, 0, 0, 0);
+            }
+            // lane holds the scores of rows sb + 4g + i for query col, in
+            // log2 units; rows past the range are -inf
+            float t[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) t[i] = sb + 4 * g + i < re ? acc[i] * c2 : -INFINITY;
+            const float mb =
+                max_xor32(max_xor16(fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3]))));
+            const float m_new = fmaxf(m_run, mb);  // finite: row sb is in range
+            float pv[4], ps = 0.f;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              pv[i] = __builtin_amdgcn_exp2f(t[i] - m_new);  // 2^-inf = 0
+              ps += pv[i];
+            }
+            ps = add_xor32(add_xor16(ps));
+            if (__builtin_amdgcn_ballot_w64(m_new != m_run) != 0) {
+              const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+              l_run = l_run * alpha + ps;
+#pragma unroll
+              for (int i = 0; i < 4; ++i) {
+                const float ai = __shfl(alpha, 4 * g + i);
+#pragma unroll
+                for (int cb = 0; cb < D / 16; ++cb) O[cb][i] *= ai;
+              }
+            } else {
+              l_run += ps;
+            }
+            // P is the A operand in place; V row 4g + i, channel 16 cb + col
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+#pragma unroll
+              for (int cb = 0; cb < D / 16; ++cb) {
+                const float vb = *reinterpret_cast<const float*>(
+                    vblk + granule_offset<G>(h + 4 * g + i, 4 * cb + (col >> 2)) -
+                    h * (16 * G) + 4 * (col & 3));
+                O[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(pv[i], vb, O[cb], 0, 0, 0);
+              }
+            }
+            m_run = m_new;
+          }
+        } else for (int sb = rb; sb < re; sb += 32) {
           // every LDS operand of the block is read first: the V reads'
           // latency then overlaps the QK products and the softmax
           const unsigned char* kblk = Kb + sb * (16 * G);
           const uint32_t vblk = lds_offset(Vb) + (uint32_t)(sb * (16 * G));
-          u32x4 kx[D / 32], ky[D / 32], vb[D / 16];
+          u32x4 kx[KS], ky[KS], vb[D / 16];
 #pragma unroll
           for (int s = 0; s < D / 32; ++s) {
             kx[s] = *reinterpret_cast<const u32x4*>(kblk + koff[s]);
@@ -664,7 +397,7 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
         }
       }
     } else {
-      // one group; the two waves of a query block merge their row halves
+      // one group; the tsplit waves of a query block merge their row parts
       // (the ring is idle: every wave passed the barrier after the loop)
       float* cO = reinterpret_cast<float*>(smem);  // [NW][16][D]
       float* cm = cO + NW * 16 * D;                 // [NW][16]
@@ -680,22 +413,37 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
         cl[wave * 16 + col] = l_run;
       }
       lds_barrier();
+      constexpr int MP = BF ? 2 : 4;  // most parts
       if (part == 0 && active) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int rr = 4 * g + i;
           const int q = qb * 16 + rr;
-          const float m0 = cm[wave * 16 + rr], m1 = cm[(wave + 1) * 16 + rr];
-          const float M = fmaxf(m0, m1);
-          const float w0 = m0 > -INFINITY ? __builtin_amdgcn_exp2f(m0 - M) : 0.f;
-          const float w1 = m1 > -INFINITY ? __builtin_amdgcn_exp2f(m1 - M) : 0.f;
-          const float lsum = w0 * cl[wave * 16 + rr] + w1 * cl[(wave + 1) * 16 + rr];
+          float mp[MP], w[MP];
+#pragma unroll
+          for (int k = 0; k < MP; ++k)
+            mp[k] = BF || k < tsplit ? cm[(wave + k) * 16 + rr] : -INFINITY;
+          float M = mp[0];
+#pragma unroll
+          for (int k = 1; k < MP; ++k) M = fmaxf(M, mp[k]);
+          float lsum = 0.f;
+#pragma unroll
+          for (int k = 0; k < MP; ++k) {
+            w[k] = mp[k] > -INFINITY ? __builtin_amdgcn_exp2f(mp[k] - M) : 0.f;
+            if (BF || k < tsplit) lsum += w[k] * cl[(wave + k) * 16 + rr];
+          }
           if (q < a.B) {
 #pragma unroll
-            for (int cb = 0; cb < D / 16; ++cb)
+            for (int cb = 0; cb < D / 16; ++cb) {
+              float o[MP];
+#pragma unroll
+              for (int k = 0; k < MP; ++k)
+                o[k] = BF || k < tsplit
+                           ? w[k] * cO[((wave + k) * 16 + rr) * D + cb * 16 + col]
+                           : 0.f;
               po_base[(long)q * D + cb * 16 + col] =
-                  w0 * cO[(wave * 16 + rr) * D + cb * 16 + col] +
-                  w1 * cO[((wave + 1) * 16 + rr) * D + cb * 16 + col];
+                  BF ? o[0] + o[1] : (o[0] + o[1]) + (o[MP - 2] + o[MP - 1]);
+            }
             if (col == 0) {
               ps_base[q] = M * kLn2;  // back to natural-log units
               ps_base[a.B + q] = lsum;
@@ -838,53 +586,38 @@ AttnPlan plan_attn(const wf_params& p, long nrows) {
   AttnPlan a{};
   const long U = (long)p.batch * p.heads;
   const int D = p.head_dim;
-  if (p.dtype == WF_BF16) {
-    // one workgroup per CU streaming its rows through the LDS ring
-    const long chunks = std::max(1L, (nrows + kRingRows - 1) / kRingRows);
-    const long want = std::max(1L, (long)(device_cu_count() + U - 1) / U);
-    long splits = std::min(chunks, want);
-    splits = std::max(splits, (nrows + 4095) / 4096);  // at most 4096 rows each
-    const long cps = (chunks + splits - 1) / splits;
-    a.rps = (int)(cps * kRingRows);
-    a.splits = (int)((nrows + a.rps - 1) / a.rps);
-    const size_t stage = (size_t)2 * kRingRows * 2 * D;      // K + V chunk
-    const size_t toks = (size_t)a.rps * sizeof(int32_t);
-    const size_t budget = 160 * 1024 - 1024;
-    // three slots (two chunks in flight) measured slightly faster than four
-    a.nbuf = (int)std::min<size_t>(3, (budget - toks) / stage);
-    if (a.nbuf < 2) a.nbuf = 0;  // rejected by the caller
-    constexpr int nw = kAttnRingBlock / kWave;  // row-half merge: [nw][16][D] + 2 [nw][16]
-    const size_t comb = (size_t)nw * 16 * D * 4 + (size_t)2 * nw * 16 * 4;
-    a.lds_bytes = std::max((size_t)a.nbuf * stage, comb) + toks;
-    return a;
-  }
-  const long chunks = std::max(1L, (nrows + kAttnChunk - 1) / kAttnChunk);
-  // about 512 workgroups: splits of whole chunks; every split is non-empty
-  const long want = std::max(1L, (512 + U - 1) / U);
-  const long splits = std::min(chunks, want);
+  const int es = p.dtype == WF_BF16 ? 2 : 4;
+  // one workgroup per CU streaming its rows through the LDS ring
+  const long chunks = std::max(1L, (nrows + kRingRows - 1) / kRingRows);
+  const long want = std::max(1L, (long)(device_cu_count() + U - 1) / U);
+  long splits = std::min(chunks, want);
+  splits = std::max(splits, (nrows + 4095) / 4096);  // at most 4096 rows each
   const long cps = (chunks + splits - 1) / splits;
-  a.rps = (int)(cps * kAttnChunk);
+  a.rps = (int)(cps * kRingRows);
   a.splits = (int)((nrows + a.rps - 1) / a.rps);
-  const size_t stage = (size_t)kAttnChunk * (D + 4) * 4 * 2;
-  const size_t comb = (size_t)4 * 16 * D * 4 + (size_t)2 * 4 * 16 * 4;
-  a.lds_bytes = std::max(stage, comb);
+  const size_t stage = (size_t)2 * kRingRows * es * D;     // K + V chunk
+  const size_t toks = (size_t)a.rps * sizeof(int32_t);
+  const size_t budget = 160 * 1024 - 1024;
+  // three slots (two chunks in flight) measured slightly faster than four;
+  // fp32 rows of 128 channels leave room for two
+  a.nbuf = (int)std::min<size_t>(3, (budget - toks) / stage);
+  if (a.nbuf < 2) a.nbuf = 0;  // rejected by the caller
+  constexpr int nw = kAttnRingBlock / kWave;  // row-part merge: [nw][16][D] + 2 [nw][16]
+  const size_t comb = (size_t)nw * 16 * D * 4 + (size_t)2 * nw * 16 * 4;
+  a.lds_bytes = std::max((size_t)a.nbuf * stage, comb) + toks;
   return a;
 }
 
 template <typename T, int D>
 static hipError_t attn_launch(const AttnArgs& a, size_t lds, hipStream_t s) {
-  auto kern = [] {
-    if constexpr (sizeof(T) == 2) return attn_ring_kernel<D>;
-    else return attn_kernel<T, D>;
-  }();
+  auto kern = attn_ring_kernel<T, D>;
   if (lds > 65536) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)lds);
     if (e != hipSuccess) return e;
   }
-  const int block = sizeof(T) == 2 ? kAttnRingBlock : kBlock;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(a.U * a.NS)), dim3(block), lds, s, a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(a.U * a.NS)), dim3(kAttnRingBlock), lds, s, a);
   return hipGetLastError();
 }
 
@@ -927,10 +660,10 @@ hipError_t launch_attn(const wf_params& p, const void* Q, const void* K,
 }
 
 bool attn_can_select(const wf_params& p, long nrows) {
-  if (p.dtype != WF_BF16 || p.segments > kSelectLdsSegs) return false;
+  if (p.segments > kSelectLdsSegs || (p.dtype != WF_BF16 && !wide_weights(p))) return false;
   const AttnPlan pl = plan_attn(p, nrows);
   if (pl.nbuf < 2) return false;
-  const size_t ring = (size_t)pl.nbuf * 2 * kRingRows * 2 * p.head_dim;
+  const size_t ring = (size_t)pl.nbuf * 2 * kRingRows * (p.dtype == WF_BF16 ? 2 : 4) * p.head_dim;
   return sizeof(SelectShared<kAttnRingBlock>) + (size_t)p.segments * sizeof(int32_t) <= ring;
 }
 
@@ -971,10 +704,16 @@ hipError_t launch_attn_select(const wf_params& p, const void* Q, const void* K, 
   a.scale = effective_scale(p);
   // the unit's scan weights in the ring beside the histograms and region
   // ids when they fit
-  const size_t ring = (size_t)pl.nbuf * 2 * kRingRows * 2 * p.head_dim;
+  const size_t ring = (size_t)pl.nbuf * 2 * kRingRows * (p.dtype == WF_BF16 ? 2 : 4) * p.head_dim;
   const size_t fixed = sizeof(SelectShared<kAttnRingBlock>) + (size_t)a.S * sizeof(int32_t);
   a.w_in_lds = fixed + (size_t)a.P * sizeof(float) <= ring ? 1 : 0;
-  auto kern = p.head_dim == 128 ? attn_ring_kernel<128, true> : attn_ring_kernel<64, true>;
+  auto kern = [&] {
+    if (p.dtype == WF_BF16)
+      return p.head_dim == 128 ? attn_ring_kernel<bf16_t, 128, true>
+                               : attn_ring_kernel<bf16_t, 64, true>;
+    return p.head_dim == 128 ? attn_ring_kernel<float, 128, true>
+                             : attn_ring_kernel<float, 64, true>;
+  }();
   if (pl.lds_bytes > 65536) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1035,7 +774,7 @@ hipError_t launch_gather(const wf_params& p, const void* K, const void* V,
 
 hipError_t load_attn_kernels() {
   hipFuncAttributes fa;
-  return hipFuncGetAttributes(&fa, reinterpret_cast<const void*>(attn_ring_kernel<128, true>));
+  return hipFuncGetAttributes(&fa, reinterpret_cast<const void*>(attn_ring_kernel<bf16_t, 128, true>));
 }
 
 }  // namespace wf

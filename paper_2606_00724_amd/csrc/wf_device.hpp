@@ -68,79 +68,6 @@ __device__ __forceinline__ void store_elem<bf16_t>(bf16_t* p, long i, float v) {
   p[i].bits = (uint16_t)f32_to_bf16_bits(v);
 }
 
-// ------------------------------------------------------------ MFMA tiles
-//
-// A 16x16 output tile C[m][n] = sum_c Arow_m[c] * Brow_n[c], where lane l
-// supplies row m = l % 16 of A and row n = l % 16 of B (both stored with
-// channels contiguous).  On return lane l holds C[4 (l / 16) + i][l % 16] in
-// element i.
-//
-// bf16 rows use v_mfma_f32_16x16x32_bf16: lane group g = l / 16 feeds
-// channels 8g .. 8g+7 of every 32-channel step.  fp32 rows use
-// v_mfma_f32_16x16x4_f32 with the channel order permuted so that lane group g
-// walks the contiguous channel range [g D/4, (g+1) D/4): the reduction runs
-// over every channel exactly once either way.
-
-template <int D>
-__device__ __forceinline__ f32x4 tile_dot_bf16(const bf16_t* a_row,
-                                               const bf16_t* b_row,
-                                               f32x4 acc) {
-  const int g = (threadIdx.x & 63) >> 4;
-#pragma unroll
-  for (int s = 0; s < D / 32; ++s) {
-    u32x4 a = *reinterpret_cast<const u32x4*>(a_row + 32 * s + 8 * g);
-    u32x4 b = *reinterpret_cast<const u32x4*>(b_row + 32 * s + 8 * g);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-        __builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0,
-        0, 0);
-  }
-  return acc;
-}
-
-template <int D>
-__device__ __forceinline__ f32x4 tile_dot_f32(const float* a_row,
-                                              const float* b_row, f32x4 acc) {
-  const int g = (threadIdx.x & 63) >> 4;
-  const float* a = a_row + g * (D / 4);
-  const float* b = b_row + g * (D / 4);
-#pragma unroll
-  for (int s4 = 0; s4 < D / 16; ++s4) {
-    f32x4 av = *reinterpret_cast<const f32x4*>(a + 4 * s4);
-    f32x4 bv = *reinterpret_cast<const f32x4*>(b + 4 * s4);
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[e], bv[e], acc, 0, 0, 0);
-  }
-  return acc;
-}
-
-template <typename T, int D>
-__device__ __forceinline__ f32x4 tile_dot(const T* a_row, const T* b_row,
-                                          f32x4 acc);
-template <>
-__device__ __forceinline__ f32x4 tile_dot<bf16_t, 64>(const bf16_t* a,
-                                                      const bf16_t* b,
-                                                      f32x4 c) {
-  return tile_dot_bf16<64>(a, b, c);
-}
-template <>
-__device__ __forceinline__ f32x4 tile_dot<bf16_t, 128>(const bf16_t* a,
-                                                       const bf16_t* b,
-                                                       f32x4 c) {
-  return tile_dot_bf16<128>(a, b, c);
-}
-template <>
-__device__ __forceinline__ f32x4 tile_dot<float, 64>(const float* a,
-                                                     const float* b, f32x4 c) {
-  return tile_dot_f32<64>(a, b, c);
-}
-template <>
-__device__ __forceinline__ f32x4 tile_dot<float, 128>(const float* a,
-                                                      const float* b,
-                                                      f32x4 c) {
-  return tile_dot_f32<128>(a, b, c);
-}
-
 constexpr float kLog2e = 1.44269504088896341f;  // log2(e)
 constexpr float kLn2 = 0.69314718055994531f;     // ln(2)
 
@@ -683,63 +610,6 @@ __device__ __forceinline__ void block_select_topk_any(const float* score, int n,
 }
 
 // ------------------------------------------------------------ LDS staging
-
-// Rows of D elements moved to LDS in 16-byte vectors, row stride D plus one
-// vector of padding.  Vector v of a chunk is (row v / VPR, column v % VPR);
-// thread t owns vectors t, t + NT, ...  Loads go to registers first (all of a
-// thread's loads in flight together), then to LDS, so a chunk can be
-// prefetched while the previous one is consumed.
-template <typename T, int D, int ROWS, int NT>
-struct RowStager {
-  static constexpr int EPV = 16 / sizeof(T);
-  static constexpr int VPR = D / EPV;
-  static constexpr int STRIDE = D + EPV;
-  static constexpr int PER_THREAD = (ROWS * VPR + NT - 1) / NT;
-  u32x4 buf[PER_THREAD];
-
-  // src(r) -> row pointer, or nullptr for a zero row; r < ROWS
-  template <class Src>
-  __device__ __forceinline__ void load(Src src) {
-    const T* rowp[PER_THREAD];
-#pragma unroll
-    for (int i = 0; i < PER_THREAD; ++i) {
-      const int v = i * NT + threadIdx.x;
-      rowp[i] = v < ROWS * VPR ? src(v / VPR) : nullptr;
-    }
-#pragma unroll
-    for (int i = 0; i < PER_THREAD; ++i) {
-      const int v = i * NT + threadIdx.x;
-      buf[i] = rowp[i] ? *reinterpret_cast<const u32x4*>(rowp[i] + (v % VPR) * EPV)
-                       : u32x4{0u, 0u, 0u, 0u};
-    }
-  }
-
-  __device__ __forceinline__ void store(T* dst) const {
-#pragma unroll
-    for (int i = 0; i < PER_THREAD; ++i) {
-      const int v = i * NT + threadIdx.x;
-      if (v < ROWS * VPR)
-        *reinterpret_cast<u32x4*>(dst + (v / VPR) * STRIDE + (v % VPR) * EPV) = buf[i];
-    }
-  }
-
-  // bf16 only: store transposed, dst[c * TSTRIDE + r] = row r, channel c
-  template <int TSTRIDE>
-  __device__ __forceinline__ void store_transposed(uint16_t* dst) const {
-#pragma unroll
-    for (int i = 0; i < PER_THREAD; ++i) {
-      const int v = i * NT + threadIdx.x;
-      if (v < ROWS * VPR) {
-        const int r = v / VPR, c0 = (v % VPR) * 8;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          dst[(c0 + 2 * e) * TSTRIDE + r] = (uint16_t)(buf[i][e] & 0xffffu);
-          dst[(c0 + 2 * e + 1) * TSTRIDE + r] = (uint16_t)(buf[i][e] >> 16);
-        }
-      }
-    }
-  }
-};
 
 // Copies `rows` (runtime, any count) rows to LDS, 8 loads in flight per
 // thread; src(r) -> row pointer.

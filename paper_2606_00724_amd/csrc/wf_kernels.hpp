@@ -9,8 +9,7 @@ namespace wf {
 
 constexpr int kBlock = 256;        // threads per workgroup, all kernels
 constexpr int kMaxCoefTile = 64;   // coarse coefficients per skim tile
-constexpr int kScanChunk = 128;    // pool tokens per scan workgroup
-constexpr int kAttnChunk = 128;    // cache rows per attention workgroup
+constexpr int kScanChunk = 128;    // tokens per chunk of the token skims
 constexpr int kCoefPad = 4;        // fp32 pad per LDS coefficient row
 
 // kHaarStream: kHaarSum with the keys read with the nt policy

@@ -3,7 +3,7 @@
 // the pool only, Section 3.2), then the top-k tokens (eq. 9) -> mu^0.
 //
 // The pool of a unit is S runs of 2^J consecutive rows.  It is split into
-// chunks of kScanChunk pool positions, one workgroup each.  The softmax over
+// ranges of whole chunks (PoolShape), one workgroup each.  The softmax over
 // the pool needs every chunk's row maximum and normaliser before any weight
 // can be formed, so the scan runs as two passes over the chunks:
 //   pass 1 (stats):   logits of the chunk on MFMA, per-row max and
@@ -20,195 +20,17 @@
 
 namespace wf {
 
-// Pool chunk staging: row r of a chunk starting at pool position p0 is token
-// seg[p >> J] 2^J + (p & (2^J - 1)) with p = p0 + r; rows past the end are
-// zero.
-template <typename T, int D>
-struct PoolRows {
-  const T* Kunit;
-  const int32_t* seg;
-  long p0, last;  // last: the unit's last row (region ids are clamped to it)
-  int np, J, mask;
-  __device__ __forceinline__ const T* operator()(int r) const {
-    if (r >= np) return nullptr;
-    const long p = p0 + r;
-    const long tok = ((long)seg[p >> J] << J) | (p & mask);
-    return Kunit + min(max(tok, 0L), last) * D;
-  }
-};
-
-template <int WEIGHTS, typename T, int D>
-__global__ __launch_bounds__(kBlock) void scan_chunk_kernel(ScanArgs a) {
-  using Stager = RowStager<T, D, kScanChunk, kBlock>;
-  constexpr int STRIDE = Stager::STRIDE;
-  constexpr int NW = kBlock / kWave;
-  constexpr int TB = kScanChunk / 16;       // token blocks per chunk
-  constexpr int TBW = TB / NW;              // token blocks per wave
-  extern __shared__ __align__(16) unsigned char smem[];
-  T* Qs = reinterpret_cast<T*>(smem);                       // [B][STRIDE]
-  T* Ks = Qs + (size_t)a.B * STRIDE;                         // [chunk][STRIDE]
-  float* red = reinterpret_cast<float*>(Ks + kScanChunk * STRIDE);
-  const int nqb = (a.B + 15) / 16;
-  // stats pass:   part [nqb][NW][16][2] per chunk, run_m [B], run_z [B]
-  // weights pass: row_max [B], row_inv [B]
-  float* part = red;
-  float* run_m = red + nqb * NW * 32;
-  float* run_z = run_m + a.B;
-
-  const int item = xcd_swizzle(blockIdx.x, gridDim.x);
-  const int u = item / a.C, c = item % a.C;
-  const long pb = (long)c * a.span;
-  const long pe = min(pb + (long)a.span, (long)a.P);
-  const int nchunks = (int)((pe - pb + kScanChunk - 1) / kScanChunk);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int g = lane >> 4, col = lane & 15;
-  const T* Qunit = reinterpret_cast<const T*>(a.Q) + (long)u * a.B * D;
-
-  PoolRows<T, D> src;
-  src.Kunit = reinterpret_cast<const T*>(a.K) + (long)u * a.Ls * D;
-  src.seg = a.seg + (long)(u / a.share) * a.S;
-  src.J = a.J;
-  src.mask = (1 << a.J) - 1;
-  src.last = a.Ls - 1;
-  src.p0 = pb;
-  src.np = (int)min((long)kScanChunk, pe - pb);
-  Stager st;
-  st.load(src);
-
-  stage_rows_any<T, D, kBlock>(Qs, a.B, [&](int r) { return Qunit + (long)r * D; });
-  if constexpr (WEIGHTS) {
-    float* row_max = red;
-    float* row_inv = red + a.B;
-    const float* stt = a.stats + (long)u * a.Cs * 2 * a.B;
-    for (int q = threadIdx.x; q < a.B; q += kBlock) {
-      float mx = -INFINITY;
-      for (int k = 0; k < a.Cs; ++k) mx = fmaxf(mx, stt[(long)k * 2 * a.B + q]);
-      float z = 0.f;
-      for (int k = 0; k < a.Cs; ++k) {
-        const float mk = stt[(long)k * 2 * a.B + q];
-        if (mk > -INFINITY) z += stt[(long)k * 2 * a.B + a.B + q] * __expf(mk - mx);
-      }
-      row_max[q] = mx;
-      row_inv[q] = 1.f / z;
-    }
-  } else {
-    for (int q = threadIdx.x; q < a.B; q += kBlock) {
-      run_m[q] = -INFINITY;
-      run_z[q] = 0.f;
-    }
-  }
-
-  for (int ch = 0; ch < nchunks; ++ch) {
-    const long p0 = pb + (long)ch * kScanChunk;
-    const int np = (int)min((long)kScanChunk, pe - p0);
-    __syncthreads();  // the previous chunk's readers are done with Ks
-    st.store(Ks);
-    __syncthreads();
-    if (ch + 1 < nchunks) {
-      src.p0 = p0 + kScanChunk;
-      src.np = (int)min((long)kScanChunk, pe - src.p0);
-      st.load(src);
-    }
-    float wacc[TBW];
-#pragma unroll
-    for (int k = 0; k < TBW; ++k) wacc[k] = 0.f;
-    for (int qb = 0; qb < nqb; ++qb) {
-      const T* arow = Qs + min(qb * 16 + col, a.B - 1) * STRIDE;
-      f32x4 sacc[TBW];
-#pragma unroll
-      for (int k = 0; k < TBW; ++k) {
-        const int tb = wave * TBW + k;
-        sacc[k] = tile_dot<T, D>(arow, Ks + (tb * 16 + col) * STRIDE,
-                                 f32x4{0.f, 0.f, 0.f, 0.f});
-      }
-      // lane holds logit[q = 16 qb + 4 g + i][p = p0 + 16 tb + col]
-      if constexpr (!WEIGHTS) {
-        float* rq = part + (qb * NW + wave) * 32;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          float mx = -INFINITY;
-#pragma unroll
-          for (int k = 0; k < TBW; ++k) {
-            const bool ok = (wave * TBW + k) * 16 + col < np;
-            const float v = ok ? sacc[k][i] * a.scale : -INFINITY;
-            sacc[k][i] = v;
-            mx = fmaxf(mx, v);
-          }
-          mx = wave_max16(mx);
-          float z = 0.f;
-          if (mx > -INFINITY) {
-#pragma unroll
-            for (int k = 0; k < TBW; ++k)
-              if ((wave * TBW + k) * 16 + col < np) z += __expf(sacc[k][i] - mx);
-          }
-          z = wave_sum16(z);
-          if (col == 0) {
-            rq[(4 * g + i) * 2] = mx;
-            rq[(4 * g + i) * 2 + 1] = z;
-          }
-        }
-      } else {
-        const float* row_max = red;
-        const float* row_inv = red + a.B;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int q = qb * 16 + 4 * g + i;
-          if (q < a.B) {
-            const float mq = row_max[q], iz = row_inv[q];
-#pragma unroll
-            for (int k = 0; k < TBW; ++k)
-              wacc[k] += __expf(sacc[k][i] * a.scale - mq) * iz;
-          }
-        }
-      }
-    }
-    if constexpr (!WEIGHTS) {
-      __syncthreads();
-      for (int q = threadIdx.x; q < a.B; q += kBlock) {
-        const int qb = q >> 4, r = q & 15;
-        float mx = run_m[q];
-#pragma unroll
-        for (int w = 0; w < NW; ++w) mx = fmaxf(mx, part[((qb * NW + w) * 16 + r) * 2]);
-        float z = run_m[q] > -INFINITY ? run_z[q] * __expf(run_m[q] - mx) : 0.f;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-          const float mw = part[((qb * NW + w) * 16 + r) * 2];
-          if (mw > -INFINITY) z += part[((qb * NW + w) * 16 + r) * 2 + 1] * __expf(mw - mx);
-        }
-        run_m[q] = mx;
-        run_z[q] = z;
-      }
-    } else {
-      // column sums over the 4 lane groups (rows 4g + i)
-#pragma unroll
-      for (int k = 0; k < TBW; ++k) {
-        const float w = add_xor32(add_xor16(wacc[k]));
-        const int pl = (wave * TBW + k) * 16 + col;
-        if (g == 0 && pl < np) a.wpool[(long)u * a.P + p0 + pl] = w;
-      }
-    }
-  }
-  if constexpr (!WEIGHTS) {
-    __syncthreads();
-    float* stt = a.stats + ((long)u * a.Cs + c) * 2 * a.B;
-    for (int q = threadIdx.x; q < a.B; q += kBlock) {
-      stt[q] = run_m[q];
-      stt[a.B + q] = run_z[q];
-    }
-  }
-}
-
-// bf16 pool rows through an LDS ring filled by direct global->LDS loads.
+// Pool rows through an LDS ring filled by direct global->LDS loads.
 // Row r of the chunk at p0 is pool position min(p0 + r, plast) (rows past
 // the range repeat the last valid row and are masked).
-template <int D>
+template <typename T, int D>
 struct PoolRowPtr {
-  const bf16_t* Kunit;
+  const T* Kunit;
   const int32_t* segs;  // LDS: region ids from s_lo on
   long p0, plast;
   long last;            // the unit's last row (region ids are clamped to it)
   int J, mask, s_lo;
-  __device__ __forceinline__ const bf16_t* operator()(int r) const {
+  __device__ __forceinline__ const T* operator()(int r) const {
     // row numbers fit in 32 bits (ctx_len <= 2^30)
     const int p = (int)min(p0 + r, plast);
     const int t = (segs[(p >> J) - s_lo] << J) | (p & mask);
@@ -219,8 +41,9 @@ struct PoolRowPtr {
 // The pool rows of one chunk into a ring slot, as issue_chunk, but every
 // row's region id is read from LDS before the first load is issued: an LDS
 // read between two of the asm loads waits out its own latency each time.
-template <int CR, int G, int NW, bool STREAM, int D>
-__device__ __forceinline__ void issue_pool_chunk(uint32_t lds_base, const PoolRowPtr<D>& rowptr) {
+template <int CR, int G, int NW, bool STREAM, typename T, int D>
+__device__ __forceinline__ void issue_pool_chunk(uint32_t lds_base,
+                                                 const PoolRowPtr<T, D>& rowptr) {
   constexpr int RPI = 64 / G;
   constexpr int IPW = CR * G / (64 * NW);
   static_assert(IPW * 64 * NW == CR * G, "chunk must fill whole instructions");
@@ -258,6 +81,34 @@ __device__ __forceinline__ void stat_absorb2(float& m, float& z, float m2, float
 // ends of the fp32 range.
 constexpr float kRefSlack = 16.f;
 
+// The ring kernel's shape per element type.  bf16: chunks of 128 rows, 16 of
+// them a wave, every query block in every wave.  fp32: 64 rows of twice the
+// bytes, 16 of them a wave pair that shares the query blocks, so that eight
+// waves still hide the products' latencies.
+template <typename T>
+struct PoolShape {
+  static constexpr bool BF = sizeof(T) == 2;
+  static constexpr int CR = BF ? 128 : 64;     // pool rows per chunk
+  static constexpr int QW = BF ? 1 : 2;        // waves that share a row block's queries
+  static constexpr int RW = kPoolWaves / QW;   // waves over the rows
+  static constexpr int QPG = BF ? 4 : 2;       // query blocks a wave holds in registers
+};
+
+// 16 x 16 logits of one query block and one row block from their 16-byte
+// granules: granule 4 s + g of each row in lane group g.
+template <typename T>
+__device__ __forceinline__ f32x4 granule_dot(u32x4 q, u32x4 k, f32x4 acc) {
+  if constexpr (sizeof(T) == 2) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, q),
+                                                   __builtin_bit_cast(bf16x8, k), acc, 0, 0, 0);
+  } else {
+    const f32x4 qf = __builtin_bit_cast(f32x4, q), kf = __builtin_bit_cast(f32x4, k);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(qf[e], kf[e], acc, 0, 0, 0);
+    return acc;
+  }
+}
+
 // SEL: the workgroup first takes the unit's top-S
 // regions from W (eq. 9) itself, then queues its first pool chunks.  In the
 // weights pass of the token-level path it forms the pool normalisers from
@@ -265,27 +116,33 @@ constexpr float kRefSlack = 16.f;
 // (the step from cached coefficients) the selection is all it adds, and the
 // weights pass that follows reads the region ids the unit's first range
 // wrote.
-template <int WEIGHTS, int D, bool SEL = false>
+template <int WEIGHTS, typename T, int D, bool SEL = false>
 __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
+  using Shape = PoolShape<T>;
   constexpr int NW = kPoolWaves;
-  constexpr int CR = kScanChunk;
-  constexpr int G = D / 8;             // 16-byte granules per row
-  constexpr int CHB = CR * 2 * D;      // bytes per chunk buffer
+  constexpr int CR = Shape::CR;
+  constexpr int QW = Shape::QW, RW = Shape::RW;
+  constexpr int ES = (int)sizeof(T), EPV = 16 / ES;  // element size, elements per granule
+  constexpr int G = D / EPV;           // 16-byte granules per row
+  constexpr int CHB = CR * ES * D;     // bytes per chunk buffer
   constexpr int IPW = CR * G / (64 * NW);
-  constexpr int QSTR = D + 8;
-  constexpr int TBW = CR / 16 / NW;    // token blocks per wave
-  static_assert(TBW >= 1 && TBW * 16 * NW == CR, "whole 16-row blocks per wave");
-  constexpr int QPG = 4;               // query blocks held in registers
-  constexpr int S32 = D / 32;
+  constexpr int QSTR = D + EPV;
+  constexpr int TBW = CR / 16 / RW;    // token blocks per wave
+  static_assert(TBW >= 1 && TBW * 16 * RW == CR, "whole 16-row blocks per wave");
+  constexpr int QPG = Shape::QPG;      // query blocks held in registers
+  constexpr int S32 = G / 4;           // granules of a row per lane group
+  // bf16 query rows are staged in LDS; fp32 ones, twice the bytes, are read
+  // from memory by each group of query blocks
+  constexpr bool QLDS = Shape::BF;
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned char* ring = smem;                                            // [nbuf][CHB]
-  bf16_t* Qs = reinterpret_cast<bf16_t*>(smem + (size_t)a.nbuf * CHB);  // [B][QSTR]
-  int32_t* segs = reinterpret_cast<int32_t*>(Qs + (size_t)a.B * QSTR);  // [seg_cap]
+  T* Qs = reinterpret_cast<T*>(smem + (size_t)a.nbuf * CHB);            // QLDS: [B][QSTR]
+  int32_t* segs = reinterpret_cast<int32_t*>(Qs + (QLDS ? (size_t)a.B * QSTR : 0));  // [seg_cap]
   float* red = reinterpret_cast<float*>(segs + a.seg_cap);
   const int nqb = (a.B + 15) / 16;
-  float* part = red;                   // [nqb][NW][16][2]
-  float* lse2 = red + nqb * NW * 32;   // weights: log2 of the pool's sum of exp, per query
-  float* wsum = lse2 + a.B;            // weights: W' of the range
+  float* part = red;                   // [nqb][RW][16][2]
+  float* lse2 = red + nqb * RW * 32;   // weights: log2 of the pool's sum of exp, per query
+  float* wsum = lse2 + a.B;            // weights: W' of the range [QW][span]
 
   const int item = xcd_swizzle(blockIdx.x, gridDim.x);
   const int u = item / a.C, c = item % a.C;
@@ -294,24 +151,27 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
   const int nch = (int)((pe - pb + CR - 1) / CR);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = lane >> 4, col = lane & 15;
+  // the wave's rows, its share of the query blocks
+  const int rw = QW == 1 ? wave : wave % RW, wq = QW == 1 ? 0 : wave / RW;
 
   // SEL, at most 64 query rows: the query rows are loaded into registers
   // first and written to LDS after the selection, by when they have landed;
   // more rows go to LDS before it
-  const bf16_t* Qunit = reinterpret_cast<const bf16_t*>(a.Q) + (long)u * a.B * D;
-  constexpr int QVR = D / 8;                                  // 16-byte vectors per row
+  const T* Qunit = reinterpret_cast<const T*>(a.Q) + (long)u * a.B * D;
+  constexpr int QVR = G;                                      // 16-byte vectors per row
   constexpr int QV = (64 * QVR + kPoolBlock - 1) / kPoolBlock;  // vectors per thread
   const int qtotal = a.B * QVR;
   u32x4 qpre[QV];
-  const bool qheld = SEL && a.B <= 64;
+  // (the selecting weights pass has at most 64)
+  const bool qheld = QLDS && SEL && (WEIGHTS || a.B <= 64);
   if (qheld) {
 #pragma unroll
     for (int i = 0; i < QV; ++i) {
       const int v = min(i * kPoolBlock + (int)threadIdx.x, qtotal - 1);
-      qpre[i] = *reinterpret_cast<const u32x4*>(Qunit + (long)(v / QVR) * D + (v % QVR) * 8);
+      qpre[i] = *reinterpret_cast<const u32x4*>(Qunit + (long)(v / QVR) * D + (v % QVR) * EPV);
     }
-  } else {
-    stage_rows_any<bf16_t, D, kPoolBlock>(Qs, a.B, [&](int r) { return Qunit + (long)r * D; });
+  } else if constexpr (QLDS) {
+    stage_rows_any<T, D, kPoolBlock>(Qs, a.B, [&](int r) { return Qunit + (long)r * D; });
   }
 
   // region ids of this range: the span's own, or with SEL all S of the unit
@@ -319,14 +179,14 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
   const uint32_t ring_lds = lds_offset(ring);
   const int nbuf = a.nbuf;
   // the pool chunk at the row pointer's p0 into the ring slot at `slot`
-  auto issue = [&](const PoolRowPtr<D>& rows, uint32_t slot) {
+  auto issue = [&](const PoolRowPtr<T, D>& rows, uint32_t slot) {
     if (WEIGHTS || a.stream)
       issue_pool_chunk<CR, G, NW, true>(slot, rows);
     else
       issue_pool_chunk<CR, G, NW, false>(slot, rows);
   };
-  PoolRowPtr<D> rp;
-  rp.Kunit = reinterpret_cast<const bf16_t*>(a.K) + (long)u * a.Ls * D;
+  PoolRowPtr<T, D> rp;
+  rp.Kunit = reinterpret_cast<const T*>(a.K) + (long)u * a.Ls * D;
   rp.segs = segs;
   rp.plast = pe - 1;
   rp.last = a.Ls - 1;
@@ -411,7 +271,7 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
 #pragma unroll
     for (int i = 0; i < QV; ++i) {
       const int v = i * kPoolBlock + (int)threadIdx.x;
-      if (v < qtotal) *reinterpret_cast<u32x4*>(Qs + (v / QVR) * QSTR + (v % QVR) * 8) = qpre[i];
+      if (v < qtotal) *reinterpret_cast<u32x4*>(Qs + (v / QVR) * QSTR + (v % QVR) * EPV) = qpre[i];
     }
   }
   if constexpr (WEIGHTS && !SEL) {
@@ -441,16 +301,26 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
 #pragma unroll
   for (int k = 0; k < TBW; ++k)
 #pragma unroll
-    for (int s = 0; s < S32; ++s) boff[k][s] = granule_offset<G>((wave * TBW + k) * 16 + col, 4 * s + g);
-  for (int qg = 0; qg < nqb; qg += QPG) {
+    for (int s = 0; s < S32; ++s) boff[k][s] = granule_offset<G>((rw * TBW + k) * 16 + col, 4 * s + g);
+  // query block j of a wave in group qg is block qg + j QW + wq
+  for (int qg = 0; qg < nqb; qg += QPG * QW) {
     // query operands of this group, in registers for the whole range
     u32x4 qreg[QPG][S32];
 #pragma unroll
     for (int j = 0; j < QPG; ++j) {
-      const bf16_t* arow = Qs + min((qg + j) * 16 + col, a.B - 1) * QSTR;
+      const int q = min((qg + j * QW + wq) * 16 + col, a.B - 1);
+      const T* arow = QLDS ? Qs + q * QSTR : Qunit + (long)q * D;
 #pragma unroll
       for (int s = 0; s < S32; ++s)
-        qreg[j][s] = *reinterpret_cast<const u32x4*>(arow + 32 * s + 8 * g);
+        qreg[j][s] = *reinterpret_cast<const u32x4*>(arow + EPV * (4 * s + g));
+    }
+    // rows from memory are consumed here, so that the compiler's own wait for
+    // them is not inside the loop below
+    if constexpr (!QLDS) {
+#pragma unroll
+      for (int j = 0; j < QPG; ++j)
+#pragma unroll
+        for (int s = 0; s < S32; ++s) asm volatile("" ::"v"(qreg[j][s]));
     }
     // weights: the log2-domain normalisers of the lane's query rows (rows
     // past B contribute 2^-inf = 0)
@@ -459,7 +329,7 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
     for (int j = 0; j < QPG; ++j)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int q = (qg + j) * 16 + 4 * g + i;
+        const int q = (qg + j * QW + wq) * 16 + 4 * g + i;
         c2[j][i] = WEIGHTS && q < a.B ? lse2[q] : INFINITY;
       }
     // statistics: a lane's reference per query row (log2 units, within
@@ -493,24 +363,32 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
       const unsigned char* buf = ring + (ch % nbuf) * CHB;
 #pragma unroll
       for (int k = 0; k < TBW; ++k) {
-        const int row = (wave * TBW + k) * 16 + col;
+        const int row = (rw * TBW + k) * 16 + col;
         const bool ok = row < np;
         u32x4 bv[S32];
 #pragma unroll
         for (int s = 0; s < S32; ++s) bv[s] = *reinterpret_cast<const u32x4*>(buf + boff[k][s]);
-        // the query blocks' products interleaved: independent accumulators
-        // (blocks past B use clamped query rows; their results are unused)
         f32x4 acc[QPG];
 #pragma unroll
         for (int j = 0; j < QPG; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (Shape::BF) {
+          // the query blocks' products interleaved: independent accumulators
+          // (blocks past B use clamped query rows; their results are unused)
 #pragma unroll
-        for (int s = 0; s < S32; ++s)
+          for (int s = 0; s < S32; ++s)
 #pragma unroll
-          for (int j = 0; j < QPG; ++j)
-            acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                __builtin_bit_cast(bf16x8, qreg[j][s]), __builtin_bit_cast(bf16x8, bv[s]),
-                acc[j], 0, 0, 0);
-        // lane holds logit[q = 16 (qg + j) + 4 g + i][p = p0 + row]
+            for (int j = 0; j < QPG; ++j) acc[j] = granule_dot<T>(qreg[j][s], bv[s], acc[j]);
+        } else {
+          // an fp32 block takes 4 S32 products of 32 cycles: blocks past B
+          // are left out (32 fp32 units, 32 queries: the two passes 17.0 + 11.3 us, without 15.3 + 9.5)
+#pragma unroll
+          for (int j = 0; j < QPG; ++j) {
+            if (qg + j * QW + wq >= nqb) break;  // uniform
+#pragma unroll
+            for (int s = 0; s < S32; ++s) acc[j] = granule_dot<T>(qreg[j][s], bv[s], acc[j]);
+          }
+        }
+        // lane holds logit[q = 16 (qg + j QW + wq) + 4 g + i][p = p0 + row]
         float wk = 0.f;
         if constexpr (!WEIGHTS) {
           // The reference need not be the maximum: it is raised, and the sum
@@ -522,7 +400,7 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
           float t[QPG][4], top = -INFINITY;
 #pragma unroll
           for (int j = 0; j < QPG; ++j) {
-            if (qg + j >= nqb) break;
+            if (qg + j * QW + wq >= nqb) break;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
               t[j][i] = ok ? fmaf(acc[j][i], s2, -sm[j][i]) : -INFINITY;
@@ -532,7 +410,7 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
           if (__builtin_amdgcn_ballot_w64(top > kRefSlack) != 0) {
 #pragma unroll
             for (int j = 0; j < QPG; ++j) {
-              if (qg + j >= nqb) break;
+              if (qg + j * QW + wq >= nqb) break;
 #pragma unroll
               for (int i = 0; i < 4; ++i) {
                 if (t[j][i] > kRefSlack) {
@@ -546,14 +424,14 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
           }
 #pragma unroll
           for (int j = 0; j < QPG; ++j) {
-            if (qg + j >= nqb) break;
+            if (qg + j * QW + wq >= nqb) break;
 #pragma unroll
             for (int i = 0; i < 4; ++i) sz[j][i] += __builtin_amdgcn_exp2f(t[j][i]);
           }
         } else {
 #pragma unroll
           for (int j = 0; j < QPG; ++j) {
-            if (qg + j >= nqb) break;
+            if (qg + j * QW + wq >= nqb) break;
 #pragma unroll
             for (int i = 0; i < 4; ++i)
               wk += __builtin_amdgcn_exp2f(fmaf(acc[j][i], s2, -c2[j][i]));
@@ -563,7 +441,8 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
           wk = add_xor32(add_xor16(wk));
           // query groups add up in place: the same lane owns this position
           // in every group
-          if (g == 0 && ok) wsum[p0 - pb + row] = (qg == 0 ? 0.f : wsum[p0 - pb + row]) + wk;
+          float* ws = wsum + wq * a.span + (p0 - pb) + row;
+          if (g == 0 && ok) *ws = (qg == 0 ? 0.f : *ws) + wk;
         }
       }
     }
@@ -580,9 +459,10 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
           const float m = wave_max16(sm[j][i]);
           const float z = wave_sum16(
               sm[j][i] > -INFINITY ? sz[j][i] * __builtin_amdgcn_exp2f(sm[j][i] - m) : 0.f);
-          if (col == 0 && qg + j < nqb) {
-            part[(((qg + j) * NW + wave) * 16 + 4 * g + i) * 2] = m;
-            part[(((qg + j) * NW + wave) * 16 + 4 * g + i) * 2 + 1] = z;
+          const int qb = qg + j * QW + wq;
+          if (col == 0 && qb < nqb) {
+            part[((qb * RW + rw) * 16 + 4 * g + i) * 2] = m;
+            part[((qb * RW + rw) * 16 + 4 * g + i) * 2 + 1] = z;
           }
         }
       }
@@ -595,14 +475,15 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
       const int qb = q >> 4, r = q & 15;
       float mx = -INFINITY, z = 0.f;
 #pragma unroll
-      for (int w = 0; w < NW; ++w)
-        stat_absorb2(mx, z, part[((qb * NW + w) * 16 + r) * 2], part[((qb * NW + w) * 16 + r) * 2 + 1]);
+      for (int w = 0; w < RW; ++w)
+        stat_absorb2(mx, z, part[((qb * RW + w) * 16 + r) * 2], part[((qb * RW + w) * 16 + r) * 2 + 1]);
       stt[q] = mx;
       stt[a.B + q] = z;
     }
   } else {
     float* dst = a.wpool + (long)u * a.P + pb;
-    for (int i = threadIdx.x; i < (int)(pe - pb); i += kPoolBlock) dst[i] = wsum[i];
+    for (int i = threadIdx.x; i < (int)(pe - pb); i += kPoolBlock)
+      dst[i] = QW == 1 ? wsum[i] : wsum[i] + wsum[a.span + i];
   }
 }
 
@@ -644,36 +525,31 @@ ScanPlan plan_scan(const wf_params& p, bool select) {
   ScanPlan s{};
   const long P = (long)p.segments << p.levels;
   const long U = (long)p.batch * p.heads;
-  const long chunks = (P + kScanChunk - 1) / kScanChunk;
+  const bool bf = p.dtype == WF_BF16;
+  const int es = bf ? 2 : 4;
+  const int cr = bf ? PoolShape<bf16_t>::CR : PoolShape<float>::CR;
+  const int qw = bf ? PoolShape<bf16_t>::QW : PoolShape<float>::QW;
+  const long chunks = (P + cr - 1) / cr;
   const int nqb = (p.q_len + 15) / 16;
-  if (p.dtype == WF_BF16) {
-    // one workgroup per CU, each streaming a long range through the ring
-    const long want = std::max(1L, (long)(device_cu_count() + U - 1) / U);
-    long C = std::min(chunks, want);
-    long cpw = (chunks + C - 1) / C;
-    cpw = std::min(cpw, 32L);  // at most 4096 positions per workgroup
-    s.span = (int)(cpw * kScanChunk);
-    s.chunks = (int)((P + s.span - 1) / s.span);
-    // region ids in LDS: the span's, or all S when the scan selects them
-    s.seg_cap = select ? p.segments : (s.span >> p.levels) + 2;
-    const size_t chb = (size_t)kScanChunk * 2 * p.head_dim;
-    // wave partials, the per-query normalisers, then W' of the range
-    const size_t red_ring =
-        ((size_t)nqb * kPoolWaves * 16 * 2 + (size_t)p.q_len + (size_t)s.span) * sizeof(float);
-    const size_t other = (size_t)p.q_len * (p.head_dim + 8) * 2 + (size_t)s.seg_cap * 4 + red_ring;
-    // three slots (two chunks in flight) measured slightly faster than four
-    s.nbuf = (int)std::min<size_t>(3, (kLdsBudget - std::min(other, kLdsBudget)) / chb);
-    s.lds_bytes = s.nbuf * chb + other;
-    if (s.nbuf < 2) s.nbuf = 0;  // rejected by the caller
-    return s;
-  }
-  // fp32: register-staged chunks, about 1024 workgroups of 1..8 chunks
-  const long cpw = std::max(1L, std::min(8L, U * chunks / 1024));
-  s.span = (int)(cpw * kScanChunk);
+  // one workgroup per CU, each streaming a long range through the ring
+  const long want = std::max(1L, (long)(device_cu_count() + U - 1) / U);
+  long C = std::min(chunks, want);
+  long cpw = (chunks + C - 1) / C;
+  cpw = std::min(cpw, 4096L / cr);  // at most 4096 positions per workgroup
+  s.span = (int)(cpw * cr);
   s.chunks = (int)((P + s.span - 1) / s.span);
-  const size_t stride = (size_t)p.head_dim * 4 + 16;
-  const size_t red_base = ((size_t)nqb * 4 * 16 * 2 + (size_t)2 * p.q_len) * sizeof(float);
-  s.lds_bytes = (size_t)(p.q_len + kScanChunk) * stride + red_base;
+  // region ids in LDS: the span's, or all S when the scan selects them
+  s.seg_cap = select ? p.segments : (s.span >> p.levels) + 2;
+  const size_t chb = (size_t)cr * es * p.head_dim;
+  // wave partials, the per-query normalisers, then W' of the range
+  const size_t red_ring = ((size_t)nqb * (kPoolWaves / qw) * 16 * 2 + (size_t)p.q_len +
+                           (size_t)qw * s.span) * sizeof(float);
+  const size_t queries = bf ? (size_t)p.q_len * (p.head_dim + 8) * 2 : 0;
+  const size_t other = queries + (size_t)s.seg_cap * 4 + red_ring;
+  // three slots (two chunks in flight) measured slightly faster than four
+  s.nbuf = (int)std::min<size_t>(3, (kLdsBudget - std::min(other, kLdsBudget)) / chb);
+  s.lds_bytes = s.nbuf * chb + other;
+  if (s.nbuf < 2) s.nbuf = 0;  // rejected by the caller
   return s;
 }
 
@@ -693,10 +569,16 @@ static hipError_t launch_with_lds(Kernel kern, dim3 grid, int block, size_t lds,
 template <int WEIGHTS, typename T, int D>
 static hipError_t scan_launch(const ScanArgs& a, size_t lds, hipStream_t s) {
   const dim3 grid((unsigned)(a.U * a.C));
-  if constexpr (sizeof(T) == 2)
-    return launch_with_lds(scan_ring_kernel<WEIGHTS, D>, grid, kPoolBlock, lds, s, a);
-  else
-    return launch_with_lds(scan_chunk_kernel<WEIGHTS, T, D>, grid, kBlock, lds, s, a);
+  return launch_with_lds(scan_ring_kernel<WEIGHTS, T, D>, grid, kPoolBlock, lds, s, a);
+}
+
+// The two-pass scan takes fp32 query blocks up to the size whose rows, beside
+// 128 pool rows, fit the LDS (174 rows of 128 channels): callers see the same
+// limit whatever a kernel stages.
+static bool fp32_rows_fit(const wf_params& p) {
+  const size_t stride = (size_t)p.head_dim * 4 + 16, nqb = (size_t)(p.q_len + 15) / 16;
+  return p.dtype == WF_BF16 ||
+         (p.q_len + 128) * stride + (nqb * 128 + 2 * (size_t)p.q_len) * sizeof(float) <= 160 * 1024;
 }
 
 // Whether the statistics pass reads the pool with the streaming (nt) policy.
@@ -705,7 +587,8 @@ static hipError_t scan_launch(const ScanArgs& a, size_t lds, hipStream_t s) {
 // 10.3); a larger one only displaces itself and is found in the Infinity Cache
 // either way (128 MiB: 40.2 + 24.4 us kept, 31.2 + 26.4 streamed).
 static int scan_streams(const wf_params& p) {
-  const size_t pool = ((size_t)p.batch * p.heads * p.segments << p.levels) * 2 * p.head_dim;
+  const size_t pool = ((size_t)p.batch * p.heads * p.segments << p.levels) * p.head_dim *
+                      (p.dtype == WF_BF16 ? 2 : 4);
   return pool > (size_t)32 << 20 ? 1 : 0;
 }
 
@@ -713,7 +596,7 @@ static int scan_streams(const wf_params& p) {
 // themselves; false when the shape does not allow it
 static bool scan_select_args(const wf_params& p, const void* Q, const void* K, const float* W,
                              int32_t* seg_out, int share, ScanArgs& a, ScanPlan& pl) {
-  if (p.dtype != WF_BF16 || p.segments > kSelectLdsSegs || share < 1 ||
+  if (p.segments > kSelectLdsSegs || share < 1 ||
       (p.batch * p.heads) % share != 0)
     return false;
   pl = plan_scan(p, true);
@@ -739,7 +622,8 @@ static bool scan_select_args(const wf_params& p, const void* Q, const void* K, c
   a.stream = scan_streams(p);
   a.scale = effective_scale(p);
   // W in the ring slots before the spare one when it fits there
-  const size_t chb = (size_t)kScanChunk * 2 * p.head_dim;
+  const size_t chb = p.dtype == WF_BF16 ? (size_t)PoolShape<bf16_t>::CR * 2 * p.head_dim
+                                        : (size_t)PoolShape<float>::CR * 4 * p.head_dim;
   a.w_in_lds = (size_t)a.nJ * sizeof(float) <= (size_t)(pl.nbuf - 1) * chb ? 1 : 0;
   return true;
 }
@@ -756,15 +640,15 @@ hipError_t launch_scan_select_weights(const wf_params& p, const void* Q, const v
   ScanArgs a;
   ScanPlan pl;
   // (the pool normalisers take a thread per query row, 64 rows at most)
-  if (p.q_len > 64 || !scan_select_args(p, Q, K, W, seg_out, share, a, pl))
+  if (p.dtype != WF_BF16 || p.q_len > 64 || !scan_select_args(p, Q, K, W, seg_out, share, a, pl))
     return hipErrorInvalidValue;
   a.blocks = blocks;
   a.wpool = wpool;
   a.Cs = 1;
   const dim3 grid((unsigned)(a.U * a.C));
   if (p.head_dim == 128)
-    return launch_with_lds(scan_ring_kernel<1, 128, true>, grid, kPoolBlock, pl.lds_bytes, s, a);
-  return launch_with_lds(scan_ring_kernel<1, 64, true>, grid, kPoolBlock, pl.lds_bytes, s, a);
+    return launch_with_lds(scan_ring_kernel<1, bf16_t, 128, true>, grid, kPoolBlock, pl.lds_bytes, s, a);
+  return launch_with_lds(scan_ring_kernel<1, bf16_t, 64, true>, grid, kPoolBlock, pl.lds_bytes, s, a);
 }
 
 hipError_t launch_scan_select_stats(const wf_params& p, const void* Q, const void* K,
@@ -772,19 +656,26 @@ hipError_t launch_scan_select_stats(const wf_params& p, const void* Q, const voi
                                     hipStream_t s) {
   ScanArgs a;
   ScanPlan pl;
-  if (!scan_select_args(p, Q, K, W, seg_out, 1, a, pl)) return hipErrorInvalidValue;
+  if (!fp32_rows_fit(p) || !scan_select_args(p, Q, K, W, seg_out, 1, a, pl))
+    return hipErrorInvalidValue;
   a.stats = stats;
   a.Cs = pl.chunks;
   const dim3 grid((unsigned)(a.U * a.C));
-  if (p.head_dim == 128)
-    return launch_with_lds(scan_ring_kernel<0, 128, true>, grid, kPoolBlock, pl.lds_bytes, s, a);
-  return launch_with_lds(scan_ring_kernel<0, 64, true>, grid, kPoolBlock, pl.lds_bytes, s, a);
+  auto kern = [&] {
+    if (p.dtype == WF_BF16)
+      return p.head_dim == 128 ? scan_ring_kernel<0, bf16_t, 128, true>
+                               : scan_ring_kernel<0, bf16_t, 64, true>;
+    return p.head_dim == 128 ? scan_ring_kernel<0, float, 128, true>
+                             : scan_ring_kernel<0, float, 64, true>;
+  }();
+  return launch_with_lds(kern, grid, kPoolBlock, pl.lds_bytes, s, a);
 }
 
 hipError_t launch_scan_chunks(const wf_params& p, int weights, const void* Q,
                               const void* K, const int32_t* seg, float* stats,
                               float* wpool, hipStream_t s, int stat_slices, int share) {
-  if (share < 1 || (p.batch * p.heads) % share != 0) return hipErrorInvalidValue;
+  if (share < 1 || (p.batch * p.heads) % share != 0 || !fp32_rows_fit(p))
+    return hipErrorInvalidValue;
   const ScanPlan pl = plan_scan(p);
   ScanArgs a;
   a.share = share;

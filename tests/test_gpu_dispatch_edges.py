@@ -46,3 +46,38 @@ def test_wide_route(wf, w):
     wide = w.name != "w1023"
     assert names[1] == ("skim_weights" if wide else "skim_select"), names
     _check_case(wf, w, w.name, "wide", cached=True)
+
+
+# fp32 keys through the rings: query blocks shared by two waves (1 to 16 of
+# them), one chunk, a chunk and one row, several chunks, both head sizes, a
+# remainder and a tail; below 1024 coefficients the select kernels
+F32 = [
+    _w("f_b1", dtype="f32", heads=2, ctx_len=1024, levels=3, segments=8, budget=64, q_len=1),
+    _w("f_b16", dtype="f32", heads=2, ctx_len=1029, levels=3, segments=9, budget=65, q_len=16,
+       head_dim=64, gen_len=3),
+    _w("f_b33", dtype="f32", heads=4, ctx_len=8 * 300 + 5, levels=3, segments=60, budget=257,
+       q_len=33, gen_len=40),
+    _w("f_b64", dtype="f32", heads=8, ctx_len=4096, levels=4, segments=100, budget=700, q_len=64),
+    _w("f_b100", dtype="f32", heads=6, ctx_len=4 * 257, levels=2, segments=64, budget=100,
+       q_len=100, head_dim=64),
+    _w("f_b160", dtype="f32", heads=4, ctx_len=4 * 300, levels=2, segments=64, budget=100,
+       q_len=160),
+    _w("f_long", dtype="f32", heads=1, ctx_len=32 * 1030, levels=5, segments=400, budget=5000,
+       q_len=20, wavelet="db2"),
+]
+
+
+@pytest.mark.parametrize("w", F32, ids=lambda w: w.name)
+def test_fp32_rings(wf, w):
+    _check_case(wf, w, w.name, "fp32", cached=True)
+
+
+def test_fp32_query_rows_keep_their_limit(wf):
+    """175 rows of 128 channels never fitted the scan: still an error."""
+    import torch
+    p = wf.make_params(batch=1, heads=1, ctx_len=1024, head_dim=128, q_len=176, levels=3,
+                       segments=8, budget=32, dtype="f32")
+    x = torch.zeros(1, 1, 1024, 128, device="cuda")
+    with pytest.raises(Exception):
+        wf.filter_attend(p, x[:, :, :176].contiguous(), x, x)
+    torch.cuda.synchronize()
