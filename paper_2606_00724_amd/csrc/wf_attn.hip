@@ -105,10 +105,13 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
         if (tout) tout[pos] = t;
       }
     };
-    constexpr int EPT = 16;  // weights per thread held in registers
+    // weights per thread held in registers: 16, or 32 past 8192 positions
+    constexpr int EPT = 16;
     if (a.P <= EPT * kAttnRingBlock) {
       // (the selection's first barrier publishes the region ids)
       block_select_topk_regs<kAttnRingBlock, EPT>(Wg, a.P, a.nsel, emit, sh);
+    } else if (a.P <= 2 * EPT * kAttnRingBlock) {
+      block_select_topk_regs<kAttnRingBlock, 2 * EPT>(Wg, a.P, a.nsel, emit, sh);
     } else {
       if (a.w_in_lds) {
         for (int i = threadIdx.x; i < a.P; i += kAttnRingBlock) Wl[i] = Wg[i];

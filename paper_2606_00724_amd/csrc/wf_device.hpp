@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace wf {
 
 constexpr int kWave = 64;
@@ -286,6 +288,59 @@ __device__ __forceinline__ void hist_add(uint32_t* h, bool m, uint32_t d, int la
   }
 }
 
+// The bits every key shares need no pass: the AND and OR of the block's keys
+// (each thread's in kand, kor) give the highest bit in which two keys differ,
+// -1 for none, and the passes start there; mask covers the bits above it and
+// prefix holds them.  Scores of a few octaves share their sign and high
+// exponent bits, and their first pass would otherwise put most of its counts
+// on a few bins.  Also clears the first pass's histogram; ends with a barrier.
+template <int NT>
+__device__ __forceinline__ int select_common_bits(uint32_t kand, uint32_t kor, uint32_t& mask,
+                                                  uint32_t& prefix, SelectShared<NT>& sh) {
+  constexpr int NW = NT / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  // over the wave on DPP rotations and lane swaps (an LDS permute costs its
+  // round trip at each of the six steps)
+  auto row = [](uint32_t v, auto r) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x120 + decltype(r)::value, 0xf, 0xf,
+                                                 false);  // row_ror:r
+  };
+  auto step = [&](auto r) {
+    kand &= row(kand, r);
+    kor |= row(kor, r);
+  };
+  step(std::integral_constant<int, 8>{});
+  step(std::integral_constant<int, 4>{});
+  step(std::integral_constant<int, 2>{});
+  step(std::integral_constant<int, 1>{});
+  const auto a16 = __builtin_amdgcn_permlane16_swap(kand, kand, false, false);
+  const auto o16 = __builtin_amdgcn_permlane16_swap(kor, kor, false, false);
+  kand = a16[0] & a16[1];
+  kor = o16[0] | o16[1];
+  const auto a32 = __builtin_amdgcn_permlane32_swap(kand, kand, false, false);
+  const auto o32 = __builtin_amdgcn_permlane32_swap(kor, kor, false, false);
+  kand = a32[0] & a32[1];
+  kor = o32[0] | o32[1];
+  // in the third histogram, which the second pass clears: when no two keys
+  // differ there is no pass, hence no barrier, before the compaction's counts
+  if (lane == 0) {
+    sh.hist[2][wid] = kand;
+    sh.hist[2][NW + wid] = kor;
+  }
+  for (int i = tid; i < 256; i += NT) sh.hist[0][i] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    kand &= sh.hist[2][w];
+    kor |= sh.hist[2][NW + w];
+  }
+  const uint32_t diff = kand ^ kor;
+  const int top = diff ? 31 - __clz((int)diff) : -1;
+  mask = top < 0 ? 0xffffffffu : top == 31 ? 0u : ~((2u << top) - 1u);
+  prefix = kand & mask;
+  return top;
+}
+
 // Picks the k largest of score[0..n) (ties: lower index first) and calls
 // emit(pos, i) for each picked position i, pos = its rank in ascending order
 // of i (0..k-1).  Requires 1 <= k <= n and 64 <= NT <= 1024.  score may live in LDS or
@@ -308,14 +363,26 @@ __device__ __forceinline__ void block_select_topk(const float* score, int n, int
                                   SelectShared<NT>& sh) {
   static_assert(NT >= 64 && NT <= 1024 && NT % 64 == 0, "block of whole waves");
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  for (int i = tid; i < 256; i += NT) sh.hist[0][i] = 0;
-  __syncthreads();
-  uint32_t prefix = 0, mask = 0, need = (uint32_t)k;
-  for (int pass = 0; pass < 4; ++pass) {
-    const int shift = 24 - 8 * pass;
+  // the bits that every key shares (select_common_bits)
+  uint32_t kand = 0xffffffffu, kor = 0u;
+  for (int b0 = 0; b0 < n; b0 += 8 * NT) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = score[min(b0 + u * NT + tid, n - 1)];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const uint32_t key = order_key(v[u]);
+      kand &= key;
+      kor |= key;
+    }
+  }
+  uint32_t mask, prefix, need = (uint32_t)k;
+  const int top = select_common_bits<NT>(kand, kor, mask, prefix, sh);
+  for (int pass = 0; top - 8 * pass >= 0; ++pass) {
+    const int shift = max(top - 7 - 8 * pass, 0);
     uint32_t* h = sh.hist[pass % 3];
     // the histogram of the next pass was last read two passes ago
-    if (pass < 3)
+    if (top - 8 * (pass + 1) >= 0)
       for (int i = tid; i < 256; i += NT) sh.hist[(pass + 1) % 3][i] = 0;
     // batches of eight elements per thread whose loads are issued together
     // (a load under a per-lane condition would be waited for at once): lanes
@@ -460,11 +527,6 @@ __device__ __forceinline__ void block_select_topk_regs(const float* score, int n
   uint32_t key[EPT];
 #pragma unroll
   for (int j = 0; j < EPT; ++j) key[j] = j < nslot && j * NT + tid < n ? order_key(v[j]) : 0u;
-  // the bits every key shares need no pass: the AND and OR of the keys
-  // over the block give the highest bit in which two keys differ, and the
-  // passes start there (scores of a few octaves share their sign and high
-  // exponent bits, and their first pass would otherwise put most of its
-  // counts on a few bins)
   constexpr int NW = NT / 64;
   uint32_t kand = 0xffffffffu, kor = 0u;
 #pragma unroll
@@ -473,26 +535,8 @@ __device__ __forceinline__ void block_select_topk_regs(const float* score, int n
       kand &= key[j];
       kor |= key[j];
     }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    kand &= (uint32_t)__shfl_xor((int)kand, off);
-    kor |= (uint32_t)__shfl_xor((int)kor, off);
-  }
-  if (lane == 0) {  // sh.cnt is free until the compaction, after the passes' barriers
-    sh.cnt[0][wid] = kand;
-    sh.cnt[0][NW + wid] = kor;
-  }
-  for (int i = tid; i < 256; i += NT) sh.hist[0][i] = 0;
-  __syncthreads();
-#pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    kand &= sh.cnt[0][w];
-    kor |= sh.cnt[0][NW + w];
-  }
-  const uint32_t diff = kand ^ kor;
-  const int top = diff ? 31 - __clz((int)diff) : -1;  // highest differing bit
-  uint32_t mask = top < 0 ? 0xffffffffu : top == 31 ? 0u : ~((2u << top) - 1u);
-  uint32_t prefix = kand & mask, need = (uint32_t)k;
+  uint32_t mask, prefix, need = (uint32_t)k;
+  const int top = select_common_bits<NT>(kand, kor, mask, prefix, sh);
   for (int pass = 0; top - 8 * pass >= 0; ++pass) {
     // digit bits top - 8 pass .. top - 8 pass - 7; the last digit may reach
     // below bit 0 and is then taken from bit 0 (its upper bits are resolved

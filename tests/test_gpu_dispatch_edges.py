@@ -81,3 +81,35 @@ def test_fp32_query_rows_keep_their_limit(wf):
     with pytest.raises(Exception):
         wf.filter_attend(p, x[:, :, :176].contiguous(), x, x)
     torch.cuda.synchronize()
+
+
+# the selections past the register reach of 8192 scores (32 a thread up to
+# 16384, then from LDS or memory), on the token-level path and the general one
+POOL = [
+    _w("p8192", heads=1, ctx_len=16384, levels=3, segments=1024, budget=4000),
+    _w("p8200", heads=1, ctx_len=16384, levels=3, segments=1025, budget=4001),
+    _w("p16384", heads=1, ctx_len=32768, levels=5, segments=512, budget=9000, gen_len=5),
+    _w("p16416", heads=1, ctx_len=32768, levels=5, segments=513, budget=3000),
+    _w("p27136", heads=1, ctx_len=27136 + 17, levels=6, segments=424, budget=20000, q_len=16),
+]
+
+
+@pytest.mark.parametrize("w", POOL, ids=lambda w: w.name)
+def test_large_pools(wf, w):
+    _check_case(wf, w, w.name, "pool", cached=True)
+
+
+@pytest.mark.parametrize("dtype,levels", [("bf16", 3), ("bf16", 2), ("f32", 2)])
+def test_equal_scores_need_no_pass(wf, dtype, levels):
+    """Equal keys: no two scores differ, the lowest positions are taken."""
+    import torch
+    p = wf.make_params(batch=1, heads=20, ctx_len=1024, head_dim=128, q_len=32, levels=levels,
+                       segments=40, budget=70, dtype=dtype)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    K = torch.ones(1, 20, 1024, 128, dtype=dt, device="cuda")
+    Q = torch.full((1, 20, 32, 128), 0.25, dtype=dt, device="cuda")
+    for _ in range(3):
+        O, tok, seg = wf.filter_attend(p, Q, K, K, want_indices=True)
+        torch.cuda.synchronize()
+        assert (seg.cpu() == torch.arange(40, dtype=torch.int32)).all()
+        assert (tok.cpu() == torch.arange(70, dtype=torch.int32)).all()
