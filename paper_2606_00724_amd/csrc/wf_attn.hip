@@ -592,9 +592,8 @@ AttnPlan plan_attn(const wf_params& p, long nrows) {
   const int es = p.dtype == WF_BF16 ? 2 : 4;
   // one workgroup per CU streaming its rows through the LDS ring
   const long chunks = std::max(1L, (nrows + kRingRows - 1) / kRingRows);
-  const long want = std::max(1L, (long)(device_cu_count() + U - 1) / U);
-  long splits = std::min(chunks, want);
-  splits = std::max(splits, (nrows + 4095) / 4096);  // at most 4096 rows each
+  // (at most 4096 rows)
+  const long splits = ranges_per_unit(U, chunks, device_cu_count(), 4096L / kRingRows);
   const long cps = (chunks + splits - 1) / splits;
   a.rps = (int)(cps * kRingRows);
   a.splits = (int)((nrows + a.rps - 1) / a.rps);

@@ -901,9 +901,10 @@ static FastPlan plan_token(const wf_params& p, int J, long Lf, bool lse, bool ga
   // holds its results until its keys are read (token_skim_held_kernel),
   // whenever a range of that shape has at most kHeldChunks chunks.
   if (lse && J == 5 && !gather && !db2_token_path(p) && p.q_len <= 16 * kFastMaxQBlocks) {
-    const long R = std::min(chunks, std::max(1L, ((long)device_cu_count() + U - 1) / U));
-    const long cpr = (chunks + R - 1) / R;
-    if (cpr <= kHeldChunks) {
+    const long most = std::min(chunks, std::max(1L, ((long)device_cu_count() + U - 1) / U));
+    if ((chunks + most - 1) / most <= kHeldChunks) {
+      const long R = ranges_per_unit(U, chunks, device_cu_count(), kHeldChunks);
+      const long cpr = (chunks + R - 1) / R;
       f.span = (int)(cpr * kScanChunk);
       f.R = (int)((Lf + f.span - 1) / f.span);
       f.par_cap = 0;
@@ -922,16 +923,24 @@ static FastPlan plan_token(const wf_params& p, int J, long Lf, bool lse, bool ga
   // Two resident workgroups per CU, each two chunks deep, stream faster than
   // one three deep (the barrier of one overlaps the other's loads); that
   // shape is taken whenever two fit in the CU's LDS.
-  const long want0 = std::max(1L, (2L * device_cu_count() + U - 1) / U);
-  const long cpr0 = (chunks + std::min(chunks, want0) - 1) / std::min(chunks, want0);
+  // (gathered rows: no range longer than ceil(slots / U) of them, as its ids
+  // take LDS; the db2 skim: none too long to hold its results where that
+  // many are not)
+  auto ranges = [&](long slots) {
+    const long most = std::min(chunks, std::max(1L, (slots + U - 1) / U));
+    const long cpr = (chunks + most - 1) / most;
+    const long max_cpr = gather ? cpr : cpr <= kHeldChunks ? kHeldChunks : chunks;
+    return ranges_per_unit(U, chunks, slots, max_cpr);
+  };
+  const long R0 = ranges(2L * device_cu_count());
+  const long cpr0 = (chunks + R0 - 1) / R0;
   const size_t ids = gather ? (size_t)(((cpr0 * kScanChunk) >> (J + 1)) + 2) * 4 : 0;
   const size_t fixed = bb + ((ids + 15) & ~(size_t)15);
   const size_t fit2 = kLdsPerCu / 2 > fixed ? (kLdsPerCu / 2 - fixed) / chb : 0;
   // (the db2 skim needs more than 128 registers a lane: one workgroup per CU)
   const int per_cu = fit2 >= 2 && !db2_token_path(p) &&
                      token_skim_waves_per_simd(p.head_dim, J, lse) >= 4 ? 2 : 1;
-  const long want = std::max(1L, ((long)per_cu * device_cu_count() + U - 1) / U);
-  const long R = std::min(chunks, want);
+  const long R = ranges((long)per_cu * device_cu_count());
   const long cpr = (chunks + R - 1) / R;
   f.span = (int)(cpr * kScanChunk);
   f.R = (int)((Lf + f.span - 1) / f.span);

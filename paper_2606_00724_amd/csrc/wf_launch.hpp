@@ -72,6 +72,29 @@ inline long remainder_len(const wf_params& p) { return (long)p.ctx_len - filtere
 // Floats per row of the two-stage skim's coarse logits: L >> J rounded up to
 // whole 16-byte vectors (the recursion's rows are not padded).
 inline long skim_ld(const wf_params& p) { return (((long)p.ctx_len >> p.levels) + 3) & ~3L; }
+// Ranges each of U units' `chunks` chunks are split into, for a kernel of which
+// `slots` workgroups are resident at once and a workgroup takes at most max_cpw
+// chunks.  ceil(slots / U) ranges fill every slot, but where U does not divide
+// the slots the workgroups past them run after the others, nearly alone: one
+// range fewer then ends sooner, as fewer workgroups share the same bandwidth
+// (about 0.7 of the CUs reach it) and the fixed part of a workgroup (its
+// selection, its first loads: about six chunks) is paid once.  28 units of 61K
+// keys, 32-token blocks: 216.8 us a call with 10 ranges a unit, 147.5 with 9; 100 units
+// of 32K: 317.6 and 224.6.  Never more ranges than ceil(slots / U) except for max_cpw.
+inline long ranges_per_unit(long U, long chunks, long slots, long max_cpw) {
+  const long up = std::min(chunks, std::max(1L, (slots + U - 1) / U));
+  const long down = std::min(chunks, std::max(1L, slots / U));
+  const long least = (chunks + max_cpw - 1) / max_cpw;
+  auto cost = [&](long C) {
+    const double cpw = (double)((chunks + C - 1) / C), fixed = 6.0;
+    const long n = U * ((chunks + (long)cpw - 1) / (long)cpw), rest = n % slots;
+    return (double)(n / slots) * (cpw + fixed) +
+           (rest ? cpw * std::max(0.7, (double)rest / (double)slots) + fixed : 0.0);
+  };
+  const long C = std::max(least, cost(down) <= cost(up) ? down : up);
+  return std::min(chunks, C);
+}
+
 // Whether a call has the coefficients to fill the chip with a W kernel and
 // selections in the kernels that consume them, whatever its keys, query rows
 // and coefficient count.  16 units of 128 bf16 query rows: with 1024

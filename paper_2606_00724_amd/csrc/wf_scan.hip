@@ -532,10 +532,9 @@ ScanPlan plan_scan(const wf_params& p, bool select) {
   const long chunks = (P + cr - 1) / cr;
   const int nqb = (p.q_len + 15) / 16;
   // one workgroup per CU, each streaming a long range through the ring
-  const long want = std::max(1L, (long)(device_cu_count() + U - 1) / U);
-  long C = std::min(chunks, want);
-  long cpw = (chunks + C - 1) / C;
-  cpw = std::min(cpw, 4096L / cr);  // at most 4096 positions per workgroup
+  // (at most 4096 positions)
+  const long C = ranges_per_unit(U, chunks, device_cu_count(), 4096L / cr);
+  const long cpw = (chunks + C - 1) / C;
   s.span = (int)(cpw * cr);
   s.chunks = (int)((P + s.span - 1) / s.span);
   // region ids in LDS: the span's, or all S when the scan selects them

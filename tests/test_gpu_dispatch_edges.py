@@ -113,3 +113,20 @@ def test_equal_scores_need_no_pass(wf, dtype, levels):
         torch.cuda.synchronize()
         assert (seg.cpu() == torch.arange(40, dtype=torch.int32)).all()
         assert (tok.cpu() == torch.arange(70, dtype=torch.int32)).all()
+
+
+# unit counts that do not divide the CUs: fewer, longer ranges
+RANGES = [
+    _w("r28_held", heads=28, ctx_len=32 * 330 + 7, levels=5, segments=30, budget=500),
+    _w("r28_two", heads=28, ctx_len=8 * 700, levels=3, segments=90, budget=500, head_dim=64),
+    _w("r100", heads=100, ctx_len=16 * 130, levels=4, segments=20, budget=200, q_len=17),
+    _w("r28_db2", heads=28, ctx_len=64 * 70, levels=6, segments=12, budget=300, wavelet="db2"),
+    _w("r28_general", heads=28, ctx_len=4 * 900, levels=2, segments=200, budget=500, q_len=40),
+    _w("r40_f32", heads=40, ctx_len=8 * 200, levels=3, segments=60, budget=300, dtype="f32"),
+    _w("r300", heads=300, ctx_len=8 * 40, levels=3, segments=20, budget=100, q_len=8),
+]
+
+
+@pytest.mark.parametrize("w", RANGES, ids=lambda w: w.name)
+def test_ranges_of_odd_unit_counts(wf, w):
+    _check_case(wf, w, w.name, "ranges", cached=True)
