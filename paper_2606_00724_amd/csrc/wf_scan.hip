@@ -489,29 +489,29 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
 
 constexpr int kScanSelectBlock = 1024;
 
-__global__ __launch_bounds__(kScanSelectBlock) void scan_select_kernel(
-    ScanSelectArgs a, int w_in_lds, int seg_in_lds) {
+__global__ __launch_bounds__(kScanSelectBlock) void scan_select_kernel(ScanSelectArgs a,
+                                                                       int seg_in_lds) {
   __shared__ SelectShared<kScanSelectBlock> sh;
-  extern __shared__ float wsh[];
+  extern __shared__ int32_t seg_sh[];
   const int u = blockIdx.x;
   const float* W = a.wpool + (long)u * a.P;
-  // the unit's region ids, read by the emits (from LDS when they fit)
+  // the unit's region ids, read by the emits (from LDS when they fit; the
+  // selection's first barrier publishes them)
   const int32_t* seg = a.seg + (long)u * a.S;
   if (seg_in_lds) {
-    int32_t* seg_sh = reinterpret_cast<int32_t*>(wsh + (w_in_lds ? a.P : 0));
     for (int i = threadIdx.x; i < a.S; i += kScanSelectBlock) seg_sh[i] = seg[i];
     seg = seg_sh;
   }
-  if (w_in_lds)
-    for (int i = threadIdx.x; i < a.P; i += kScanSelectBlock) wsh[i] = W[i];
-  __syncthreads();
   const int J = a.J;
   const int mask = (1 << J) - 1;
   int32_t* tok = a.tok + (long)u * a.keff;
   auto emit = [&](uint32_t pos, int p) { tok[pos] = (seg[p >> J] << J) | (p & mask); };
-  // one instance per address space of the weights
-  if (w_in_lds)
-    block_select_topk<kScanSelectBlock>(wsh, a.P, a.keff, emit, sh);
+  // weights in registers, eight or 16 a thread (28 units of 13184: 25.7 us
+  // from LDS, 16.0 here), else from memory
+  if (a.P <= 8 * kScanSelectBlock)
+    block_select_topk_regs<kScanSelectBlock, 8>(W, a.P, a.keff, emit, sh);
+  else if (a.P <= 16 * kScanSelectBlock)
+    block_select_topk_regs<kScanSelectBlock, 16>(W, a.P, a.keff, emit, sh);
   else
     block_select_topk<kScanSelectBlock>(W, a.P, a.keff, emit, sh);
 }
@@ -722,18 +722,10 @@ hipError_t launch_scan_select(const wf_params& p, const float* wpool,
   a.S = p.segments;
   a.P = p.segments << p.levels;
   a.keff = wf_effective_budget(&p);
-  const int in_lds = a.P <= kSelectLdsFloats ? 1 : 0;
   const int seg_in_lds = a.S <= kSelectLdsSegs ? 1 : 0;
-  // W' when it fits, then the region ids when they fit
-  const size_t lds =
-      ((in_lds ? (size_t)a.P : 0) + (seg_in_lds ? (size_t)a.S : 0)) * sizeof(float);
-  if (lds > 32768) {  // with the static arrays, past the default 64 KiB
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(scan_select_kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(scan_select_kernel, dim3((unsigned)a.U),
-                     dim3(kScanSelectBlock), lds, s, a, in_lds, seg_in_lds);
+  const size_t lds = seg_in_lds ? (size_t)a.S * sizeof(int32_t) : 0;
+  hipLaunchKernelGGL(scan_select_kernel, dim3((unsigned)a.U), dim3(kScanSelectBlock), lds, s, a,
+                     seg_in_lds);
   return hipGetLastError();
 }
 

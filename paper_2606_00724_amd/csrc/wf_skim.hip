@@ -377,15 +377,17 @@ __global__ __launch_bounds__(kBlock) void skim_weights_kernel(SkimSelectArgs a, 
 
 // The same W for a narrower candidate set (a thousand or so columns a unit),
 // where a thread per four columns leaves too few threads: thread (g, c) adds
-// the terms of query rows 16 g .. 16 g + 15 (and every 64th row after them)
-// of four adjacent columns, the four groups' partial sums meet in LDS and are
-// added in order of g.  The first batch of logits is loaded before the
-// slices are merged, so that the two loads overlap.  ld is a multiple of 4:
-// the last group of a row may reach into its padding, whose sums are not
-// stored.
+// the terms of 64 / NQG query rows (and those 64 rows on) of four adjacent
+// columns, the NQG groups' partial sums meet in LDS and are added in order of
+// g.  The first batch of logits is loaded before the slices are merged, so
+// that the two loads overlap.  ld is a multiple of 4: the last group of a row
+// may reach into its padding, whose sums are not stored.  NQG = 16 where a
+// workgroup has at most 16 groups of columns, which would leave three quarters
+// of the lanes of NQG = 4 idle (16 units of 128 rows, 1024 columns: 10.9 us
+// with 4, 7.6 with 16; 28 units of 32 rows, 1000 columns: 11.2 and 6.0).
+template <int NQG>
 __global__ __launch_bounds__(kBlock) void skim_weights_rows_kernel(SkimSelectArgs a, int parts) {
-  constexpr int QB = 16;             // query rows of one batch
-  constexpr int NQG = 4;             // query groups
+  constexpr int QB = 64 / NQG;       // query rows of one batch
   constexpr int CPW = kBlock / NQG;  // four-column groups per step
   __shared__ float row_c[WF_MAX_Q_LEN];
   __shared__ float pm[4][64], pz[4][64];
@@ -693,7 +695,20 @@ hipError_t launch_skim_tiles(const wf_params& p, bool fused, const void* Q,
                            skim_ld(p), nullptr, 0, Q, K, approx, logits, stats, s);
 }
 
-static hipError_t skim_select_common(const wf_params& p, long nJ, long ld, int ntiles, int S,
+// W of args `a` over at least two workgroups per CU, at most 1024 columns each
+static void launch_weights_rows(const SkimSelectArgs& a, hipStream_t s) {
+  const long n4 = (a.nJ + 3) / 4;
+  const long want = std::max((a.nJ + 1023L) / 1024,
+                             (2L * device_cu_count() + a.U - 1) / a.U);
+  const int parts = (int)std::min(n4, want);
+  const dim3 grid((unsigned)(a.U * parts));
+  if ((n4 + parts - 1) / parts <= 16)
+    hipLaunchKernelGGL(skim_weights_rows_kernel<16>, grid, dim3(kBlock), 0, s, a, parts);
+  else
+    hipLaunchKernelGGL(skim_weights_rows_kernel<4>, grid, dim3(kBlock), 0, s, a, parts);
+}
+
+static hipError_t skim_select_common(const wf_params& p, bool two_stage, long nJ, long ld, int ntiles, int S,
                                      const int32_t* parent, int npar, int pairs,
                                      const float* logits, const float* stats, float* W,
                                      int32_t* out, hipStream_t s) {
@@ -718,9 +733,16 @@ static hipError_t skim_select_common(const wf_params& p, long nJ, long ld, int n
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  // wide candidate sets: W over all CUs first (1024 columns a workgroup)
-  const int w_ready = a.nJ >= 4096 && (a.nJ & 3) == 0 && a.ld == a.nJ ? 1 : 0;
-  if (w_ready) {
+  // W over all CUs first: on the two-stage path where the call has the
+  // coefficients to fill the chip with it (28 units of 1914: 24.2 us in one
+  // kernel, 11.7 + 7.8 in two; 32 of 512: 14.5 and 7.1 + 6.4), on the
+  // recursion's scales from 4096 candidates on (1024 columns a workgroup)
+  int w_ready = 0;
+  if (two_stage && wide_weights(p)) {
+    w_ready = 1;
+    launch_weights_rows(a, s);
+  } else if (a.nJ >= 4096 && (a.nJ & 3) == 0 && a.ld == a.nJ) {
+    w_ready = 1;
     const int parts = (a.nJ + 1023) / 1024;
     hipLaunchKernelGGL(skim_weights_kernel, dim3((unsigned)(a.U * parts)), dim3(kBlock), 0, s,
                        a, parts);
@@ -764,20 +786,14 @@ hipError_t launch_skim_weights(const wf_params& p, int ntiles, const float* logi
   a.ld = (int)skim_ld(p);
   a.ntiles = ntiles;
   if (!logits || !stats || !W || a.nJ == 0) return hipErrorInvalidValue;
-  // at most 1024 columns a workgroup, and two workgroups per CU at least
-  const long n4 = (a.nJ + 3) / 4;
-  const long want = std::max((a.nJ + 1023L) / 1024,
-                             (2L * device_cu_count() + a.U - 1) / a.U);
-  const int parts = (int)std::min(n4, want);
-  hipLaunchKernelGGL(skim_weights_rows_kernel, dim3((unsigned)(a.U * parts)), dim3(kBlock), 0,
-                     s, a, parts);
+  launch_weights_rows(a, s);
   return hipGetLastError();
 }
 
 hipError_t launch_skim_select(const wf_params& p, int ntiles,
                               const float* logits, const float* stats,
                               float* W, int32_t* seg, hipStream_t s) {
-  return skim_select_common(p, (long)p.ctx_len >> p.levels, skim_ld(p), ntiles, p.segments, nullptr, 0,
+  return skim_select_common(p, true, (long)p.ctx_len >> p.levels, skim_ld(p), ntiles, p.segments, nullptr, 0,
                             0, logits, stats, W, seg, s);
 }
 
@@ -815,14 +831,14 @@ hipError_t launch_rec_select(const wf_params& p, int b, long n, int keep,
                              const float* stats, float* W, int32_t* out, hipStream_t s) {
   const int cpt = rec_cpt(p, b);
   const int ntiles = (int)((n + cpt - 1) / cpt);
-  return skim_select_common(p, n, n, ntiles, keep, parent, npar, b == 1 ? 1 : 0, logits,
+  return skim_select_common(p, false, n, n, ntiles, keep, parent, npar, b == 1 ? 1 : 0, logits,
                             stats, W, out, s);
 }
 hipError_t launch_rec_select_slices(const wf_params& p, int b, long n, int keep,
                                     const int32_t* parent, int npar, int nslices,
                                     const float* logits, const float* stats, float* W,
                                     int32_t* out, hipStream_t s) {
-  return skim_select_common(p, n, n, nslices, keep, parent, npar, b == 1 ? 1 : 0, logits,
+  return skim_select_common(p, false, n, n, nslices, keep, parent, npar, b == 1 ? 1 : 0, logits,
                             stats, W, out, s);
 }
 
