@@ -531,22 +531,35 @@ ScanPlan plan_scan(const wf_params& p, bool select) {
   const int qw = bf ? PoolShape<bf16_t>::QW : PoolShape<float>::QW;
   const long chunks = (P + cr - 1) / cr;
   const int nqb = (p.q_len + 15) / 16;
-  // one workgroup per CU, each streaming a long range through the ring
-  // (at most 4096 positions)
+  const size_t chb = (size_t)cr * es * p.head_dim;
+  const size_t queries = bf ? (size_t)p.q_len * (p.head_dim + 8) * 2 : 0;
+  // LDS beside the ring of a workgroup with `span` positions and seg_cap
+  // region ids: queries, ids, wave partials, the per-query normalisers, W'
+  auto beside = [&](long span, long seg_cap) {
+    return queries + (size_t)seg_cap * 4 +
+           ((size_t)nqb * (kPoolWaves / qw) * 16 * 2 + (size_t)p.q_len + (size_t)qw * span) *
+               sizeof(float);
+  };
+  auto slots = [&](size_t other) {
+    // three slots (two chunks in flight) measured slightly faster than four
+    return (int)std::min<size_t>(3, (kLdsBudget - std::min(other, kLdsBudget)) / chb);
+  };
+  // one workgroup per CU, each streaming a long range through the ring (at
+  // most 4096 positions; no longer than ceil(CUs / U) ranges make it where
+  // W' of more would leave no room for two slots).  The same ranges whether
+  // or not the scan selects: both forms share their statistics.
+  const long most = std::min(chunks, std::max(1L, ((long)device_cu_count() + U - 1) / U));
+  const long most_cpw = std::min((chunks + most - 1) / most, 4096L / cr);
+  auto fits = [&](long c) { return slots(beside(c * cr, (c * cr >> p.levels) + 2)) >= 2; };
   const long C = ranges_per_unit(U, chunks, device_cu_count(), 4096L / cr);
-  const long cpw = (chunks + C - 1) / C;
+  long cpw = (chunks + C - 1) / C;
+  if (!fits(cpw) || !fits(most_cpw)) cpw = most_cpw;
   s.span = (int)(cpw * cr);
   s.chunks = (int)((P + s.span - 1) / s.span);
   // region ids in LDS: the span's, or all S when the scan selects them
   s.seg_cap = select ? p.segments : (s.span >> p.levels) + 2;
-  const size_t chb = (size_t)cr * es * p.head_dim;
-  // wave partials, the per-query normalisers, then W' of the range
-  const size_t red_ring = ((size_t)nqb * (kPoolWaves / qw) * 16 * 2 + (size_t)p.q_len +
-                           (size_t)qw * s.span) * sizeof(float);
-  const size_t queries = bf ? (size_t)p.q_len * (p.head_dim + 8) * 2 : 0;
-  const size_t other = queries + (size_t)s.seg_cap * 4 + red_ring;
-  // three slots (two chunks in flight) measured slightly faster than four
-  s.nbuf = (int)std::min<size_t>(3, (kLdsBudget - std::min(other, kLdsBudget)) / chb);
+  const size_t other = beside(s.span, s.seg_cap);
+  s.nbuf = slots(other);
   s.lds_bytes = s.nbuf * chb + other;
   if (s.nbuf < 2) s.nbuf = 0;  // rejected by the caller
   return s;
