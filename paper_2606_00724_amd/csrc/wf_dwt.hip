@@ -310,7 +310,7 @@ hipError_t launch_dwt(const wf_params& p, const void* K, float* approx,
   const Taps taps = make_taps(p.wavelet, p.levels);
   if (p.wavelet == WF_HAAR && !details) {
     // A_J is the scaled block sum: coefficient tiles at streaming rate
-    const int cpt = haar_cpt(p.levels);
+    const int cpt = haar_cpt(p.levels, a.U, a.nJ);
     a.ntiles = (int)((a.nJ + cpt - 1) / cpt);
     const size_t lds = (size_t)cpt * (p.head_dim + kCoefPad) * sizeof(float);
     auto run = [&](auto kern) -> hipError_t {

@@ -645,4 +645,17 @@ inline const EdgeTaps& symmetric_edge_filters(int J) {
 // Haar coefficient tile size at level J.
 inline int haar_cpt(int J) { return std::min(kMaxCoefTile, std::max(16, 2048 >> J)); }
 
+// The same for U units of nJ coefficients: halved, down to the 16 of one MFMA
+// tile, while there is at most one tile per CU.  A tile's workgroup has 32 KiB
+// of loads in flight, less than a CU needs, and none during its products: two
+// fp32 units of 128 coefficients 11.0 -> 6.0 us, 16 bf16 units of 1024 23.8 ->
+// 20.8, A_J of 32 units of 512 14.1 -> 12.1.  With more tiles than that to
+// begin with (28 units of 512, J = 6) halving them costs 1.5 us, and four per
+// CU cost the W kernel more slices to merge than the tiles save (8.0 -> 10.4).
+inline int haar_cpt(int J, long U, long nJ) {
+  int cpt = haar_cpt(J);
+  while (cpt > 16 && U * ((nJ + cpt - 1) / cpt) <= device_cu_count()) cpt /= 2;
+  return cpt;
+}
+
 }  // namespace wf

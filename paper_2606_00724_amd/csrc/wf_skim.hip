@@ -595,7 +595,7 @@ SkimPlan plan_skim(const wf_params& p, bool fused) {
     k.cpt = kMaxCoefTile;
   } else if (p.wavelet == WF_HAAR) {
     k.source = keys_stream(p) ? kHaarStream : kHaarSum;
-    k.cpt = std::min(kMaxCoefTile, std::max(16, 2048 >> J));
+    k.cpt = haar_cpt(J, (long)p.batch * p.heads, (long)p.ctx_len >> J);
   } else {
     k.source = kCascade;
     k.cpt = kMaxCoefTile;  // 4 (d=128) or 8 (d=64) streams of 16 or 8
