@@ -174,7 +174,7 @@ static Layout layout_for(const wf_params& p, int op, long attn_rows) {
     l.sstats = take(U * fp.R * 2 * B * sizeof(float));
   } else if (skim) {
     const SkimPlan sp = plan_skim(p, op == WF_OP_FUSED);  // from A_J otherwise
-    l.logits = take(U * B * (size_t)skim_ld(p) * sizeof(float));
+    l.logits = take(U * B * nJ * sizeof(float));
     l.sstats = take(U * sp.ntiles * 2 * B * sizeof(float));
   }
   // On the coefficient-tile path, and with fp32 keys, the attention's partials

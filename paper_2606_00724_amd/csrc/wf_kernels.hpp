@@ -31,14 +31,13 @@ struct SkimTileArgs {
   const void* K;        // [U][L][D]      (Haar sum / cascade)
   const float* approx;  // [U][nJ][D]     (from approx)
   const void* Q;        // [U][B][D]
-  float* logits;        // [U][B][ld]
+  float* logits;        // [U][B][nJ]
   float* stats;         // [U][ntiles][2][B]: row max, then row sum of exp
   const int32_t* parent;  // nullable: coefficient n is block 2 parent[n/2] + n%2
                           // of level J ([U][npar], ascending block ids at J + 1)
   int npar;
   long Ls;              // rows per unit in K (L: the filtered rows)
   int U, L, B, J, nJ;
-  int ld;               // floats per row of logits (>= nJ)
   int cpt;              // coefficients per tile
   int ntiles;           // tiles per unit
   int boundary;
@@ -46,7 +45,7 @@ struct SkimTileArgs {
 };
 
 struct SkimSelectArgs {
-  const float* logits;  // [U][B][ld]
+  const float* logits;  // [U][B][nJ]
   const float* stats;   // [U][ntiles][2][B]
   float* W;             // [U][nJ] out
   int32_t* seg;         // [U][S] out (block ids), or [U][2S] tokens when pairs
@@ -54,7 +53,6 @@ struct SkimSelectArgs {
   int npar;
   int pairs;            // emit the two tokens of each kept 2-token block
   int U, B, nJ, ntiles, S;
-  int ld;               // floats per row of logits (>= nJ)
 };
 
 struct ScanArgs {

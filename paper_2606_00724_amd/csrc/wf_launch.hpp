@@ -69,9 +69,6 @@ inline long filtered_len(const wf_params& p) {
   return ((long)p.ctx_len >> p.levels) << p.levels;
 }
 inline long remainder_len(const wf_params& p) { return (long)p.ctx_len - filtered_len(p); }
-// Floats per row of the two-stage skim's coarse logits: L >> J rounded up to
-// whole 16-byte vectors (the recursion's rows are not padded).
-inline long skim_ld(const wf_params& p) { return (((long)p.ctx_len >> p.levels) + 3) & ~3L; }
 // Ranges each of U units' `chunks` chunks are split into, for a kernel of which
 // `slots` workgroups are resident at once and a workgroup takes at most max_cpw
 // chunks.  ceil(slots / U) ranges fill every slot, but where U does not divide
@@ -179,7 +176,7 @@ hipError_t launch_rec_select_slices(const wf_params& p, int b, long n, int keep,
 hipError_t launch_skim_select(const wf_params& p, int ntiles,
                               const float* logits, const float* stats,
                               float* W, int32_t* seg, hipStream_t s);
-// W [U][nJ] of the coarse logits [U][B][skim_ld] and their tiles' (max, sum)
+// W [U][nJ] of the coarse logits [U][B][nJ] and their tiles' (max, sum)
 // pairs, spread over enough workgroups per unit to fill the chip (no
 // selection).
 hipError_t launch_skim_weights(const wf_params& p, int ntiles, const float* logits,

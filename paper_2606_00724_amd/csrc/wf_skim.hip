@@ -143,7 +143,7 @@ __device__ void skim_epilogue(const SkimTileArgs& a, int u, int tile, long n0,
       s = wave_sum16(s);
       z[i] = s;
     }
-    float* lg = a.logits + (long)u * a.B * a.ld + n0;
+    float* lg = a.logits + (long)u * a.B * a.nJ + n0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int q = qb * 16 + 4 * g + i;
@@ -151,7 +151,7 @@ __device__ void skim_epilogue(const SkimTileArgs& a, int u, int tile, long n0,
 #pragma unroll
         for (int cb = 0; cb < kMaxCoefTile / 16; ++cb) {
           const int c = cb * 16 + col;
-          if (cb < ncb && c < ncoef) lg[(long)q * a.ld + c] = acc[cb][i];
+          if (cb < ncb && c < ncoef) lg[(long)q * a.nJ + c] = acc[cb][i];
         }
       }
     }
@@ -287,12 +287,12 @@ skim_tile_kernel(SkimTileArgs a, Taps taps, EdgeTaps edge) {
 // One workgroup per unit: merge the tiles' row statistics, form W (eq. 8) and
 // select the top-S regions (eq. 9).
 // W_j (eq. 8) of unit u for the columns 4 j4 .. 4 j4 + 3, j4 in [j4_lo,
-// j4_hi) (nJ = ld a multiple of 4), from the query-major logits and the row
+// j4_hi) (nJ a multiple of 4), from the query-major logits and the row
 // normalisers c_q = M_q log2(e) + log2(Z_q); also into wsh when given.
 template <int NT>
 __device__ void skim_w_columns(const SkimSelectArgs& a, int u, const float* row_c, int j4_lo,
                                int j4_hi, float* wsh) {
-  const float* lg = a.logits + (long)u * a.B * a.ld;
+  const float* lg = a.logits + (long)u * a.B * a.nJ;
   float* W = a.W + (long)u * a.nJ;
   // four adjacent columns per thread, 16 query rows of loads in flight
   constexpr int QB = 16;
@@ -302,7 +302,7 @@ __device__ void skim_w_columns(const SkimSelectArgs& a, int u, const float* row_
       float4 v[QB];
 #pragma unroll
       for (int i = 0; i < QB; ++i)
-        v[i] = q0 + i < a.B ? *reinterpret_cast<const float4*>(lg + (long)(q0 + i) * a.ld + 4 * j4)
+        v[i] = q0 + i < a.B ? *reinterpret_cast<const float4*>(lg + (long)(q0 + i) * a.nJ + 4 * j4)
                             : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
       for (int i = 0; i < QB; ++i) {
@@ -375,13 +375,21 @@ __global__ __launch_bounds__(kBlock) void skim_weights_kernel(SkimSelectArgs a, 
   skim_w_columns<kBlock>(a, u, row_c, part * per, min(n4, (part + 1) * per), nullptr);
 }
 
+typedef float f32x4_dword __attribute__((ext_vector_type(4), aligned(4)));
+// four floats at a 4-byte aligned address, one 16-byte load
+__device__ __forceinline__ float4 load4(const float* p) {
+  const f32x4_dword v = *reinterpret_cast<const f32x4_dword*>(p);
+  return make_float4(v[0], v[1], v[2], v[3]);
+}
+
 // The same W for a narrower candidate set (a thousand or so columns a unit),
 // where a thread per four columns leaves too few threads: thread (g, c) adds
 // the terms of 64 / NQG query rows (and those 64 rows on) of four adjacent
 // columns, the NQG groups' partial sums meet in LDS and are added in order of
 // g.  The first batch of logits is loaded before the slices are merged, so
-// that the two loads overlap.  ld is a multiple of 4: the last group of a row
-// may reach into its padding, whose sums are not stored.  NQG = 16 where a
+// that the two loads overlap.  The last group of a row may reach up to three
+// floats into the next row, and past the last row into the statistics that
+// follow the logits in the workspace; their sums are not stored.  NQG = 16 where a
 // workgroup has at most 16 groups of columns, which would leave three quarters
 // of the lanes of NQG = 4 idle (16 units of 128 rows, 1024 columns: 10.9 us
 // with 4, 7.6 with 16; 28 units of 32 rows, 1000 columns: 11.2 and 6.0).
@@ -397,13 +405,13 @@ __global__ __launch_bounds__(kBlock) void skim_weights_rows_kernel(SkimSelectArg
   const int n4 = (a.nJ + 3) / 4, per = (n4 + parts - 1) / parts;
   const int j4_lo = part * per, j4_hi = min(n4, j4_lo + per);
   const int qg = threadIdx.x / CPW, cl = threadIdx.x % CPW;
-  const float* lg = a.logits + (long)u * a.B * a.ld;
+  const float* lg = a.logits + (long)u * a.B * a.nJ;
   float4 v[QB];
   auto load = [&](int j4, int q0) {
 #pragma unroll
     for (int i = 0; i < QB; ++i)
       v[i] = j4 < j4_hi && q0 + i < a.B
-                 ? *reinterpret_cast<const float4*>(lg + (long)(q0 + i) * a.ld + 4 * j4)
+                 ? load4(lg + (long)(q0 + i) * a.nJ + 4 * j4)
                  : make_float4(0.f, 0.f, 0.f, 0.f);
   };
   load(j4_lo + cl, QB * qg);
@@ -531,8 +539,8 @@ __global__ __launch_bounds__(kSelectBlock) void skim_select_kernel(SkimSelectArg
       }
       __syncthreads();
     }
-    const float* lg = a.logits + (long)u * a.B * a.ld;
-    if ((a.nJ & 3) == 0 && a.ld == a.nJ) {
+    const float* lg = a.logits + (long)u * a.B * a.nJ;
+    if ((a.nJ & 3) == 0) {
       skim_w_columns<NT>(a, u, row_c, 0, a.nJ / 4, w_in_lds ? wsh : nullptr);
     } else {
       constexpr int RB = 16;  // rows in flight per thread
@@ -541,7 +549,7 @@ __global__ __launch_bounds__(kSelectBlock) void skim_select_kernel(SkimSelectArg
         for (int q0 = 0; q0 < a.B; q0 += RB) {
           float v[RB];
 #pragma unroll
-          for (int i = 0; i < RB; ++i) v[i] = q0 + i < a.B ? lg[(long)(q0 + i) * a.ld + j] : 0.f;
+          for (int i = 0; i < RB; ++i) v[i] = q0 + i < a.B ? lg[(long)(q0 + i) * a.nJ + j] : 0.f;
 #pragma unroll
           for (int i = 0; i < RB; ++i)
             if (q0 + i < a.B) w += __builtin_amdgcn_exp2f(fmaf(v[i], kLog2e, -row_c[q0 + i]));
@@ -644,7 +652,7 @@ static hipError_t skim_dispatch(int source, const SkimTileArgs& a, const Taps& t
 }
 
 static hipError_t skim_tiles_common(const wf_params& p, int source, int cpt, int J,
-                                    long nJ, long ld, const int32_t* parent, int npar,
+                                    long nJ, const int32_t* parent, int npar,
                                     const void* Q, const void* K, const float* approx,
                                     float* logits, float* stats, hipStream_t s) {
   SkimTileArgs a;
@@ -664,7 +672,6 @@ static hipError_t skim_tiles_common(const wf_params& p, int source, int cpt, int
   a.B = p.q_len;
   a.J = J;
   a.nJ = (int)nJ;
-  a.ld = (int)ld;
   a.cpt = cpt;
   a.ntiles = (int)((nJ + cpt - 1) / cpt);
   a.boundary = p.boundary;
@@ -692,7 +699,7 @@ hipError_t launch_skim_tiles(const wf_params& p, bool fused, const void* Q,
                              float* stats, hipStream_t s) {
   const SkimPlan pl = plan_skim(p, fused);
   return skim_tiles_common(p, pl.source, pl.cpt, p.levels, (long)p.ctx_len >> p.levels,
-                           skim_ld(p), nullptr, 0, Q, K, approx, logits, stats, s);
+                           nullptr, 0, Q, K, approx, logits, stats, s);
 }
 
 // W of args `a` over at least two workgroups per CU, at most 1024 columns each
@@ -708,7 +715,7 @@ static void launch_weights_rows(const SkimSelectArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(skim_weights_rows_kernel<4>, grid, dim3(kBlock), 0, s, a, parts);
 }
 
-static hipError_t skim_select_common(const wf_params& p, bool two_stage, long nJ, long ld, int ntiles, int S,
+static hipError_t skim_select_common(const wf_params& p, bool two_stage, long nJ, int ntiles, int S,
                                      const int32_t* parent, int npar, int pairs,
                                      const float* logits, const float* stats, float* W,
                                      int32_t* out, hipStream_t s) {
@@ -723,7 +730,6 @@ static hipError_t skim_select_common(const wf_params& p, bool two_stage, long nJ
   a.U = p.batch * p.heads;
   a.B = p.q_len;
   a.nJ = (int)nJ;
-  a.ld = (int)ld;
   a.ntiles = ntiles;
   a.S = S;
   const int in_lds = a.nJ <= kSelectLdsFloats ? 1 : 0;
@@ -741,7 +747,7 @@ static hipError_t skim_select_common(const wf_params& p, bool two_stage, long nJ
   if (two_stage && wide_weights(p)) {
     w_ready = 1;
     launch_weights_rows(a, s);
-  } else if (a.nJ >= 4096 && (a.nJ & 3) == 0 && a.ld == a.nJ) {
+  } else if (a.nJ >= 4096 && (a.nJ & 3) == 0) {
     w_ready = 1;
     const int parts = (a.nJ + 1023) / 1024;
     hipLaunchKernelGGL(skim_weights_kernel, dim3((unsigned)(a.U * parts)), dim3(kBlock), 0, s,
@@ -783,7 +789,6 @@ hipError_t launch_skim_weights(const wf_params& p, int ntiles, const float* logi
   a.U = p.batch * p.heads;
   a.B = p.q_len;
   a.nJ = (int)((long)p.ctx_len >> p.levels);
-  a.ld = (int)skim_ld(p);
   a.ntiles = ntiles;
   if (!logits || !stats || !W || a.nJ == 0) return hipErrorInvalidValue;
   launch_weights_rows(a, s);
@@ -793,8 +798,8 @@ hipError_t launch_skim_weights(const wf_params& p, int ntiles, const float* logi
 hipError_t launch_skim_select(const wf_params& p, int ntiles,
                               const float* logits, const float* stats,
                               float* W, int32_t* seg, hipStream_t s) {
-  return skim_select_common(p, true, (long)p.ctx_len >> p.levels, skim_ld(p), ntiles, p.segments, nullptr, 0,
-                            0, logits, stats, W, seg, s);
+  return skim_select_common(p, true, (long)p.ctx_len >> p.levels, ntiles, p.segments, nullptr,
+                            0, 0, logits, stats, W, seg, s);
 }
 
 RecPlan plan_recursion(const wf_params& p, const int32_t* counts) {
@@ -823,7 +828,7 @@ hipError_t launch_rec_tiles(const wf_params& p, int b, long n, const int32_t* pa
                            : parent == nullptr && keys_stream(p) ? kHaarStream
                                                            : kHaarSum,
                            rec_cpt(p, b), b, n,
-                           n, parent, npar, Q, K, nullptr, logits, stats, s);
+                           parent, npar, Q, K, nullptr, logits, stats, s);
 }
 
 hipError_t launch_rec_select(const wf_params& p, int b, long n, int keep,
@@ -831,14 +836,14 @@ hipError_t launch_rec_select(const wf_params& p, int b, long n, int keep,
                              const float* stats, float* W, int32_t* out, hipStream_t s) {
   const int cpt = rec_cpt(p, b);
   const int ntiles = (int)((n + cpt - 1) / cpt);
-  return skim_select_common(p, false, n, n, ntiles, keep, parent, npar, b == 1 ? 1 : 0, logits,
+  return skim_select_common(p, false, n, ntiles, keep, parent, npar, b == 1 ? 1 : 0, logits,
                             stats, W, out, s);
 }
 hipError_t launch_rec_select_slices(const wf_params& p, int b, long n, int keep,
                                     const int32_t* parent, int npar, int nslices,
                                     const float* logits, const float* stats, float* W,
                                     int32_t* out, hipStream_t s) {
-  return skim_select_common(p, false, n, n, nslices, keep, parent, npar, b == 1 ? 1 : 0, logits,
+  return skim_select_common(p, false, n, nslices, keep, parent, npar, b == 1 ? 1 : 0, logits,
                             stats, W, out, s);
 }
 
