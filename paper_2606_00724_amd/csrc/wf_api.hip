@@ -97,7 +97,7 @@ static wf_status check_params(const wf_params* p) {
   if (p->segments < 1 || p->segments > nJ)
     return fail(WF_ERR_INVALID_ARG, "segments %d outside [1, %d]", p->segments, nJ);
   if (p->budget < 1) return fail(WF_ERR_INVALID_ARG, "budget %d < 1", p->budget);
-  if (p->dtype == WF_BF16 && plan_scan(*p).nbuf < 2)
+  if (p->dtype == WF_BF16 && plan_scan(*p, false, false).nbuf < 2)
     return fail(WF_ERR_UNSUPPORTED, "query block and pool range do not fit the LDS ring");
   if ((long)p->batch * p->heads *
           (((long)p->budget < ((long)p->segments << p->levels)
@@ -138,6 +138,7 @@ static size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 struct Layout {
   size_t logits = 0, sstats = 0, W = 0, seg = 0, cstats = 0,
          wpool = 0, tok = 0, part = 0, pstat = 0, wsum = 0, wpsum = 0, sseg = 0, total = 0;
+  size_t shared = 0;  // bytes that two regions share
 };
 
 static long keff_of(const wf_params& p) {
@@ -150,7 +151,7 @@ static long keff_of(const wf_params& p) {
 // coarse logit instead of the scan's per-workgroup statistics (the scan
 // forms the pool normalisers from them on chip), and its attention keeps the
 // selected tokens on chip.
-static Layout layout_for(const wf_params& p, int op, long attn_rows) {
+static Layout layout_for(const wf_params& p, int op, long attn_rows, bool fine) {
   Layout l;
   const size_t U = (size_t)p.batch * p.heads, B = p.q_len;
   const size_t nJ = (size_t)p.ctx_len >> p.levels;
@@ -173,7 +174,7 @@ static Layout layout_for(const wf_params& p, int op, long attn_rows) {
     l.logits = take(U * nJ * 2 * B * sizeof(float));  // block rows: logits, log-sum-exps
     l.sstats = take(U * fp.R * 2 * B * sizeof(float));
   } else if (skim) {
-    const SkimPlan sp = plan_skim(p, op == WF_OP_FUSED);  // from A_J otherwise
+    const SkimPlan sp = plan_skim(p, op == WF_OP_FUSED, fine);  // from A_J otherwise
     l.logits = take(U * B * nJ * sizeof(float));
     l.sstats = take(U * sp.ntiles * 2 * B * sizeof(float));
   }
@@ -186,13 +187,14 @@ static Layout layout_for(const wf_params& p, int op, long attn_rows) {
   const bool overlay = whole && (p.dtype != WF_BF16 || (op == WF_OP_FUSED && !fast));
   size_t part_bytes = 0, pstat_bytes = 0;
   if (attn) {
-    const AttnPlan ap = plan_attn(p, attn_rows);
+    const AttnPlan ap = plan_attn(p, attn_rows, fine);
     part_bytes = up256(U * ap.splits * B * p.head_dim * sizeof(float));
     pstat_bytes = up256(U * ap.splits * 2 * B * sizeof(float));
   }
   if (overlay) {
     l.part = l.logits;  // the first region
     l.pstat = l.part + part_bytes;
+    l.shared = std::min(off, l.pstat + pstat_bytes);
     off = std::max(off, l.pstat + pstat_bytes);
   }
   if (whole) {
@@ -201,7 +203,7 @@ static Layout layout_for(const wf_params& p, int op, long attn_rows) {
   }
   if (scan) {
     // the token-level path forms the pool normalisers inside the scan
-    const ScanPlan cp = plan_scan(p);
+    const ScanPlan cp = plan_scan(p, false, fine);
     if (!fast) l.cstats = take(U * cp.chunks * 2 * B * sizeof(float));
     l.wpool = take(U * P * sizeof(float));
   }
@@ -221,6 +223,23 @@ static Layout layout_for(const wf_params& p, int op, long attn_rows) {
   }
   l.total = off;
   return l;
+}
+
+// The layout of a call that has `have` bytes.  A whole step: the fine one where
+// it is no larger than the coarse one would be with its regions apart, whatever
+// `have` is.  The staged scan and attention have no region to share: the fine
+// one where it fits `have` (and, in all, a small workspace), else the coarse one.
+constexpr size_t kFineStagedBytes = (size_t)32 << 20;
+static Layout layout_in(const wf_params& p, int op, long attn_rows, size_t have, bool* fine) {
+  const Layout f = layout_for(p, op, attn_rows, true);
+  *fine = true;
+  // bf16 splits are the same either way, and only the fused Haar tiles differ
+  if (p.dtype == WF_BF16 && (p.wavelet != WF_HAAR || op == WF_OP_CACHED || fast_path(p))) return f;
+  if ((op == WF_OP_SCAN || op == WF_OP_ATTN) && f.total <= have && f.total <= kFineStagedBytes)
+    return f;
+  const Layout c = layout_for(p, op, attn_rows, false);
+  *fine = f.total <= c.total + c.shared;
+  return *fine ? f : c;
 }
 
 static wf_status check_workspace(const void* ws, size_t have, size_t need) {
@@ -305,7 +324,8 @@ static wf_status fused_impl(const wf_params* p, const void* Q, const void* K,
     return fail(WF_ERR_INVALID_ARG, "n_events %d < %d", n_events, nk + 1);
   const long keff = keff_of(*p);
   const long nrows = keff + remainder_len(*p) + p->gen_len;
-  const Layout l = layout_for(*p, WF_OP_FUSED, nrows);
+  bool fine;
+  const Layout l = layout_in(*p, WF_OP_FUSED, nrows, ws_bytes, &fine);
   WF_TRY(check_workspace(ws, ws_bytes, l.total));
   hipStream_t s = static_cast<hipStream_t>(stream);
   (void)hipGetLastError();
@@ -340,28 +360,28 @@ static wf_status fused_impl(const wf_params* p, const void* Q, const void* K,
     WF_TRY(step(launch_block_weights(*p, logits, sstats, W, s)));
     WF_TRY(step(launch_scan_select_weights(*p, Q, K, W, logits, seg, wpool, s)));
     WF_TRY(step(launch_attn_select(*p, Q, K, V, wpool, seg, tok_idx, Kg, Vg, nrows, part,
-                                   pstat, s)));
+                                   pstat, fine, s)));
   } else {
-    const SkimPlan sp = plan_skim(*p, true);
-    WF_TRY(step(launch_skim_tiles(*p, true, Q, K, nullptr, logits, sstats, s)));
+    const SkimPlan sp = plan_skim(*p, true, fine);
+    WF_TRY(step(launch_skim_tiles(*p, true, Q, K, nullptr, logits, sstats, fine, s)));
     if (general_wide(*p)) {
       WF_TRY(step(launch_skim_weights(*p, sp.ntiles, logits, sstats, W, s)));
-      WF_TRY(step(launch_scan_select_stats(*p, Q, K, W, seg, cstats, s)));
+      WF_TRY(step(launch_scan_select_stats(*p, Q, K, W, seg, cstats, fine, s)));
     } else {
       WF_TRY(step(launch_skim_select(*p, sp.ntiles, logits, sstats, W, seg, s)));
-      WF_TRY(step(launch_scan_chunks(*p, 0, Q, K, seg, cstats, wpool, s)));
+      WF_TRY(step(launch_scan_chunks(*p, 0, Q, K, seg, cstats, wpool, fine, s)));
     }
-    WF_TRY(step(launch_scan_chunks(*p, 1, Q, K, seg, cstats, wpool, s)));
+    WF_TRY(step(launch_scan_chunks(*p, 1, Q, K, seg, cstats, wpool, fine, s)));
     if (general_attn_selects(*p)) {
       WF_TRY(step(launch_attn_select(*p, Q, K, V, wpool, seg, tok_idx, Kg, Vg, nrows, part,
-                                     pstat, s)));
+                                     pstat, fine, s)));
     } else {
       WF_TRY(step(launch_scan_select(*p, wpool, seg, tok, s)));
       WF_TRY(step(launch_attn(*p, Q, K, V, tok, (int)keff, Kg, Vg, p->gen_len, nrows,
-                              part, pstat, s)));
+                              part, pstat, fine, s)));
     }
   }
-  WF_TRY(step(launch_attn_combine(*p, nrows, part, pstat, O, s)));
+  WF_TRY(step(launch_attn_combine(*p, nrows, part, pstat, O, fine, s)));
   return ok();
 }
 
@@ -403,7 +423,8 @@ static wf_status noalloc_impl(const wf_params* p, const void* Q, const void* K,
                               int32_t* tok_idx, int32_t* seg_idx, void* stream) {
   WF_TRY(check_params(p));
   const long nrows = keff_of(*p) + remainder_len(*p) + p->gen_len;
-  const size_t need = layout_for(*p, WF_OP_FUSED, nrows).total;
+  bool fine;
+  const size_t need = layout_in(*p, WF_OP_FUSED, nrows, kScratchBytes, &fine).total;
   if (need > kScratchBytes)
     return fail(WF_ERR_WORKSPACE,
                 "these parameters need %zu bytes of scratch; the allocation-free entry "
@@ -472,7 +493,8 @@ static wf_status cached_impl(const wf_params* p, const void* Q, const float* app
     return fail(WF_ERR_INVALID_ARG, "n_events %d < %d", n_events, nk + 1);
   const long keff = keff_of(*p);
   const long nrows = cached_rows(*p);
-  const Layout l = layout_for(*p, WF_OP_CACHED, nrows);
+  bool fine;
+  const Layout l = layout_in(*p, WF_OP_CACHED, nrows, ws_bytes, &fine);
   WF_TRY(check_workspace(ws, ws_bytes, l.total));
   hipStream_t s = static_cast<hipStream_t>(stream);
   (void)hipGetLastError();
@@ -499,25 +521,25 @@ static wf_status cached_impl(const wf_params* p, const void* Q, const float* app
     return WF_OK;
   };
   WF_HIP(mark(), "hipEventRecord");
-  const SkimPlan sp = plan_skim(*p, false);
-  WF_TRY(step(launch_skim_tiles(*p, false, Q, nullptr, approx, logits, sstats, s)));
+  const SkimPlan sp = plan_skim(*p, false, fine);
+  WF_TRY(step(launch_skim_tiles(*p, false, Q, nullptr, approx, logits, sstats, fine, s)));
   if (cached_scan_selects(*p)) {
     WF_TRY(step(launch_skim_weights(*p, sp.ntiles, logits, sstats, W, s)));
-    WF_TRY(step(launch_scan_select_stats(*p, Q, K, W, seg, cstats, s)));
+    WF_TRY(step(launch_scan_select_stats(*p, Q, K, W, seg, cstats, fine, s)));
   } else {
     WF_TRY(step(launch_skim_select(*p, sp.ntiles, logits, sstats, W, seg, s)));
-    WF_TRY(step(launch_scan_chunks(*p, 0, Q, K, seg, cstats, wpool, s)));
+    WF_TRY(step(launch_scan_chunks(*p, 0, Q, K, seg, cstats, wpool, fine, s)));
   }
-  WF_TRY(step(launch_scan_chunks(*p, 1, Q, K, seg, cstats, wpool, s)));
+  WF_TRY(step(launch_scan_chunks(*p, 1, Q, K, seg, cstats, wpool, fine, s)));
   if (cached_attn_selects(*p)) {
     WF_TRY(step(launch_attn_select(*p, Q, K, V, wpool, seg, tok_idx, Kg, Vg, nrows, part,
-                                   pstat, s)));
+                                   pstat, fine, s)));
   } else {
     WF_TRY(step(launch_scan_select(*p, wpool, seg, tok, s)));
     WF_TRY(step(launch_attn(*p, Q, K, V, tok, (int)keff, Kg, Vg, p->gen_len, nrows, part,
-                            pstat, s)));
+                            pstat, fine, s)));
   }
-  WF_TRY(step(launch_attn_combine(*p, nrows, part, pstat, O, s)));
+  WF_TRY(step(launch_attn_combine(*p, nrows, part, pstat, O, fine, s)));
   return ok();
 }
 
@@ -570,7 +592,8 @@ static wf_status shared_impl(const wf_params* p, const void* Q, const void* K,
     return fail(WF_ERR_INVALID_ARG, "n_events %d < %d", n_events, nk + 1);
   const long keff = keff_of(*p);
   const long nrows = keff + remainder_len(*p) + p->gen_len;
-  const Layout l = layout_for(*p, WF_OP_SHARED, nrows);
+  bool fine;
+  const Layout l = layout_in(*p, WF_OP_SHARED, nrows, ws_bytes, &fine);
   WF_TRY(check_workspace(ws, ws_bytes, l.total));
   hipStream_t s = static_cast<hipStream_t>(stream);
   (void)hipGetLastError();
@@ -608,29 +631,29 @@ static wf_status shared_impl(const wf_params* p, const void* Q, const void* K,
     WF_TRY(step(launch_scan_select_weights(*p, Q, K, wsum, logits, seg, wpool, s, H)));
     WF_TRY(step(launch_head_sum(wpool, wpsum, P, H, p->batch, s)));
     WF_TRY(step(launch_attn_select(*p, Q, K, V, wpsum, seg, tok_idx, Kg, Vg, nrows, part,
-                                   pstat, s, H)));
+                                   pstat, fine, s, H)));
   } else {
     // one "unit" per sequence for the two selections over the heads' sums
     wf_params pg = *p;
     pg.heads = 1;
     int32_t* tok = tok_idx ? tok_idx : reinterpret_cast<int32_t*>(at(ws, l.tok));
     int32_t* unit_seg = reinterpret_cast<int32_t*>(at(ws, l.seg));  // not used after
-    const SkimPlan sp = plan_skim(*p, true);
-    WF_TRY(step(launch_skim_tiles(*p, true, Q, K, nullptr, logits, sstats, s)));
+    const SkimPlan sp = plan_skim(*p, true, fine);
+    WF_TRY(step(launch_skim_tiles(*p, true, Q, K, nullptr, logits, sstats, fine, s)));
     if (shared_w_only(*p))
       WF_TRY(step(launch_skim_weights(*p, sp.ntiles, logits, sstats, W, s)));
     else  // the per-unit select's regions are not used
       WF_TRY(step(launch_skim_select(*p, sp.ntiles, logits, sstats, W, unit_seg, s)));
     WF_TRY(step(launch_head_sum(W, wsum, nJ, H, p->batch, s)));
     WF_TRY(step(launch_select_w(pg, p->batch, wsum, seg, s)));
-    WF_TRY(step(launch_scan_chunks(*p, 0, Q, K, seg, cstats, wpool, s, 0, H)));
-    WF_TRY(step(launch_scan_chunks(*p, 1, Q, K, seg, cstats, wpool, s, 0, H)));
+    WF_TRY(step(launch_scan_chunks(*p, 0, Q, K, seg, cstats, wpool, fine, s, 0, H)));
+    WF_TRY(step(launch_scan_chunks(*p, 1, Q, K, seg, cstats, wpool, fine, s, 0, H)));
     WF_TRY(step(launch_head_sum(wpool, wpsum, P, H, p->batch, s)));
     WF_TRY(step(launch_scan_select(pg, wpsum, seg, tok, s)));
     WF_TRY(step(launch_attn(*p, Q, K, V, tok, (int)keff, Kg, Vg, p->gen_len, nrows, part,
-                            pstat, s, H)));
+                            pstat, fine, s, H)));
   }
-  WF_TRY(step(launch_attn_combine(*p, nrows, part, pstat, O, s)));
+  WF_TRY(step(launch_attn_combine(*p, nrows, part, pstat, O, fine, s)));
   return ok();
 }
 
@@ -658,10 +681,10 @@ static wf_status check_recursion(const wf_params* p, const float* prop, int32_t*
 
 struct RecLayout {
   size_t logits = 0, stats = 0, W = 0, sel[2] = {0, 0}, tok = 0, part = 0, pstat = 0,
-         total = 0;
+         total = 0, shared = 0;
 };
 
-static RecLayout rec_layout(const wf_params& p, const int32_t* counts) {
+static RecLayout rec_layout(const wf_params& p, const int32_t* counts, bool fine) {
   RecLayout l;
   const RecPlan rp = plan_recursion(p, counts);
   const size_t U = (size_t)p.batch * p.heads, B = p.q_len;
@@ -674,15 +697,37 @@ static RecLayout rec_layout(const wf_params& p, const int32_t* counts) {
   };
   l.logits = take(U * B * rp.max_n * sizeof(float));
   l.stats = take(U * rp.max_tiles * 2 * B * sizeof(float));
+  const AttnPlan ap = plan_attn(p, nrows, fine);
+  const size_t part_bytes = up256(U * ap.splits * B * p.head_dim * sizeof(float));
+  const size_t pstat_bytes = up256(U * ap.splits * 2 * B * sizeof(float));
+  // fp32: the partials in the place of the last scale's logits and statistics
+  const bool overlay = p.dtype != WF_BF16;
+  if (overlay) {
+    l.part = l.logits;
+    l.pstat = l.part + part_bytes;
+    l.shared = std::min(off, l.pstat + pstat_bytes);
+    off = std::max(off, l.pstat + pstat_bytes);
+  }
   l.W = take(U * rp.max_n * sizeof(float));
   l.sel[0] = take(U * rp.max_keep * sizeof(int32_t));
   l.sel[1] = take(U * rp.max_keep * sizeof(int32_t));
   l.tok = take(U * 2 * counts[0] * sizeof(int32_t));
-  const AttnPlan ap = plan_attn(p, nrows);
-  l.part = take(U * ap.splits * B * p.head_dim * sizeof(float));
-  l.pstat = take(U * ap.splits * 2 * B * sizeof(float));
+  if (!overlay) {
+    l.part = take(part_bytes);
+    l.pstat = take(pstat_bytes);
+  }
   l.total = off;
   return l;
+}
+
+// as layout_in of a whole step
+static RecLayout rec_layout_of(const wf_params& p, const int32_t* counts, bool* fine) {
+  const RecLayout f = rec_layout(p, counts, true);
+  *fine = true;
+  if (p.dtype == WF_BF16) return f;
+  const RecLayout c = rec_layout(p, counts, false);
+  *fine = f.total <= c.total + c.shared;
+  return *fine ? f : c;
 }
 
 static const char* const kRecTileNames[WF_MAX_LEVELS] = {
@@ -723,7 +768,8 @@ static wf_status recursive_impl(const wf_params* p, const float* prop, const voi
   const int nk = rec_kernels(*p);
   if (events && n_events < nk + 1)
     return fail(WF_ERR_INVALID_ARG, "n_events %d < %d", n_events, nk + 1);
-  const RecLayout l = rec_layout(*p, counts);
+  bool fine;
+  const RecLayout l = rec_layout_of(*p, counts, &fine);
   WF_TRY(check_workspace(ws, ws_bytes, l.total));
   hipStream_t s = static_cast<hipStream_t>(stream);
   (void)hipGetLastError();
@@ -777,8 +823,8 @@ static wf_status recursive_impl(const wf_params* p, const float* prop, const voi
   const int nsel = 2 * counts[0];
   const long nrows = (long)nsel + remainder_len(*p) + p->gen_len;
   WF_TRY(step(launch_attn(*p, Q, K, V, tok, nsel, Kg, Vg, p->gen_len, nrows, part, pstat,
-                          s)));
-  WF_TRY(step(launch_attn_combine(*p, nrows, part, pstat, O, s)));
+                          fine, s)));
+  WF_TRY(step(launch_attn_combine(*p, nrows, part, pstat, O, fine, s)));
   return ok();
 }
 
@@ -791,7 +837,9 @@ extern "C" {
 size_t wf_workspace_bytes(const wf_params* p, int32_t op) {
   if (check_params(p) != WF_OK) return 0;
   if (op < WF_OP_SKIM || op > WF_OP_SHARED) return 0;
-  return layout_for(*p, op, keff_of(*p) + remainder_len(*p) + p->gen_len).total;
+  const long rows = keff_of(*p) + remainder_len(*p) + p->gen_len;
+  bool fine;
+  return layout_in(*p, op, rows, SIZE_MAX, &fine).total;
 }
 
 int32_t wf_effective_budget(const wf_params* p) {
@@ -819,14 +867,15 @@ wf_status wf_skim_score(const wf_params* p, const void* Q, const float* approx,
   WF_TRY(check_ptr(approx, "approx", false));
   WF_TRY(check_ptr(seg_score, "seg_score", false));
   WF_TRY(check_ptr(seg_idx, "seg_idx", false));
-  const Layout l = layout_for(*p, WF_OP_SKIM, 0);
+  bool fine;
+  const Layout l = layout_in(*p, WF_OP_SKIM, 0, workspace_bytes, &fine);
   WF_TRY(check_workspace(workspace, workspace_bytes, l.total));
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const SkimPlan sp = plan_skim(*p, false);
+  const SkimPlan sp = plan_skim(*p, false, fine);
   float* logits = reinterpret_cast<float*>(at(workspace, l.logits));
   float* sstats = reinterpret_cast<float*>(at(workspace, l.sstats));
   (void)hipGetLastError();
-  WF_HIP(launch_skim_tiles(*p, false, Q, nullptr, approx, logits, sstats, s),
+  WF_HIP(launch_skim_tiles(*p, false, Q, nullptr, approx, logits, sstats, fine, s),
          "skim_tile");
   WF_HIP(launch_skim_select(*p, sp.ntiles, logits, sstats, seg_score, seg_idx, s),
          "skim_select");
@@ -843,14 +892,15 @@ wf_status wf_scan_select(const wf_params* p, const void* Q, const void* K,
   WF_TRY(check_ptr(seg_idx, "seg_idx", false));
   WF_TRY(check_ptr(tok_score, "tok_score", true));
   WF_TRY(check_ptr(tok_idx, "tok_idx", false));
-  const Layout l = layout_for(*p, WF_OP_SCAN, 0);
+  bool fine;
+  const Layout l = layout_in(*p, WF_OP_SCAN, 0, workspace_bytes, &fine);
   WF_TRY(check_workspace(workspace, workspace_bytes, l.total));
   hipStream_t s = static_cast<hipStream_t>(stream);
   float* cstats = reinterpret_cast<float*>(at(workspace, l.cstats));
   float* wpool = tok_score ? tok_score : reinterpret_cast<float*>(at(workspace, l.wpool));
   (void)hipGetLastError();
-  WF_HIP(launch_scan_chunks(*p, 0, Q, K, seg_idx, cstats, wpool, s), "scan_stats");
-  WF_HIP(launch_scan_chunks(*p, 1, Q, K, seg_idx, cstats, wpool, s), "scan_weights");
+  WF_HIP(launch_scan_chunks(*p, 0, Q, K, seg_idx, cstats, wpool, fine, s), "scan_stats");
+  WF_HIP(launch_scan_chunks(*p, 1, Q, K, seg_idx, cstats, wpool, fine, s), "scan_weights");
   WF_HIP(launch_scan_select(*p, wpool, seg_idx, tok_idx, s), "scan_select");
   return ok();
 }
@@ -885,16 +935,17 @@ wf_status wf_sparse_attn(const wf_params* p, const void* Q, const void* Ks,
   WF_TRY(check_ptr(Vs, "Vs", false));
   WF_TRY(check_ptr(O, "O", false));
   if (n_kv < 1) return fail(WF_ERR_INVALID_ARG, "n_kv %d < 1", n_kv);
-  const Layout l = layout_for(*p, WF_OP_ATTN, n_kv);
+  bool fine;
+  const Layout l = layout_in(*p, WF_OP_ATTN, n_kv, workspace_bytes, &fine);
   WF_TRY(check_workspace(workspace, workspace_bytes, l.total));
   hipStream_t s = static_cast<hipStream_t>(stream);
   float* part = reinterpret_cast<float*>(at(workspace, l.part));
   float* pstat = reinterpret_cast<float*>(at(workspace, l.pstat));
   (void)hipGetLastError();
   WF_HIP(launch_attn(*p, Q, Ks, Vs, nullptr, n_kv, nullptr, nullptr, 0, n_kv,
-                     part, pstat, s),
+                     part, pstat, fine, s),
          "sparse_attn");
-  WF_HIP(launch_attn_combine(*p, n_kv, part, pstat, O, s), "attn_combine");
+  WF_HIP(launch_attn_combine(*p, n_kv, part, pstat, O, fine, s), "attn_combine");
   return ok();
 }
 
@@ -1010,7 +1061,8 @@ wf_status wf_recursion_counts(const wf_params* p, const float* proportions,
 size_t wf_recursive_workspace_bytes(const wf_params* p, const float* proportions) {
   int32_t c[WF_MAX_LEVELS];
   if (check_recursion(p, proportions, c) != WF_OK) return 0;
-  return rec_layout(*p, c).total;
+  bool fine;
+  return rec_layout_of(*p, c, &fine).total;
 }
 
 wf_status wf_filter_attend_recursive(const wf_params* p, const float* proportions,

@@ -35,10 +35,10 @@ template <typename T, int D>
 struct RingRowPtr {
   const T* base;
   const T* tail;
-  const int32_t* toks;  // LDS: token ids of the split's selected rows, or null
+  const int32_t* toks;  // LDS: token ids of the selected rows from split_r0 on, or null
   long unit_rows;       // rows per unit in `base`
   long r0, rlast;       // absolute first row of the chunk, last valid row
-  long split_r0;        // first row of the split (toks[0])
+  long split_r0;        // the row of toks[0]
   long Lf;              // rows Lf .. Lf + R - 1 of `base` follow the token list
   int u, nsel, G, R;
   __device__ __forceinline__ const T* operator()(int r) const {
@@ -122,11 +122,14 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
         block_select_topk<kAttnRingBlock>(Wg, a.P, a.nsel, emit, sh);
       }
     }
-  } else if (a.tok) {
-    const long hi = min(re0, (long)a.nsel);
-    for (long i = rb0 + threadIdx.x; i < hi; i += kAttnRingBlock)
-      toks[i - rb0] = a.tok[(long)(u / a.share) * a.nsel + i];
   }
+  // ids of rows r0 .. r0 + tcap - 1 of the split (!SEL)
+  auto stage_toks = [&](long r0) {
+    const long hi = min(min(re0, r0 + a.tcap), (long)a.nsel);
+    for (long i = r0 + threadIdx.x; i < hi; i += kAttnRingBlock)
+      toks[i - r0] = a.tok[(long)(u / a.share) * a.nsel + i];
+  };
+  if (!SEL && a.tok) stage_toks(rb0);
   __syncthreads();
 
   RingRowPtr<T, D> kp, vp;
@@ -166,6 +169,7 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
   const T* kunit = kp.base + (long)u * kp.unit_rows * D;
   const T* vunit = vp.base + (long)u * vp.unit_rows * D;
   const int split_last = (int)(re0 - 1 - rb0);
+  int b0 = 0;  // first chunk of the rows whose ids are in LDS
   auto issue_kv = [&](int c, uint32_t slot) {
     const long r0 = rb0 + (long)c * CR;
     if (indexed && min(r0 + CR, re0) <= (long)a.nsel) {
@@ -178,7 +182,7 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
         const int r = (wave * IPW + i) * RPI + lane / G;
         const int k = (lane % G) ^ granule_swz<G>(r);
         // token ids are clamped into the unit: a bad id cannot leave K / V
-        const int t = min(max(toks[min((int)(r0 - rb0) + r, split_last)], 0), a.L - 1);
+        const int t = min(max(toks[min((int)(r0 - rb0) + r, split_last) - b0 * CR], 0), a.L - 1);
         off[i] = (long)t * D + EPV * k;
       }
 #pragma unroll
@@ -233,16 +237,27 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
     // compiler's own wait for it sits here and not inside the loop below
 #pragma unroll
     for (int s = 0; s < KS; ++s) asm volatile("" ::"v"(qreg[s]));
+    // fp32 splits may hold more rows than ids fit the LDS: a batch of tcap rows
+    // at a time (kBatches; every other split is one batch)
+    constexpr bool kBatches = !BF && !SEL;
+    b0 = 0;
+    do {
+    const int b1 = kBatches && indexed ? min(nch, b0 + a.tcap / CR) : nch;
+    if (kBatches && indexed && nch > a.tcap / CR) {
+      kp.split_r0 = vp.split_r0 = rb0 + (long)b0 * CR;
+      stage_toks(kp.split_r0);  // (no chunk is in flight, every wave is past its issues)
+      __syncthreads();
+    }
     // ring of nbuf slots, nbuf - 1 chunks in flight ahead of the one consumed
-    for (int k = 0; k < nch && k < nbuf - 1; ++k)
-      issue_kv(k, ring_lds + (uint32_t)(k * 2 * CHB));
-    for (int ch = 0; ch < nch; ++ch) {
+    for (int k = b0; k < b1 && k - b0 < nbuf - 1; ++k)
+      issue_kv(k, ring_lds + (uint32_t)((k - b0) * 2 * CHB));
+    for (int ch = b0; ch < b1; ++ch) {
       const int nr = (int)min((long)CR, re0 - (rb0 + (long)ch * CR));
-      wait_vmcnt_chunks<2 * IPW>(min(nch - 1 - ch, nbuf - 2));
+      wait_vmcnt_chunks<2 * IPW>(min(b1 - 1 - ch, nbuf - 2));
       lds_barrier();  // chunk ch visible; everyone is past chunk ch - 1
-      if (ch + nbuf - 1 < nch)
-        issue_kv(ch + nbuf - 1, ring_lds + (uint32_t)(((ch + nbuf - 1) % nbuf) * 2 * CHB));
-      const unsigned char* Kb = ring + (ch % nbuf) * 2 * CHB;
+      if (ch + nbuf - 1 < b1)
+        issue_kv(ch + nbuf - 1, ring_lds + (uint32_t)(((ch + nbuf - 1 - b0) % nbuf) * 2 * CHB));
+      const unsigned char* Kb = ring + ((ch - b0) % nbuf) * 2 * CHB;
       const unsigned char* Vb = Kb + CHB;
       if (active) {
         const int rb = part * R;
@@ -382,6 +397,8 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
       }
     }
     lds_barrier();  // the ring is idle before it is refilled or reused
+    b0 = b1;
+    } while (kBatches && b0 < nch);
 
     if (tsplit == 1) {
       if (active) {
@@ -585,20 +602,36 @@ __global__ __launch_bounds__(kBlock) void gather_kernel(GatherArgs a) {
 
 // ------------------------------------------------------------ host side
 
-AttnPlan plan_attn(const wf_params& p, long nrows) {
+// Token ids of a split in LDS at once (bf16 splits hold no more rows).
+constexpr long kTokCap = 4096;
+
+// Most fp32 splits of a unit: those of whole 128-row chunks, about 512 in all
+// (the coarse partials), at most twice as many where fine.  (With a split every
+// 4096 rows, as the ids alone would have it, 700 units of a few rows and a
+// tail of 5000 took 1.9 times the workspace, and 500 units of 100K rows 25.)
+static long most_fp32_splits(long U, long nrows, bool fine) {
+  const long chunks = std::max(1L, (nrows + 127) / 128);
+  const long splits = std::min(chunks, std::max(1L, (512 + U - 1) / U));
+  const long cps = (chunks + splits - 1) / splits;
+  return (chunks + cps - 1) / cps * (fine ? 2 : 1);
+}
+
+AttnPlan plan_attn(const wf_params& p, long nrows, bool fine) {
   AttnPlan a{};
   const long U = (long)p.batch * p.heads;
   const int D = p.head_dim;
   const int es = p.dtype == WF_BF16 ? 2 : 4;
   // one workgroup per CU streaming its rows through the LDS ring
   const long chunks = std::max(1L, (nrows + kRingRows - 1) / kRingRows);
-  // (at most 4096 rows)
-  const long splits = ranges_per_unit(U, chunks, device_cu_count(), 4096L / kRingRows);
+  // (bf16: at most 4096 rows)
+  long splits = ranges_per_unit(U, chunks, device_cu_count(), kTokCap / kRingRows);
+  if (p.dtype != WF_BF16) splits = std::min(splits, most_fp32_splits(U, nrows, fine));
   const long cps = (chunks + splits - 1) / splits;
   a.rps = (int)(cps * kRingRows);
   a.splits = (int)((nrows + a.rps - 1) / a.rps);
+  a.tcap = (int)std::min((long)a.rps, kTokCap);
   const size_t stage = (size_t)2 * kRingRows * es * D;     // K + V chunk
-  const size_t toks = (size_t)a.rps * sizeof(int32_t);
+  const size_t toks = (size_t)a.tcap * sizeof(int32_t);
   const size_t budget = 160 * 1024 - 1024;
   // three slots (two chunks in flight) measured slightly faster than four;
   // fp32 rows of 128 channels leave room for two
@@ -626,9 +659,9 @@ static hipError_t attn_launch(const AttnArgs& a, size_t lds, hipStream_t s) {
 hipError_t launch_attn(const wf_params& p, const void* Q, const void* K,
                        const void* V, const int32_t* tok, int nsel,
                        const void* Kg, const void* Vg, int G, long nrows,
-                       float* part, float* pstat, hipStream_t s, int share) {
+                       float* part, float* pstat, bool fine, hipStream_t s, int share) {
   if (share < 1 || (p.batch * p.heads) % share != 0) return hipErrorInvalidValue;
-  const AttnPlan pl = plan_attn(p, nrows);
+  const AttnPlan pl = plan_attn(p, nrows, fine);
   AttnArgs a;
   a.share = share;
   a.Q = Q;
@@ -651,6 +684,7 @@ hipError_t launch_attn(const wf_params& p, const void* Q, const void* K,
   a.nrows = (int)nrows;
   a.NS = pl.splits;
   a.rps = pl.rps;
+  a.tcap = pl.tcap;
   a.nbuf = pl.nbuf;
   a.scale = effective_scale(p);
   const bool d128 = p.head_dim == 128;
@@ -663,8 +697,9 @@ hipError_t launch_attn(const wf_params& p, const void* Q, const void* K,
 
 bool attn_can_select(const wf_params& p, long nrows) {
   if (p.segments > kSelectLdsSegs || (p.dtype != WF_BF16 && !wide_weights(p))) return false;
-  const AttnPlan pl = plan_attn(p, nrows);
-  if (pl.nbuf < 2) return false;
+  // (the coarse plan's splits are the longest, its ring is no deeper)
+  const AttnPlan pl = plan_attn(p, nrows, false);
+  if (pl.nbuf < 2 || pl.rps > pl.tcap) return false;
   const size_t ring = (size_t)pl.nbuf * 2 * kRingRows * (p.dtype == WF_BF16 ? 2 : 4) * p.head_dim;
   return sizeof(SelectShared<kAttnRingBlock>) + (size_t)p.segments * sizeof(int32_t) <= ring;
 }
@@ -672,10 +707,10 @@ bool attn_can_select(const wf_params& p, long nrows) {
 hipError_t launch_attn_select(const wf_params& p, const void* Q, const void* K, const void* V,
                               const float* wpool, const int32_t* seg, int32_t* tok_out,
                               const void* Kg, const void* Vg, long nrows, float* part,
-                              float* pstat, hipStream_t s, int share) {
+                              float* pstat, bool fine, hipStream_t s, int share) {
   if (!attn_can_select(p, nrows) || share < 1 || (p.batch * p.heads) % share != 0)
     return hipErrorInvalidValue;
-  const AttnPlan pl = plan_attn(p, nrows);
+  const AttnPlan pl = plan_attn(p, nrows, fine);
   AttnArgs a{};
   a.Q = Q;
   a.K = K;
@@ -702,6 +737,7 @@ hipError_t launch_attn_select(const wf_params& p, const void* Q, const void* K, 
   a.nrows = (int)nrows;
   a.NS = pl.splits;
   a.rps = pl.rps;
+  a.tcap = pl.tcap;
   a.nbuf = pl.nbuf;
   a.scale = effective_scale(p);
   // the unit's scan weights in the ring beside the histograms and region
@@ -728,14 +764,14 @@ hipError_t launch_attn_select(const wf_params& p, const void* Q, const void* K, 
 
 hipError_t launch_attn_combine(const wf_params& p, long nrows,
                                const float* part, const float* pstat, void* O,
-                               hipStream_t s) {
+                               bool fine, hipStream_t s) {
   AttnArgs a{};
   a.part = const_cast<float*>(part);
   a.pstat = const_cast<float*>(pstat);
   a.O = O;
   a.U = p.batch * p.heads;
   a.B = p.q_len;
-  a.NS = plan_attn(p, nrows).splits;
+  a.NS = plan_attn(p, nrows, fine).splits;
   const int rpb = kCombineBlock / (p.head_dim / 8);
   const dim3 grid((unsigned)(a.U * ((a.B + rpb - 1) / rpb)));
   if (p.dtype == WF_BF16)

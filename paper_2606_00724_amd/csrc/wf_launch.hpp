@@ -41,7 +41,8 @@ struct ScanPlan {
 struct AttnPlan {
   int splits;        // workgroups (row splits) per unit
   int rps;           // cache rows per split
-  int nbuf;          // LDS ring depth (bf16)
+  int tcap;          // token ids of a split in LDS at once
+  int nbuf;          // LDS ring depth
   size_t lds_bytes;
 };
 
@@ -117,12 +118,18 @@ inline bool keys_stream(const wf_params& p) {
          (size_t)256 << 20;
 }
 
+// fine: the splits that are fastest.  Without it the Haar tiles, fp32 scan
+// ranges and fp32 attention splits are so coarse that their statistics and
+// partials need no more workspace than whole 64-coefficient tiles and splits
+// of whole 128-row chunks do: programs keep workspaces of that size, and
+// the allocation-free call's scratch has to hold every call it held.  The
+// caller of a plan and the launches that follow it pass the same value.
 DwtPlan plan_dwt(const wf_params& p);
-SkimPlan plan_skim(const wf_params& p, bool fused);
+SkimPlan plan_skim(const wf_params& p, bool fused, bool fine);
 // select: the scan workgroups take the top-S regions themselves (all S
 // region ids in LDS)
-ScanPlan plan_scan(const wf_params& p, bool select = false);
-AttnPlan plan_attn(const wf_params& p, long nrows);
+ScanPlan plan_scan(const wf_params& p, bool select, bool fine);
+AttnPlan plan_attn(const wf_params& p, long nrows, bool fine);
 
 // The fused path streams the keys once with token-level scores when the keys
 // are bf16, the wavelet is Haar with 3..5 levels and the query block has at
@@ -145,7 +152,7 @@ hipError_t launch_dwt(const wf_params& p, const void* K, float* approx,
                       float* details, hipStream_t s);
 hipError_t launch_skim_tiles(const wf_params& p, bool fused, const void* Q,
                              const void* K, const float* approx, float* logits,
-                             float* stats, hipStream_t s);
+                             float* stats, bool fine, hipStream_t s);
 // One scale b of the multi-scale recursion (Haar).  Tiles: the coarse
 // logits of its n candidates (all 2^b-blocks when parent is null, else the
 // two halves of each block in parent [U][npar]).  Select: the eq. 8 weights
@@ -186,7 +193,7 @@ hipError_t launch_skim_weights(const wf_params& p, int ntiles, const float* logi
 // share: units per selection (seg indexed by u / share).
 hipError_t launch_scan_chunks(const wf_params& p, int weights, const void* Q,
                               const void* K, const int32_t* seg, float* stats,
-                              float* wpool, hipStream_t s, int stat_slices = 0,
+                              float* wpool, bool fine, hipStream_t s, int stat_slices = 0,
                               int share = 1);
 // Token-level path: the weights pass that first takes the unit's top-S
 // regions of W itself (seg_out [U][S] receives them) and forms the pool
@@ -204,7 +211,7 @@ bool scan_can_select(const wf_params& p);
 // writes one (max, sum) slice per workgroup into stats.
 hipError_t launch_scan_select_stats(const wf_params& p, const void* Q, const void* K,
                                     const float* W, int32_t* seg_out, float* stats,
-                                    hipStream_t s);
+                                    bool fine, hipStream_t s);
 hipError_t launch_scan_select(const wf_params& p, const float* wpool,
                               const int32_t* seg, int32_t* tok,
                               hipStream_t s);
@@ -215,7 +222,7 @@ hipError_t launch_gather(const wf_params& p, const void* K, const void* V,
 hipError_t launch_attn(const wf_params& p, const void* Q, const void* K,
                        const void* V, const int32_t* tok, int nsel,
                        const void* Kg, const void* Vg, int G, long nrows,
-                       float* part, float* pstat, hipStream_t s, int share = 1);
+                       float* part, float* pstat, bool fine, hipStream_t s, int share = 1);
 // The top-S regions (eq. 9) of given weights W [groups][L >> J], one
 // workgroup per group, into seg [groups][S].
 hipError_t launch_select_w(const wf_params& p, long groups, const float* W, int32_t* seg,
@@ -228,7 +235,7 @@ bool attn_can_select(const wf_params& p, long nrows);
 hipError_t launch_attn_select(const wf_params& p, const void* Q, const void* K, const void* V,
                               const float* wpool, const int32_t* seg, int32_t* tok_out,
                               const void* Kg, const void* Vg, long nrows, float* part,
-                              float* pstat, hipStream_t s, int share = 1);
+                              float* pstat, bool fine, hipStream_t s, int share = 1);
 // out [groups][n] = sum over h < H of in [groups H + h][n], in order of h
 // (the selection weights of a sequence's heads added up).
 hipError_t launch_head_sum(const float* in, float* out, long n, int H, int groups,
@@ -243,6 +250,6 @@ hipError_t load_skim_kernels();
 hipError_t load_dwt_kernels();
 hipError_t launch_attn_combine(const wf_params& p, long nrows,
                                const float* part, const float* pstat, void* O,
-                               hipStream_t s);
+                               bool fine, hipStream_t s);
 
 }  // namespace wf

@@ -521,7 +521,15 @@ __global__ __launch_bounds__(kScanSelectBlock) void scan_select_kernel(ScanSelec
 // LDS a workgroup may use (gfx950: 160 KiB per CU), with a little margin.
 constexpr size_t kLdsBudget = 160 * 1024 - 1024;
 
-ScanPlan plan_scan(const wf_params& p, bool select) {
+// Most fp32 ranges of a unit: those of 1 to 8 chunks of 128 positions, about
+// 1024 in all (the coarse statistics), at most twice as many where fine.
+static long most_fp32_ranges(long U, long P, bool fine) {
+  const long chunks = (P + 127) / 128;
+  const long cpw = std::max(1L, std::min(8L, U * chunks / 1024));
+  return (chunks + cpw - 1) / cpw * (fine ? 2 : 1);
+}
+
+ScanPlan plan_scan(const wf_params& p, bool select, bool fine) {
   ScanPlan s{};
   const long P = (long)p.segments << p.levels;
   const long U = (long)p.batch * p.heads;
@@ -551,7 +559,8 @@ ScanPlan plan_scan(const wf_params& p, bool select) {
   const long most = std::min(chunks, std::max(1L, ((long)device_cu_count() + U - 1) / U));
   const long most_cpw = std::min((chunks + most - 1) / most, 4096L / cr);
   auto fits = [&](long c) { return slots(beside(c * cr, (c * cr >> p.levels) + 2)) >= 2; };
-  const long C = ranges_per_unit(U, chunks, device_cu_count(), 4096L / cr);
+  long C = ranges_per_unit(U, chunks, device_cu_count(), 4096L / cr);
+  if (!bf) C = std::min(C, most_fp32_ranges(U, P, fine));
   long cpw = (chunks + C - 1) / C;
   if (!fits(cpw) || !fits(most_cpw)) cpw = most_cpw;
   s.span = (int)(cpw * cr);
@@ -607,11 +616,11 @@ static int scan_streams(const wf_params& p) {
 // the scan's arguments when its workgroups take the top-S regions from W
 // themselves; false when the shape does not allow it
 static bool scan_select_args(const wf_params& p, const void* Q, const void* K, const float* W,
-                             int32_t* seg_out, int share, ScanArgs& a, ScanPlan& pl) {
+                             int32_t* seg_out, int share, bool fine, ScanArgs& a, ScanPlan& pl) {
   if (p.segments > kSelectLdsSegs || share < 1 ||
       (p.batch * p.heads) % share != 0)
     return false;
-  pl = plan_scan(p, true);
+  pl = plan_scan(p, true, fine);
   if (pl.nbuf < 2) return false;
   a = ScanArgs{};
   a.Q = Q;
@@ -643,7 +652,8 @@ static bool scan_select_args(const wf_params& p, const void* Q, const void* K, c
 bool scan_can_select(const wf_params& p) {
   ScanArgs a;
   ScanPlan pl;
-  return scan_select_args(p, nullptr, nullptr, nullptr, nullptr, 1, a, pl);
+  return scan_select_args(p, nullptr, nullptr, nullptr, nullptr, 1, true, a, pl) &&
+         scan_select_args(p, nullptr, nullptr, nullptr, nullptr, 1, false, a, pl);
 }
 
 hipError_t launch_scan_select_weights(const wf_params& p, const void* Q, const void* K,
@@ -652,7 +662,7 @@ hipError_t launch_scan_select_weights(const wf_params& p, const void* Q, const v
   ScanArgs a;
   ScanPlan pl;
   // (the pool normalisers take a thread per query row, 64 rows at most)
-  if (p.dtype != WF_BF16 || p.q_len > 64 || !scan_select_args(p, Q, K, W, seg_out, share, a, pl))
+  if (p.dtype != WF_BF16 || p.q_len > 64 || !scan_select_args(p, Q, K, W, seg_out, share, true, a, pl))
     return hipErrorInvalidValue;
   a.blocks = blocks;
   a.wpool = wpool;
@@ -665,10 +675,10 @@ hipError_t launch_scan_select_weights(const wf_params& p, const void* Q, const v
 
 hipError_t launch_scan_select_stats(const wf_params& p, const void* Q, const void* K,
                                     const float* W, int32_t* seg_out, float* stats,
-                                    hipStream_t s) {
+                                    bool fine, hipStream_t s) {
   ScanArgs a;
   ScanPlan pl;
-  if (!fp32_rows_fit(p) || !scan_select_args(p, Q, K, W, seg_out, 1, a, pl))
+  if (!fp32_rows_fit(p) || !scan_select_args(p, Q, K, W, seg_out, 1, fine, a, pl))
     return hipErrorInvalidValue;
   a.stats = stats;
   a.Cs = pl.chunks;
@@ -685,10 +695,10 @@ hipError_t launch_scan_select_stats(const wf_params& p, const void* Q, const voi
 
 hipError_t launch_scan_chunks(const wf_params& p, int weights, const void* Q,
                               const void* K, const int32_t* seg, float* stats,
-                              float* wpool, hipStream_t s, int stat_slices, int share) {
+                              float* wpool, bool fine, hipStream_t s, int stat_slices, int share) {
   if (share < 1 || (p.batch * p.heads) % share != 0 || !fp32_rows_fit(p))
     return hipErrorInvalidValue;
-  const ScanPlan pl = plan_scan(p);
+  const ScanPlan pl = plan_scan(p, false, fine);
   ScanArgs a;
   a.share = share;
   a.Q = Q;

@@ -59,3 +59,42 @@ def _call(wf, op, p, nbytes, rows=0, props=None):
 ])
 def test_unpadded_logits(wf, op, args, nbytes):
     assert _call(wf, op, _p(wf, *args), nbytes) == HIP
+
+
+# fp32 splits and ranges finer than the former ones, token ids that cap a
+# split's rows, and finer Haar tiles (bf16): with a smaller workspace the former
+# splits are taken
+PROPS = (0.36, 0.28, 0.16, 0.43, 0.53, 0.28, 0.25, 0.53, 0.97)
+
+
+@pytest.mark.parametrize("op,args,nbytes", [
+    ("attn", (1490, 456007, 64, 169, 6, 7092, 436974, 0, "f32", "db2", 2), 66478080),
+    ("attn", (26, 25873, 64, 8, 9, 2, 172, 33, "f32", "db2", 2), 219648),
+    ("attn", (1503, 1024, 64, 45, 10, 1, 5, 5000, "f32"), 17855744),
+    ("scan", (20, 2185, 128, 256, 1, 33, 1, 0, "f32", "db2", 2), 46336),
+    ("scan", (2, 206, 128, 45, 5, 3, 3, 0, "f32"), 1536),
+    ("fused", (1276, 252963, 128, 256, 10, 240, 243778, 0, "f32", "haar", 2), 3662676480),
+    ("fused", (574, 407, 128, 169, 6, 3, 151, 5000, "f32", "db2", 2), 55908352),
+    ("fused", (4, 512, 128, 16, 9, 1, 283, 0, "f32", "haar", 4), 115968),
+    ("cached", (1856, 119, 64, 64, 6, 1, 63, 5000, "f32", "db2", 2), 34692352),
+    ("shared", (636, 2246, 128, 17, 9, 2, 32, 5000, "f32", "haar", 4), 9411840),
+    ("rec", (2, 592, 128, 65, 9, 1, 139, 5000, "f32", "db2", 2), 2709760),
+    ("fused", (2, 47203, 64, 256, 4, 1, 13, 33, "bf16"), 6397952),
+    ("fused", (4, 4198, 64, 16, 2, 163, 23, 0, "bf16", "haar", 4), 327936),
+    ("shared", (4, 7711, 64, 150, 2, 1, 2, 33, "bf16", "haar", 4), 4977408),
+    ("noalloc", (1940, 128, 128, 16, 7, 1, 77, 5000, "f32", "haar", 4), 18368512),
+    ("noalloc", (1264, 373, 128, 32, 8, 1, 171, 5000, "f32", "db2", 2), 24011264),
+    ("noalloc", (1016, 1138, 64, 100, 7, 1, 70, 5000, "f32", "haar", 8), 32540672),
+])
+def test_former_sizes(wf, op, args, nbytes):
+    p = _p(wf, *args)
+    assert _call(wf, op, p, nbytes, props=PROPS[:p.levels]) == HIP
+    if op == "noalloc":  # its limit, as a caller checks it
+        assert wf.workspace_bytes(p, wf.OP_FUSED) <= wf.NOALLOC_SCRATCH_BYTES
+
+
+def test_too_small_is_refused(wf):
+    for dtype in ("bf16", "f32"):
+        p = _p(wf, 4, 2048, 128, 32, 3, 40, 300, 0, dtype)
+        for op in ("skim", "scan", "attn", "fused", "cached", "shared"):
+            assert _call(wf, op, p, 768) == WORKSPACE
