@@ -93,6 +93,33 @@ inline long ranges_per_unit(long U, long chunks, long slots, long max_cpw) {
   return std::min(chunks, C);
 }
 
+// The same for the fp32 kernels, at most `most` ranges a unit.  A chunk takes an
+// fp32 workgroup the same time however few CUs are busy (64 rows of 64 channels,
+// 64 query rows: 3.7 us in the attention, 3.1 in the two scan passes, with 129
+// workgroups as with 256; one query row 1.5), so a round of workgroups lasts as
+// long as its longest, and more rounds of shorter ranges leave fewer CUs idle
+// (staged attention, 64 query rows of 64 channels: 265 units of 500 rows 73.4 ->
+// 53.4 us, 129 of 1000 68.0 -> 51.0; 128 channels, 129 of 4000: 413.9 -> 269.7).
+// fixed: a workgroup's constant part, in chunks (measured over 1 to 600 units and
+// 1 to 160 query rows: 1 in the attention and the scan of 64 channels, of which
+// two workgroups fit a CU, 2 in the scan of 128).
+inline long fp32_ranges_per_unit(long U, long chunks, long slots, long most, long fixed) {
+  most = std::min(chunks, most);
+  long best = 0, best_cost = 0, last = 0;
+  for (long rounds = 1; rounds <= 4 && last < most; ++rounds) {
+    const long C = std::min(most, std::max(1L, rounds * slots / U));  // as many as they take
+    if (C == last) continue;
+    last = C;
+    const long cpw = (chunks + C - 1) / C, n = U * ((chunks + cpw - 1) / cpw);
+    const long cost = (n + slots - 1) / slots * (cpw + fixed);
+    if (best == 0 || cost < best_cost) {
+      best = C;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
 // Whether a call has the coefficients to fill the chip with a W kernel and
 // selections in the kernels that consume them, whatever its keys, query rows
 // and coefficient count.  16 units of 128 bf16 query rows: with 1024

@@ -304,6 +304,10 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
     for (int s = 0; s < S32; ++s) boff[k][s] = granule_offset<G>((rw * TBW + k) * 16 + col, 4 * s + g);
   // query block j of a wave in group qg is block qg + j QW + wq
   for (int qg = 0; qg < nqb; qg += QPG * QW) {
+    // an fp32 range that fits the ring is in it from the first group on
+    // (160 query rows in three groups, 64 units of 128 positions: the staged
+    // scan 48.3 -> 44.3 us)
+    const bool held = !Shape::BF && qg > 0 && nch <= nbuf;
     // query operands of this group, in registers for the whole range
     u32x4 qreg[QPG][S32];
 #pragma unroll
@@ -347,16 +351,18 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
     // The weights pass reads each pool row for the last time with the
     // streaming (nt) policy: keeping the rows cached measured slower (the
     // attention that follows loads the selected keys with nt as well).
-    for (int k = 0; k < nch && k < nbuf - 1 && !(SEL && qg == 0); ++k) {
+    for (int k = 0; k < nch && k < nbuf - 1 && !(SEL && qg == 0) && !held; ++k) {
       rp.p0 = pb + (long)k * CR;
       issue(rp, ring_lds + (uint32_t)(k * CHB));
     }
     for (int ch = 0; ch < nch; ++ch) {
       const long p0 = pb + (long)ch * CR;
       const int np = (int)min((long)CR, pe - p0);
-      wait_vmcnt_chunks<IPW>(min(nch - 1 - ch, nbuf - 2));
-      lds_barrier();  // chunk ch visible; everyone is past chunk ch - 1
-      if (ch + nbuf - 1 < nch) {
+      if (!held) {
+        wait_vmcnt_chunks<IPW>(min(nch - 1 - ch, nbuf - 2));
+        lds_barrier();  // chunk ch visible; everyone is past chunk ch - 1
+      }
+      if (ch + nbuf - 1 < nch && !held) {
         rp.p0 = pb + (long)(ch + nbuf - 1) * CR;
         issue(rp, ring_lds + (uint32_t)(((ch + nbuf - 1) % nbuf) * CHB));
       }
@@ -559,8 +565,11 @@ ScanPlan plan_scan(const wf_params& p, bool select, bool fine) {
   const long most = std::min(chunks, std::max(1L, ((long)device_cu_count() + U - 1) / U));
   const long most_cpw = std::min((chunks + most - 1) / most, 4096L / cr);
   auto fits = [&](long c) { return slots(beside(c * cr, (c * cr >> p.levels) + 2)) >= 2; };
-  long C = ranges_per_unit(U, chunks, device_cu_count(), 4096L / cr);
-  if (!bf) C = std::min(C, most_fp32_ranges(U, P, fine));
+  const long C = bf ? ranges_per_unit(U, chunks, device_cu_count(), 4096L / cr)
+                    : std::max((chunks * cr + 4095) / 4096,
+                               fp32_ranges_per_unit(U, chunks, device_cu_count(),
+                                                    most_fp32_ranges(U, P, fine),
+                                                    p.head_dim == 64 ? 1 : 2));
   long cpw = (chunks + C - 1) / C;
   if (!fits(cpw) || !fits(most_cpw)) cpw = most_cpw;
   s.span = (int)(cpw * cr);
