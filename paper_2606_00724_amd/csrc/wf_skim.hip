@@ -702,12 +702,21 @@ hipError_t launch_skim_tiles(const wf_params& p, bool fused, const void* Q,
                            nullptr, 0, Q, K, approx, logits, stats, s);
 }
 
-// W of args `a` over at least two workgroups per CU, at most 1024 columns each
+// W of args `a` over as many workgroups as are resident at once, two per CU of
+// NQG = 4, at most 1024 columns each (the staged skim of 96 units of 512 columns,
+// 16 rows: 22.3 us with 576 workgroups, 18.9 with 480)
 static void launch_weights_rows(const SkimSelectArgs& a, hipStream_t s) {
-  const long n4 = (a.nJ + 3) / 4;
-  const long want = std::max((a.nJ + 1023L) / 1024,
-                             (2L * device_cu_count() + a.U - 1) / a.U);
-  const int parts = (int)std::min(n4, want);
+  const long n4 = (a.nJ + 3) / 4, wide = (a.nJ + 1023L) / 1024;
+  if ((a.nJ & 3) == 0 && a.nJ >= 4096 &&
+      a.U * wide >= (a.B < 64 ? 1L : 2L) * device_cu_count()) {
+    // 1024 columns a workgroup fill the chip, and fewer than 64 rows would leave
+    // some of the NQG groups idle (the staged skim of 256 units of 4096 columns,
+    // 16 rows: 106.5 us, with a thread per four columns 96.9)
+    hipLaunchKernelGGL(skim_weights_kernel, dim3((unsigned)(a.U * wide)), dim3(kBlock), 0, s, a,
+                       (int)wide);
+    return;
+  }
+  const int parts = (int)std::min(n4, std::max(wide, 2L * device_cu_count() / a.U));
   const dim3 grid((unsigned)(a.U * parts));
   if ((n4 + parts - 1) / parts <= 16)
     hipLaunchKernelGGL(skim_weights_rows_kernel<16>, grid, dim3(kBlock), 0, s, a, parts);
@@ -743,8 +752,13 @@ static hipError_t skim_select_common(const wf_params& p, bool two_stage, long nJ
   // coefficients to fill the chip with it (28 units of 1914: 24.2 us in one
   // kernel, 11.7 + 7.8 in two; 32 of 512: 14.5 and 7.1 + 6.4), on the
   // recursion's scales from 4096 candidates on (1024 columns a workgroup)
+  // So few rows and columns that one workgroup per unit is done with W before a
+  // second kernel starts stay in one kernel, where the units fit the CUs at once
+  // (the staged skim of 64 units of 256 columns, 8 rows: 15.8 us, in two kernels
+  // 17.3; 8 units of 8 rows: 15.9 and 15.6).
+  const bool short_w = a.nJ <= 512 && (a.B == 1 || a.U >= 8 * a.B) && a.U <= device_cu_count();
   int w_ready = 0;
-  if (two_stage && wide_weights(p)) {
+  if (two_stage && wide_weights(p) && !short_w) {
     w_ready = 1;
     launch_weights_rows(a, s);
   } else if (a.nJ >= 4096 && (a.nJ & 3) == 0) {
