@@ -839,7 +839,12 @@ size_t wf_workspace_bytes(const wf_params* p, int32_t op) {
   if (op < WF_OP_SKIM || op > WF_OP_SHARED) return 0;
   const long rows = keff_of(*p) + remainder_len(*p) + p->gen_len;
   bool fine;
-  return layout_in(*p, op, rows, SIZE_MAX, &fine).total;
+  const size_t total = layout_in(*p, op, rows, SIZE_MAX, &fine).total;
+  if (op != WF_OP_ATTN) return total;
+  // enough for a call with fewer rows too
+  const size_t splits = (size_t)p->batch * p->heads * most_attn_splits(*p, rows) * p->q_len;
+  return std::max(total, up256(splits * p->head_dim * sizeof(float)) +
+                             up256(splits * 2 * sizeof(float)));
 }
 
 int32_t wf_effective_budget(const wf_params* p) {

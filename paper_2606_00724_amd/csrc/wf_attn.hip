@@ -649,6 +649,15 @@ AttnPlan plan_attn(const wf_params& p, long nrows, bool fine) {
   return a;
 }
 
+long most_attn_splits(const wf_params& p, long nrows) {
+  const long U = (long)p.batch * p.heads;
+  if (p.dtype != WF_BF16)
+    return std::min((nrows + 127) / 128, std::max(1L, (512 + U - 1) / U));
+  const long chunks = (nrows + kRingRows - 1) / kRingRows;
+  const long least = (chunks + kTokCap / kRingRows - 1) / (kTokCap / kRingRows);
+  return std::min(chunks, std::max(least, std::max(1L, (device_cu_count() + U - 1) / U)));
+}
+
 template <typename T, int D>
 static hipError_t attn_launch(const AttnArgs& a, size_t lds, hipStream_t s) {
   auto kern = attn_ring_kernel<T, D>;

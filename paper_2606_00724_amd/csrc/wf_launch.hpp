@@ -157,6 +157,9 @@ SkimPlan plan_skim(const wf_params& p, bool fused, bool fine);
 // region ids in LDS)
 ScanPlan plan_scan(const wf_params& p, bool select, bool fine);
 AttnPlan plan_attn(const wf_params& p, long nrows, bool fine);
+// Most splits that the coarse plan of any row count up to nrows takes (fewer rows
+// can take more splits: 9 chunks in 5 splits of two, 8 in 8 of one).
+long most_attn_splits(const wf_params& p, long nrows);
 
 // The fused path streams the keys once with token-level scores when the keys
 // are bf16, the wavelet is Haar with 3..5 levels and the query block has at

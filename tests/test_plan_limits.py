@@ -19,31 +19,32 @@ def test_large_query_blocks(units, J, L, B, S, k, taken):
         assert (wf.workspace_bytes(p, op) > 0) == taken
 
 
-def _splits(wf, units, rows, d, B):
-    """fp32 splits of a unit, from the partials that the staged attention asks for"""
-    p = wf.make_params(batch=1, heads=units, ctx_len=8192, head_dim=d, q_len=B, levels=3,
-                       segments=1024, budget=rows, dtype="f32")
-    need = wf.workspace_bytes(p, wf.OP_ATTN)
+def _ranges(wf, units, rows, B):
+    """fp32 ranges of a unit's pool of `rows` positions (64 channels), from the
+    statistics that the staged scan asks for beside the weights"""
+    p = wf.make_params(batch=1, heads=units, ctx_len=8192, head_dim=64, q_len=B, levels=3,
+                       segments=rows // 8, budget=rows, dtype="f32")
 
     def up(x):
         return (x + 255) & ~255
-    for s in range(1, 1025):
-        if up(units * s * B * d * 4) + up(units * s * 2 * B * 4) == need:
-            return s
+    need = wf.workspace_bytes(p, wf.OP_SCAN) - up(units * rows * 4)
+    for c in range(1, 1025):
+        if up(units * c * 2 * B * 4) == need:
+            return c
     raise AssertionError(need)
 
 
-@pytest.mark.parametrize("units,rows", [(129, 1000), (171, 4000), (265, 500), (265, 1000),
+@pytest.mark.parametrize("units,rows", [(129, 1000), (171, 4000), (265, 512), (265, 1000),
                                         (300, 4000), (129, 4000)])
 def test_fp32_rounds_leave_few_cus_idle(units, rows):
     """A round of workgroups lasts as long as its longest: rounds times a
-    workgroup's chunks (and one for its constant part).  Where one split a unit
+    workgroup's chunks (and one for its constant part).  Where one range a unit
     would leave much of its last round idle, the chosen count costs at least
     15% less."""
     import paper_2606_00724_amd as wf
     chunks = (rows + 63) // 64
 
-    def cost(s):
-        per = -(-chunks // s)
+    def cost(c):
+        per = -(-chunks // c)
         return -(-units * -(-chunks // per) // 256) * (per + 1)
-    assert cost(_splits(wf, units, rows, 64, 64)) <= 0.85 * cost(1)
+    assert cost(_ranges(wf, units, rows, 64)) <= 0.85 * cost(1)

@@ -98,3 +98,14 @@ def test_too_small_is_refused(wf):
         p = _p(wf, 4, 2048, 128, 32, 3, 40, 300, 0, dtype)
         for op in ("skim", "scan", "attn", "fused", "cached", "shared"):
             assert _call(wf, op, p, 768) == WORKSPACE
+
+
+@pytest.mark.parametrize("units,rows,fewer,d,B,dtype", [
+    (9, 5282, 3592, 128, 1, "bf16"), (20, 4032, 3040, 64, 32, "bf16"),
+    (19, 14024, 8948, 128, 32, "f32"), (50, 667, 623, 64, 64, "f32")])
+def test_staged_attention_with_fewer_rows(wf, units, rows, fewer, d, B, dtype):
+    """A workspace sized for k_eff rows is enough for every smaller n_kv."""
+    p = _p(wf, units, 1 << 15, d, B, 3, 1 << 12, rows, 0, dtype)
+    nbytes = wf.workspace_bytes(p, wf.OP_ATTN)
+    for n in {fewer, *range(1, rows, 1 + rows // 500)}:
+        assert _call(wf, "attn", p, nbytes, rows=n) == HIP, n
