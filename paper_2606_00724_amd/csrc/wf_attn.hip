@@ -284,16 +284,18 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
             for (int i = 0; i < 4; ++i) t[i] = sb + 4 * g + i < re ? acc[i] * c2 : -INFINITY;
             const float mb =
                 max_xor32(max_xor16(fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3]))));
-            const float m_new = fmaxf(m_run, mb);  // finite: row sb is in range
+            const float m_new = fmaxf(m_run, mb);
+            // (while every score so far is -inf, their weights are 2^-inf = 0)
+            const float ref = m_new > -INFINITY ? m_new : 0.f;
             float pv[4], ps = 0.f;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-              pv[i] = __builtin_amdgcn_exp2f(t[i] - m_new);  // 2^-inf = 0
+              pv[i] = __builtin_amdgcn_exp2f(t[i] - ref);
               ps += pv[i];
             }
             ps = add_xor32(add_xor16(ps));
             if (__builtin_amdgcn_ballot_w64(m_new != m_run) != 0) {
-              const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+              const float alpha = __builtin_amdgcn_exp2f(m_run - ref);
               l_run = l_run * alpha + ps;
 #pragma unroll
               for (int i = 0; i < 4; ++i) {

@@ -1,0 +1,48 @@
+"""Keys whose score is -inf for every query (an infinite channel): weight 0 in
+the scan and in the attention, wherever they stand in a range, a chunk or a
+block of 16 rows, as the softmax over the other rows gives it."""
+import pytest
+import torch
+
+from parity import O_TOL
+
+pytestmark = pytest.mark.gpu
+
+
+def rows_of(n, spans):
+    bad = torch.zeros(n, dtype=torch.bool)
+    for a, b in spans:
+        bad[a:b] = True
+    return bad.cuda()
+
+
+def inputs(units, rows, n, d, dtype, bad):
+    gen = torch.Generator(device="cuda").manual_seed(rows + n)
+    Q = torch.randn(1, units, rows, d, generator=gen, device="cuda")
+    K = torch.randn(1, units, n, d, generator=gen, device="cuda")
+    V = torch.randn(1, units, n, d, generator=gen, device="cuda")
+    Q[..., 0] = Q[..., 0].abs() + 0.5
+    Q, K, V = (x.to(dtype) for x in (Q, K, V))
+    K[:, :, bad, 0] = float("-inf")
+    return Q, K, V
+
+
+# whole blocks of 16 rows, the first rows, the last, every other row
+SPANS = [[(16, 32)], [(0, 16)], [(0, 1), (63, 130)], [(i, i + 1) for i in range(0, 200, 2)]]
+
+
+@pytest.mark.parametrize("spans", SPANS, ids=["block", "first", "ends", "alternate"])
+@pytest.mark.parametrize("d,B", [(64, 16), (128, 50), (64, 130)])
+def test_fp32_attention(spans, d, B):
+    import paper_2606_00724_amd as wf
+    units, n = 3, 200
+    p = wf.make_params(batch=1, heads=units, ctx_len=4096, head_dim=d, q_len=B, levels=3,
+                       segments=512, budget=n, dtype="f32")
+    bad = rows_of(n, spans)
+    Q, K, V = inputs(units, B, n, d, torch.float32, bad)
+    O = torch.empty_like(Q)
+    wf.wf_sparse_attn(p, Q, K, V, n, O, wf.alloc_workspace(p, wf.OP_ATTN, Q.device))
+    torch.cuda.synchronize()
+    Kd, Vd = K[0][:, ~bad].double(), V[0][:, ~bad].double()
+    ref = torch.softmax(Q[0].double() @ Kd.transpose(1, 2).contiguous() / d ** 0.5, -1) @ Vd
+    assert (O[0] - ref).abs().max().item() <= O_TOL["f32"]
