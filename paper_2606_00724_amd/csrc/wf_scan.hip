@@ -80,6 +80,9 @@ __device__ __forceinline__ void stat_absorb2(float& m, float& z, float m2, float
 // reference before that is raised: sums of 2^16 per term stay far from the
 // ends of the fp32 range.
 constexpr float kRefSlack = 16.f;
+// The reference before any logit: so low that the first finite logit raises it,
+// and finite, so that a logit of -inf adds 2^-inf = 0 rather than a NaN.
+constexpr float kNoRef = -3.4028234663852886e38f;
 
 // The ring kernel's shape per element type.  bf16: chunks of 128 rows, 16 of
 // them a wave, every query block in every wave.  fp32: 64 rows of twice the
@@ -344,7 +347,7 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
     for (int j = 0; j < QPG; ++j)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        sm[j][i] = -INFINITY;
+        sm[j][i] = kNoRef;
         sz[j][i] = 0.f;
       }
     // ring of nbuf slots, nbuf - 1 chunks in flight ahead of the one consumed.
@@ -455,7 +458,7 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
     if constexpr (!WEIGHTS) {
       // merge the 16 lanes of each row (their largest reference, then the sums
       // brought to it), then the waves, through LDS.  Rows no lane has seen
-      // keep (-inf, 0).  (Pairwise merges of the lanes, four rounds of two
+      // keep (kNoRef, 0).  (Pairwise merges of the lanes, four rounds of two
       // exponentials each: 24.4 us instead of 17.2 for 16 units of 128 query
       // rows, 43.9 instead of 40.2 for 128 units of 64.)
 #pragma unroll
@@ -463,8 +466,7 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const float m = wave_max16(sm[j][i]);
-          const float z = wave_sum16(
-              sm[j][i] > -INFINITY ? sz[j][i] * __builtin_amdgcn_exp2f(sm[j][i] - m) : 0.f);
+          const float z = wave_sum16(sz[j][i] * __builtin_amdgcn_exp2f(sm[j][i] - m));
           const int qb = qg + j * QW + wq;
           if (col == 0 && qb < nqb) {
             part[((qb * RW + rw) * 16 + 4 * g + i) * 2] = m;

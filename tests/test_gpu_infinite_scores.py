@@ -4,7 +4,7 @@ block of 16 rows, as the softmax over the other rows gives it."""
 import pytest
 import torch
 
-from parity import O_TOL
+from parity import O_TOL, SEL_REL
 
 pytestmark = pytest.mark.gpu
 
@@ -46,3 +46,26 @@ def test_fp32_attention(spans, d, B):
     Kd, Vd = K[0][:, ~bad].double(), V[0][:, ~bad].double()
     ref = torch.softmax(Q[0].double() @ Kd.transpose(1, 2).contiguous() / d ** 0.5, -1) @ Vd
     assert (O[0] - ref).abs().max().item() <= O_TOL["f32"]
+
+
+@pytest.mark.parametrize("spans", SPANS, ids=["block", "first", "ends", "alternate"])
+@pytest.mark.parametrize("dtype,d,B", [("f32", 64, 16), ("f32", 128, 70), ("bf16", 128, 33),
+                                       ("bf16", 64, 100)])
+def test_scan(spans, dtype, d, B):
+    import paper_2606_00724_amd as wf
+    units, S, J = 600, 50, 3  # one range a unit, several chunks
+    n = S << J
+    p = wf.make_params(batch=1, heads=units, ctx_len=n, head_dim=d, q_len=B, levels=J, segments=S,
+                       budget=n // 2, dtype=dtype)
+    bad = rows_of(n, spans)
+    Q, K, _ = inputs(units, B, n, d, wf.torch_dtype(p), bad)
+    seg = torch.arange(S, dtype=torch.int32, device="cuda").repeat(units, 1).contiguous()
+    W = torch.empty((units, n), device="cuda")
+    tok = torch.empty((units, n // 2), dtype=torch.int32, device="cuda")
+    wf.wf_scan_select(p, Q, K, seg, W, tok, wf.alloc_workspace(p, wf.OP_SCAN, Q.device))
+    torch.cuda.synchronize()
+    pick = [0, 299, 599]
+    s = Q[0][pick].double() @ K[0][pick][:, ~bad].double().transpose(1, 2).contiguous() / d ** 0.5
+    ref = torch.softmax(s, -1).sum(1)
+    assert (W[:, bad] == 0).all()
+    assert ((W[pick][:, ~bad] - ref).abs() / ref).max().item() <= SEL_REL
