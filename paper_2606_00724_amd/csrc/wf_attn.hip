@@ -64,7 +64,10 @@ constexpr int kAttnRingBlock = 512;
 // tokens of the scan weights itself (eq. 9 over the pool; ties to the lower
 // pool position, which is the lower token) and keeps the ascending ids of
 // its split; tok_out (nullable) receives them.
-template <typename T, int D, bool SEL = false>
+// BATCHES (fp32): the split holds more rows than ids fit the LDS and takes them a
+// batch of tcap rows at a time (an instance of its own: the loop's registers cost
+// the smallest calls 0.4 us of 8.2).
+template <typename T, int D, bool SEL = false, bool BATCHES = false>
 __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
   constexpr bool BF = sizeof(T) == 2;
   constexpr int NW = kAttnRingBlock / kWave;
@@ -123,9 +126,9 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
       }
     }
   }
-  // ids of rows r0 .. r0 + tcap - 1 of the split (!SEL)
+  // ids of the split's rows from r0 on (!SEL)
   auto stage_toks = [&](long r0) {
-    const long hi = min(min(re0, r0 + a.tcap), (long)a.nsel);
+    const long hi = min(BATCHES ? min(re0, r0 + a.tcap) : re0, (long)a.nsel);
     for (long i = r0 + threadIdx.x; i < hi; i += kAttnRingBlock)
       toks[i - r0] = a.tok[(long)(u / a.share) * a.nsel + i];
   };
@@ -169,8 +172,8 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
   const T* kunit = kp.base + (long)u * kp.unit_rows * D;
   const T* vunit = vp.base + (long)u * vp.unit_rows * D;
   const int split_last = (int)(re0 - 1 - rb0);
-  int b0 = 0;  // first chunk of the rows whose ids are in LDS
-  auto issue_kv = [&](int c, uint32_t slot) {
+  // (b0: the batch's first chunk)
+  auto issue_kv = [&](int c, uint32_t slot, int b0) {
     const long r0 = rb0 + (long)c * CR;
     if (indexed && min(r0 + CR, re0) <= (long)a.nsel) {
       constexpr int RPI = 64 / G;
@@ -182,7 +185,7 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
         const int r = (wave * IPW + i) * RPI + lane / G;
         const int k = (lane % G) ^ granule_swz<G>(r);
         // token ids are clamped into the unit: a bad id cannot leave K / V
-        const int t = min(max(toks[min((int)(r0 - rb0) + r, split_last) - b0 * CR], 0), a.L - 1);
+        const int t = min(max(toks[min((int)(r0 - rb0) + r, split_last) - (BATCHES ? b0 * CR : 0)], 0), a.L - 1);
         off[i] = (long)t * D + EPV * k;
       }
 #pragma unroll
@@ -237,26 +240,25 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
     // compiler's own wait for it sits here and not inside the loop below
 #pragma unroll
     for (int s = 0; s < KS; ++s) asm volatile("" ::"v"(qreg[s]));
-    // fp32 splits may hold more rows than ids fit the LDS: a batch of tcap rows
-    // at a time (kBatches; every other split is one batch)
-    constexpr bool kBatches = !BF && !SEL;
-    b0 = 0;
+    int next = 0;
     do {
-    const int b1 = kBatches && indexed ? min(nch, b0 + a.tcap / CR) : nch;
-    if (kBatches && indexed && nch > a.tcap / CR) {
+    const int b0 = BATCHES ? next : 0;
+    const int b1 = BATCHES ? min(nch, b0 + a.tcap / CR) : nch;
+    if constexpr (BATCHES) {
       kp.split_r0 = vp.split_r0 = rb0 + (long)b0 * CR;
       stage_toks(kp.split_r0);  // (no chunk is in flight, every wave is past its issues)
       __syncthreads();
     }
     // ring of nbuf slots, nbuf - 1 chunks in flight ahead of the one consumed
     for (int k = b0; k < b1 && k - b0 < nbuf - 1; ++k)
-      issue_kv(k, ring_lds + (uint32_t)((k - b0) * 2 * CHB));
+      issue_kv(k, ring_lds + (uint32_t)((k - b0) * 2 * CHB), b0);
     for (int ch = b0; ch < b1; ++ch) {
       const int nr = (int)min((long)CR, re0 - (rb0 + (long)ch * CR));
       wait_vmcnt_chunks<2 * IPW>(min(b1 - 1 - ch, nbuf - 2));
       lds_barrier();  // chunk ch visible; everyone is past chunk ch - 1
       if (ch + nbuf - 1 < b1)
-        issue_kv(ch + nbuf - 1, ring_lds + (uint32_t)(((ch + nbuf - 1 - b0) % nbuf) * 2 * CHB));
+        issue_kv(ch + nbuf - 1, ring_lds + (uint32_t)(((ch + nbuf - 1 - b0) % nbuf) * 2 * CHB),
+                 b0);
       const unsigned char* Kb = ring + ((ch - b0) % nbuf) * 2 * CHB;
       const unsigned char* Vb = Kb + CHB;
       if (active) {
@@ -399,8 +401,8 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
       }
     }
     lds_barrier();  // the ring is idle before it is refilled or reused
-    b0 = b1;
-    } while (kBatches && b0 < nch);
+    next = b1;
+    } while (BATCHES && next < nch);
 
     if (tsplit == 1) {
       if (active) {
@@ -660,9 +662,9 @@ long most_attn_splits(const wf_params& p, long nrows) {
   return std::min(chunks, std::max(least, std::max(1L, (device_cu_count() + U - 1) / U)));
 }
 
-template <typename T, int D>
+template <typename T, int D, bool BATCHES = false>
 static hipError_t attn_launch(const AttnArgs& a, size_t lds, hipStream_t s) {
-  auto kern = attn_ring_kernel<T, D>;
+  auto kern = attn_ring_kernel<T, D, false, BATCHES>;
   if (lds > 65536) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -672,6 +674,8 @@ static hipError_t attn_launch(const AttnArgs& a, size_t lds, hipStream_t s) {
   hipLaunchKernelGGL(kern, dim3((unsigned)(a.U * a.NS)), dim3(kAttnRingBlock), lds, s, a);
   return hipGetLastError();
 }
+
+static hipError_t launch_attn_batches(bool d128, const AttnArgs& a, size_t lds, hipStream_t s);
 
 hipError_t launch_attn(const wf_params& p, const void* Q, const void* K,
                        const void* V, const int32_t* tok, int nsel,
@@ -708,6 +712,7 @@ hipError_t launch_attn(const wf_params& p, const void* Q, const void* K,
   if (p.dtype == WF_BF16)
     return d128 ? attn_launch<bf16_t, 128>(a, pl.lds_bytes, s)
                 : attn_launch<bf16_t, 64>(a, pl.lds_bytes, s);
+  if (tok && pl.rps > pl.tcap) return launch_attn_batches(d128, a, pl.lds_bytes, s);
   return d128 ? attn_launch<float, 128>(a, pl.lds_bytes, s)
               : attn_launch<float, 64>(a, pl.lds_bytes, s);
 }
@@ -777,6 +782,10 @@ hipError_t launch_attn_select(const wf_params& p, const void* Q, const void* K, 
   }
   hipLaunchKernelGGL(kern, dim3((unsigned)(a.U * a.NS)), dim3(kAttnRingBlock), pl.lds_bytes, s, a);
   return hipGetLastError();
+}
+
+static hipError_t launch_attn_batches(bool d128, const AttnArgs& a, size_t lds, hipStream_t s) {
+  return d128 ? attn_launch<float, 128, true>(a, lds, s) : attn_launch<float, 64, true>(a, lds, s);
 }
 
 hipError_t launch_attn_combine(const wf_params& p, long nrows,

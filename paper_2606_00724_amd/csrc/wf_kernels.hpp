@@ -124,12 +124,12 @@ struct AttnArgs {
   int R;
   int U, L, B, nsel, G, nrows, NS;
   int rps;              // cache rows per split (multiple of the chunk)
-  int tcap;             // token ids in LDS at once (multiple of the chunk)
   int nbuf;             // LDS ring depth
   float scale;
   // units per selection: the selecting attention of unit u reads wpool and
   // seg of selection u / share (tok_out by the group's first unit only)
   int share = 1;
+  int tcap;             // token ids in LDS at once (multiple of the chunk)
 };
 
 constexpr int kFastMaxQBlocks = 4;  // query rows <= 64 on the token-level skim
