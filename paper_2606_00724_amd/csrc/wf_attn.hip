@@ -279,8 +279,10 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
               for (int e = 0; e < 4; ++e)
                 acc = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[e], qv[e], acc, 0, 0, 0);
             }
-            // lane holds the scores of rows sb + 4g + i for query col, in
-            // log2 units; rows past the range are -inf
+            // lane holds the scores of rows sb + 4g + i for query col; t: in log2
+            // units, rows past the range -inf.  Only the reference is taken from
+            // the rounded t: a weight's exponent is the unrounded product less the
+            // reference, so that scores of thousands keep their differences.
             float t[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) t[i] = sb + 4 * g + i < re ? acc[i] * c2 : -INFINITY;
@@ -292,7 +294,7 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
             float pv[4], ps = 0.f;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-              pv[i] = __builtin_amdgcn_exp2f(t[i] - ref);
+              pv[i] = sb + 4 * g + i < re ? __builtin_amdgcn_exp2f(fmaf(acc[i], c2, -ref)) : 0.f;
               ps += pv[i];
             }
             ps = add_xor32(add_xor16(ps));
@@ -416,7 +418,7 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
         }
         const int q = qb * 16 + col;
         if (g == 0 && q < a.B) {
-          ps_base[q] = m_run * kLn2;  // back to natural-log units
+          ps_base[q] = m_run;
           ps_base[a.B + q] = l_run;
         }
       }
@@ -469,7 +471,7 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
                   BF ? o[0] + o[1] : (o[0] + o[1]) + (o[MP - 2] + o[MP - 1]);
             }
             if (col == 0) {
-              ps_base[q] = M * kLn2;  // back to natural-log units
+              ps_base[q] = M;
               ps_base[a.B + q] = lsum;
             }
           }
@@ -479,8 +481,8 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
   }
 }
 
-// Merges the splits of each query row: O = sum_s e^(M_s - M) O_s / sum_s
-// e^(M_s - M) l_s.  A workgroup takes 2048 / D rows of one unit, a thread 8
+// Merges the splits of each query row: O = sum_s 2^(M_s - M) O_s / sum_s
+// 2^(M_s - M) l_s (M_s in log2 units).  A workgroup takes 2048 / D rows of one unit, a thread 8
 // consecutive channels of one row (two 16-byte loads per split, one 16-byte
 // store for bf16).
 constexpr int kCombineBlock = 256;
@@ -532,13 +534,13 @@ __device__ __forceinline__ void merge_splits(const AttnArgs& a, int u, int q, in
 #pragma unroll
     for (int k = 0; k < SB; ++k) mn = fmaxf(mn, ms[k]);
     if (mn == -INFINITY) continue;
-    const float r = M > -INFINITY ? __expf(M - mn) : 0.f;
+    const float r = M > -INFINITY ? __builtin_amdgcn_exp2f(M - mn) : 0.f;
     lsum *= r;
 #pragma unroll
     for (int i = 0; i < 8; ++i) o[i] *= r;
 #pragma unroll
     for (int k = 0; k < SB; ++k) {
-      const float w = ms[k] > -INFINITY ? __expf(ms[k] - mn) : 0.f;
+      const float w = ms[k] > -INFINITY ? __builtin_amdgcn_exp2f(ms[k] - mn) : 0.f;
       lsum += zs[k] * w;
       o[0] += w * x[k][0].x;
       o[1] += w * x[k][0].y;

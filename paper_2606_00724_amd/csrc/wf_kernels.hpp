@@ -118,7 +118,7 @@ struct AttnArgs {
   const void* Kg;       // [U][G][D] tail (indexed mode only)
   const void* Vg;
   float* part;          // [U][NS][B][D] unnormalised partial outputs
-  float* pstat;         // [U][NS][2][B] partial row max, row sum
+  float* pstat;         // [U][NS][2][B] partial row max (log2 units), row sum
   void* O;              // [U][B][D]
   long Lf;              // indexed mode: rows Lf .. Lf + R - 1 of K/V follow tok
   int R;
