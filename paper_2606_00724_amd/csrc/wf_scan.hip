@@ -144,8 +144,12 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
   float* red = reinterpret_cast<float*>(segs + a.seg_cap);
   const int nqb = (a.B + 15) / 16;
   float* part = red;                   // [nqb][RW][16][2]
-  float* lse2 = red + nqb * RW * 32;   // weights: log2 of the pool's sum of exp, per query
-  float* wsum = lse2 + a.B;            // weights: W' of the range [QW][span]
+  // weights: log2 of the pool's sum of exp, per query; fp32: the reference (log2
+  // units), and 1 / sum apart, as one number of the two would round a large
+  // reference to its last place, and every weight with it
+  float* lse2 = red + nqb * RW * 32;
+  float* zinv = lse2 + a.B;                               // fp32
+  float* wsum = lse2 + (Shape::BF ? a.B : 2 * a.B);  // weights: W' of the range [QW][span]
 
   const int item = xcd_swizzle(blockIdx.x, gridDim.x);
   const int u = item / a.C, c = item % a.C;
@@ -293,7 +297,12 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
 #pragma unroll
         for (int k = 0; k < SB; ++k) stat_absorb2(mx, z, mk[k], zk[k]);
       }
-      lse2[q] = mx + __log2f(z);
+      if constexpr (Shape::BF) {
+        lse2[q] = mx + __log2f(z);
+      } else {
+        lse2[q] = mx;
+        zinv[q] = 1.f / z;
+      }
     }
   }
   __syncthreads();  // every regular load above has been consumed
@@ -331,13 +340,14 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
     }
     // weights: the log2-domain normalisers of the lane's query rows (rows
     // past B contribute 2^-inf = 0)
-    float c2[QPG][4];
+    float c2[QPG][4], ci[QPG][4];
 #pragma unroll
     for (int j = 0; j < QPG; ++j)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int q = (qg + j * QW + wq) * 16 + 4 * g + i;
         c2[j][i] = WEIGHTS && q < a.B ? lse2[q] : INFINITY;
+        if constexpr (WEIGHTS && !Shape::BF) ci[j][i] = q < a.B ? zinv[q] : 0.f;
       }
     // statistics: a lane's reference per query row (log2 units, within
     // kRefSlack of the largest logit it has seen) and its sum of
@@ -426,7 +436,8 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
                   const float v = acc[j][i] * s2;
                   sz[j][i] *= __builtin_amdgcn_exp2f(sm[j][i] - v);  // 0 at the first logit
                   sm[j][i] = v;
-                  t[j][i] = 0.f;
+                  // (fp32: v's rounding; an infinite logit counts 1)
+                  t[j][i] = !Shape::BF && v < INFINITY ? fmaf(acc[j][i], s2, -v) : 0.f;
                 }
               }
             }
@@ -442,8 +453,11 @@ __global__ __launch_bounds__(kPoolBlock) void scan_ring_kernel(ScanArgs a) {
           for (int j = 0; j < QPG; ++j) {
             if (qg + j * QW + wq >= nqb) break;
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-              wk += __builtin_amdgcn_exp2f(fmaf(acc[j][i], s2, -c2[j][i]));
+            for (int i = 0; i < 4; ++i) {
+              const float e = __builtin_amdgcn_exp2f(fmaf(acc[j][i], s2, -c2[j][i]));
+              if constexpr (Shape::BF) wk += e;
+              else wk = fmaf(e, ci[j][i], wk);
+            }
           }
         }
         if constexpr (WEIGHTS) {
@@ -553,7 +567,8 @@ ScanPlan plan_scan(const wf_params& p, bool select, bool fine) {
   // region ids: queries, ids, wave partials, the per-query normalisers, W'
   auto beside = [&](long span, long seg_cap) {
     return queries + (size_t)seg_cap * 4 +
-           ((size_t)nqb * (kPoolWaves / qw) * 16 * 2 + (size_t)p.q_len + (size_t)qw * span) *
+           ((size_t)nqb * (kPoolWaves / qw) * 16 * 2 + (size_t)(bf ? 1 : 2) * p.q_len +
+            (size_t)qw * span) *
                sizeof(float);
   };
   auto slots = [&](size_t other) {

@@ -46,3 +46,22 @@ def test_attention(units, n, B):
     err = (O[0] - w @ V[0].double()).abs()
     print("worst error over the bound", (err / bound).max().item(), flush=True)
     assert (err <= bound).all()
+
+
+@pytest.mark.parametrize("units,S,B", [(1, 8, 1), (2, 100, 17), (3, 40, 64), (300, 30, 130)])
+def test_scan(units, S, B):
+    import paper_2606_00724_amd as wf
+    d, J = 64, 3
+    n = S << J
+    p = wf.make_params(batch=1, heads=units, ctx_len=n, head_dim=d, q_len=B, levels=J, segments=S,
+                       budget=n // 2, dtype="f32")
+    Q, K, _ = inputs(units, B, n, d, 4)
+    seg = torch.arange(S, dtype=torch.int32, device="cuda").repeat(units, 1).contiguous()
+    W = torch.empty((units, n), device="cuda")
+    tok = torch.empty((units, n // 2), dtype=torch.int32, device="cuda")
+    wf.wf_scan_select(p, Q, K, seg, W, tok, wf.alloc_workspace(p, wf.OP_SCAN, Q.device))
+    torch.cuda.synchronize()
+    ref = torch.softmax(Q[0].double() @ K[0].double().transpose(1, 2).contiguous() / 8, -1).sum(1)
+    rel = ((W - ref).abs() / ref).max().item()
+    print("worst relative error over the bound", rel / REL, flush=True)
+    assert rel <= REL
