@@ -114,7 +114,8 @@ typedef struct wf_params {
 } wf_params;
 
 /* Bytes of workspace `op` needs for these parameters (0 if it needs none or
- * the parameters are invalid). */
+ * the parameters are invalid).  fp32 calls also run, with coarser splits, in the
+ * smaller workspaces that earlier releases asked for. */
 size_t wf_workspace_bytes(const wf_params* p, int32_t op);
 
 /* k_eff = min(budget, segments * 2^levels), or -1 if p is invalid. */

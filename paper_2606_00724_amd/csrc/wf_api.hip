@@ -97,7 +97,7 @@ static wf_status check_params(const wf_params* p) {
   if (p->segments < 1 || p->segments > nJ)
     return fail(WF_ERR_INVALID_ARG, "segments %d outside [1, %d]", p->segments, nJ);
   if (p->budget < 1) return fail(WF_ERR_INVALID_ARG, "budget %d < 1", p->budget);
-  if (p->dtype == WF_BF16 && plan_scan(*p, false, false).nbuf < 2)
+  if (p->dtype == WF_BF16 && plan_scan(*p, false, 0).nbuf < 2)
     return fail(WF_ERR_UNSUPPORTED, "query block and pool range do not fit the LDS ring");
   if ((long)p->batch * p->heads *
           (((long)p->budget < ((long)p->segments << p->levels)
@@ -138,7 +138,6 @@ static size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 struct Layout {
   size_t logits = 0, sstats = 0, W = 0, seg = 0, cstats = 0,
          wpool = 0, tok = 0, part = 0, pstat = 0, wsum = 0, wpsum = 0, sseg = 0, total = 0;
-  size_t shared = 0;  // bytes that two regions share
 };
 
 static long keff_of(const wf_params& p) {
@@ -151,7 +150,7 @@ static long keff_of(const wf_params& p) {
 // coarse logit instead of the scan's per-workgroup statistics (the scan
 // forms the pool normalisers from them on chip), and its attention keeps the
 // selected tokens on chip.
-static Layout layout_for(const wf_params& p, int op, long attn_rows, bool fine) {
+static Layout layout_for(const wf_params& p, int op, long attn_rows, int fine) {
   Layout l;
   const size_t U = (size_t)p.batch * p.heads, B = p.q_len;
   const size_t nJ = (size_t)p.ctx_len >> p.levels;
@@ -194,7 +193,6 @@ static Layout layout_for(const wf_params& p, int op, long attn_rows, bool fine) 
   if (overlay) {
     l.part = l.logits;  // the first region
     l.pstat = l.part + part_bytes;
-    l.shared = std::min(off, l.pstat + pstat_bytes);
     off = std::max(off, l.pstat + pstat_bytes);
   }
   if (whole) {
@@ -225,21 +223,33 @@ static Layout layout_for(const wf_params& p, int op, long attn_rows, bool fine) 
   return l;
 }
 
-// The layout of a call that has `have` bytes.  A whole step: the fine one where
-// it is no larger than the coarse one would be with its regions apart, whatever
-// `have` is.  The staged scan and attention have no region to share: the fine
-// one where it fits `have` (and, in all, a small workspace), else the coarse one.
-constexpr size_t kFineStagedBytes = (size_t)32 << 20;
-static Layout layout_in(const wf_params& p, int op, long attn_rows, size_t have, bool* fine) {
-  const Layout f = layout_for(p, op, attn_rows, true);
-  *fine = true;
-  // bf16 splits are the same either way, and only the fused Haar tiles differ
-  if (p.dtype == WF_BF16 && (p.wavelet != WF_HAAR || op == WF_OP_CACHED || fast_path(p))) return f;
-  if ((op == WF_OP_SCAN || op == WF_OP_ATTN) && f.total <= have && f.total <= kFineStagedBytes)
-    return f;
-  const Layout c = layout_for(p, op, attn_rows, false);
-  *fine = f.total <= c.total + c.shared;
-  return *fine ? f : c;
+// Whether the finer Haar tiles' statistics fit where the attention's coarsest
+// partials share their place, so that the workspace is no larger than with coarse
+// tiles and both apart.
+static int fine_tiles(const wf_params& p, int op, long attn_rows) {
+  if (p.wavelet != WF_HAAR || (op != WF_OP_FUSED && op != WF_OP_SHARED) || fast_path(p)) return 0;
+  const long more = plan_skim(p, true, kFineTiles).ntiles - plan_skim(p, true, 0).ntiles;
+  return more == 0 || 2 * more <= plan_attn(p, attn_rows, 0).splits * (p.head_dim + 2L) ? kFineTiles
+                                                                                        : 0;
+}
+
+// fp32 calls take the fine splits where these fit the bytes that they have (and,
+// in all, a small workspace), else the coarse ones, which fit the bytes that were
+// enough before the splits became finer.
+constexpr size_t kFineBytes = (size_t)32 << 20;
+template <class Of>
+static auto layout_in(const wf_params& p, size_t have, int tiles, int* fine, const Of& of) {
+  *fine = tiles | kFineSplits;
+  const auto f = of(*fine);
+  if (p.dtype == WF_BF16 || (f.total <= have && f.total <= kFineBytes)) return f;
+  const auto c = of(tiles);
+  if (f.total <= c.total) return f;
+  *fine = tiles;
+  return c;
+}
+static Layout layout_in(const wf_params& p, int op, long attn_rows, size_t have, int* fine) {
+  return layout_in(p, have, fine_tiles(p, op, attn_rows), fine,
+                   [&](int f) { return layout_for(p, op, attn_rows, f); });
 }
 
 static wf_status check_workspace(const void* ws, size_t have, size_t need) {
@@ -324,7 +334,7 @@ static wf_status fused_impl(const wf_params* p, const void* Q, const void* K,
     return fail(WF_ERR_INVALID_ARG, "n_events %d < %d", n_events, nk + 1);
   const long keff = keff_of(*p);
   const long nrows = keff + remainder_len(*p) + p->gen_len;
-  bool fine;
+  int fine;
   const Layout l = layout_in(*p, WF_OP_FUSED, nrows, ws_bytes, &fine);
   WF_TRY(check_workspace(ws, ws_bytes, l.total));
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -423,7 +433,7 @@ static wf_status noalloc_impl(const wf_params* p, const void* Q, const void* K,
                               int32_t* tok_idx, int32_t* seg_idx, void* stream) {
   WF_TRY(check_params(p));
   const long nrows = keff_of(*p) + remainder_len(*p) + p->gen_len;
-  bool fine;
+  int fine;
   const size_t need = layout_in(*p, WF_OP_FUSED, nrows, kScratchBytes, &fine).total;
   if (need > kScratchBytes)
     return fail(WF_ERR_WORKSPACE,
@@ -493,7 +503,7 @@ static wf_status cached_impl(const wf_params* p, const void* Q, const float* app
     return fail(WF_ERR_INVALID_ARG, "n_events %d < %d", n_events, nk + 1);
   const long keff = keff_of(*p);
   const long nrows = cached_rows(*p);
-  bool fine;
+  int fine;
   const Layout l = layout_in(*p, WF_OP_CACHED, nrows, ws_bytes, &fine);
   WF_TRY(check_workspace(ws, ws_bytes, l.total));
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -592,7 +602,7 @@ static wf_status shared_impl(const wf_params* p, const void* Q, const void* K,
     return fail(WF_ERR_INVALID_ARG, "n_events %d < %d", n_events, nk + 1);
   const long keff = keff_of(*p);
   const long nrows = keff + remainder_len(*p) + p->gen_len;
-  bool fine;
+  int fine;
   const Layout l = layout_in(*p, WF_OP_SHARED, nrows, ws_bytes, &fine);
   WF_TRY(check_workspace(ws, ws_bytes, l.total));
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -681,10 +691,10 @@ static wf_status check_recursion(const wf_params* p, const float* prop, int32_t*
 
 struct RecLayout {
   size_t logits = 0, stats = 0, W = 0, sel[2] = {0, 0}, tok = 0, part = 0, pstat = 0,
-         total = 0, shared = 0;
+         total = 0;
 };
 
-static RecLayout rec_layout(const wf_params& p, const int32_t* counts, bool fine) {
+static RecLayout rec_layout(const wf_params& p, const int32_t* counts, int fine) {
   RecLayout l;
   const RecPlan rp = plan_recursion(p, counts);
   const size_t U = (size_t)p.batch * p.heads, B = p.q_len;
@@ -705,7 +715,6 @@ static RecLayout rec_layout(const wf_params& p, const int32_t* counts, bool fine
   if (overlay) {
     l.part = l.logits;
     l.pstat = l.part + part_bytes;
-    l.shared = std::min(off, l.pstat + pstat_bytes);
     off = std::max(off, l.pstat + pstat_bytes);
   }
   l.W = take(U * rp.max_n * sizeof(float));
@@ -720,14 +729,8 @@ static RecLayout rec_layout(const wf_params& p, const int32_t* counts, bool fine
   return l;
 }
 
-// as layout_in of a whole step
-static RecLayout rec_layout_of(const wf_params& p, const int32_t* counts, bool* fine) {
-  const RecLayout f = rec_layout(p, counts, true);
-  *fine = true;
-  if (p.dtype == WF_BF16) return f;
-  const RecLayout c = rec_layout(p, counts, false);
-  *fine = f.total <= c.total + c.shared;
-  return *fine ? f : c;
+static RecLayout rec_layout_in(const wf_params& p, const int32_t* counts, size_t have, int* fine) {
+  return layout_in(p, have, 0, fine, [&](int f) { return rec_layout(p, counts, f); });
 }
 
 static const char* const kRecTileNames[WF_MAX_LEVELS] = {
@@ -768,8 +771,8 @@ static wf_status recursive_impl(const wf_params* p, const float* prop, const voi
   const int nk = rec_kernels(*p);
   if (events && n_events < nk + 1)
     return fail(WF_ERR_INVALID_ARG, "n_events %d < %d", n_events, nk + 1);
-  bool fine;
-  const RecLayout l = rec_layout_of(*p, counts, &fine);
+  int fine;
+  const RecLayout l = rec_layout_in(*p, counts, ws_bytes, &fine);
   WF_TRY(check_workspace(ws, ws_bytes, l.total));
   hipStream_t s = static_cast<hipStream_t>(stream);
   (void)hipGetLastError();
@@ -838,7 +841,7 @@ size_t wf_workspace_bytes(const wf_params* p, int32_t op) {
   if (check_params(p) != WF_OK) return 0;
   if (op < WF_OP_SKIM || op > WF_OP_SHARED) return 0;
   const long rows = keff_of(*p) + remainder_len(*p) + p->gen_len;
-  bool fine;
+  int fine;
   const size_t total = layout_in(*p, op, rows, SIZE_MAX, &fine).total;
   if (op != WF_OP_ATTN) return total;
   // enough for a call with fewer rows too
@@ -872,7 +875,7 @@ wf_status wf_skim_score(const wf_params* p, const void* Q, const float* approx,
   WF_TRY(check_ptr(approx, "approx", false));
   WF_TRY(check_ptr(seg_score, "seg_score", false));
   WF_TRY(check_ptr(seg_idx, "seg_idx", false));
-  bool fine;
+  int fine;
   const Layout l = layout_in(*p, WF_OP_SKIM, 0, workspace_bytes, &fine);
   WF_TRY(check_workspace(workspace, workspace_bytes, l.total));
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -897,7 +900,7 @@ wf_status wf_scan_select(const wf_params* p, const void* Q, const void* K,
   WF_TRY(check_ptr(seg_idx, "seg_idx", false));
   WF_TRY(check_ptr(tok_score, "tok_score", true));
   WF_TRY(check_ptr(tok_idx, "tok_idx", false));
-  bool fine;
+  int fine;
   const Layout l = layout_in(*p, WF_OP_SCAN, 0, workspace_bytes, &fine);
   WF_TRY(check_workspace(workspace, workspace_bytes, l.total));
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -940,7 +943,7 @@ wf_status wf_sparse_attn(const wf_params* p, const void* Q, const void* Ks,
   WF_TRY(check_ptr(Vs, "Vs", false));
   WF_TRY(check_ptr(O, "O", false));
   if (n_kv < 1) return fail(WF_ERR_INVALID_ARG, "n_kv %d < 1", n_kv);
-  bool fine;
+  int fine;
   const Layout l = layout_in(*p, WF_OP_ATTN, n_kv, workspace_bytes, &fine);
   WF_TRY(check_workspace(workspace, workspace_bytes, l.total));
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -1066,8 +1069,8 @@ wf_status wf_recursion_counts(const wf_params* p, const float* proportions,
 size_t wf_recursive_workspace_bytes(const wf_params* p, const float* proportions) {
   int32_t c[WF_MAX_LEVELS];
   if (check_recursion(p, proportions, c) != WF_OK) return 0;
-  bool fine;
-  return rec_layout_of(*p, c, &fine).total;
+  int fine;
+  return rec_layout_in(*p, c, SIZE_MAX, &fine).total;
 }
 
 wf_status wf_filter_attend_recursive(const wf_params* p, const float* proportions,

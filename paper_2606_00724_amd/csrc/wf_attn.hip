@@ -615,14 +615,14 @@ constexpr long kTokCap = 4096;
 // (the coarse partials), at most twice as many where fine.  (With a split every
 // 4096 rows, as the ids alone would have it, 700 units of a few rows and a
 // tail of 5000 took 1.9 times the workspace, and 500 units of 100K rows 25.)
-static long most_fp32_splits(long U, long nrows, bool fine) {
+static long most_fp32_splits(long U, long nrows, int fine) {
   const long chunks = std::max(1L, (nrows + 127) / 128);
   const long splits = std::min(chunks, std::max(1L, (512 + U - 1) / U));
   const long cps = (chunks + splits - 1) / splits;
-  return (chunks + cps - 1) / cps * (fine ? 2 : 1);
+  return (chunks + cps - 1) / cps * (fine & kFineSplits ? 2 : 1);
 }
 
-AttnPlan plan_attn(const wf_params& p, long nrows, bool fine) {
+AttnPlan plan_attn(const wf_params& p, long nrows, int fine) {
   AttnPlan a{};
   const long U = (long)p.batch * p.heads;
   const int D = p.head_dim;
@@ -682,7 +682,7 @@ static hipError_t launch_attn_batches(bool d128, const AttnArgs& a, size_t lds, 
 hipError_t launch_attn(const wf_params& p, const void* Q, const void* K,
                        const void* V, const int32_t* tok, int nsel,
                        const void* Kg, const void* Vg, int G, long nrows,
-                       float* part, float* pstat, bool fine, hipStream_t s, int share) {
+                       float* part, float* pstat, int fine, hipStream_t s, int share) {
   if (share < 1 || (p.batch * p.heads) % share != 0) return hipErrorInvalidValue;
   const AttnPlan pl = plan_attn(p, nrows, fine);
   AttnArgs a;
@@ -722,7 +722,7 @@ hipError_t launch_attn(const wf_params& p, const void* Q, const void* K,
 bool attn_can_select(const wf_params& p, long nrows) {
   if (p.segments > kSelectLdsSegs || (p.dtype != WF_BF16 && !wide_weights(p))) return false;
   // (the coarse plan's splits are the longest, its ring is no deeper)
-  const AttnPlan pl = plan_attn(p, nrows, false);
+  const AttnPlan pl = plan_attn(p, nrows, 0);
   if (pl.nbuf < 2 || pl.rps > pl.tcap) return false;
   const size_t ring = (size_t)pl.nbuf * 2 * kRingRows * (p.dtype == WF_BF16 ? 2 : 4) * p.head_dim;
   return sizeof(SelectShared<kAttnRingBlock>) + (size_t)p.segments * sizeof(int32_t) <= ring;
@@ -731,7 +731,7 @@ bool attn_can_select(const wf_params& p, long nrows) {
 hipError_t launch_attn_select(const wf_params& p, const void* Q, const void* K, const void* V,
                               const float* wpool, const int32_t* seg, int32_t* tok_out,
                               const void* Kg, const void* Vg, long nrows, float* part,
-                              float* pstat, bool fine, hipStream_t s, int share) {
+                              float* pstat, int fine, hipStream_t s, int share) {
   if (!attn_can_select(p, nrows) || share < 1 || (p.batch * p.heads) % share != 0)
     return hipErrorInvalidValue;
   const AttnPlan pl = plan_attn(p, nrows, fine);
@@ -792,7 +792,7 @@ static hipError_t launch_attn_batches(bool d128, const AttnArgs& a, size_t lds, 
 
 hipError_t launch_attn_combine(const wf_params& p, long nrows,
                                const float* part, const float* pstat, void* O,
-                               bool fine, hipStream_t s) {
+                               int fine, hipStream_t s) {
   AttnArgs a{};
   a.part = const_cast<float*>(part);
   a.pstat = const_cast<float*>(pstat);

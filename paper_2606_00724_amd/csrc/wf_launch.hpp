@@ -145,18 +145,20 @@ inline bool keys_stream(const wf_params& p) {
          (size_t)256 << 20;
 }
 
-// fine: the splits that are fastest.  Without it the Haar tiles, fp32 scan
-// ranges and fp32 attention splits are so coarse that their statistics and
-// partials need no more workspace than whole 64-coefficient tiles and splits
-// of whole 128-row chunks do: programs keep workspaces of that size, and
-// the allocation-free call's scratch has to hold every call it held.  The
-// caller of a plan and the launches that follow it pass the same value.
+// fine: the splits that are fastest, kFineTiles for the Haar tiles and kFineSplits
+// for the fp32 scan ranges and attention splits.  Without them those are so coarse
+// that their statistics and partials need no more workspace than whole
+// 64-coefficient tiles and splits of whole 128-row chunks do: programs keep
+// workspaces of that size, and the allocation-free call's scratch has to hold every
+// call it held.  The caller of a plan and the launches that follow it pass the
+// same value.
+constexpr int kFineTiles = 1, kFineSplits = 2;
 DwtPlan plan_dwt(const wf_params& p);
-SkimPlan plan_skim(const wf_params& p, bool fused, bool fine);
+SkimPlan plan_skim(const wf_params& p, bool fused, int fine);
 // select: the scan workgroups take the top-S regions themselves (all S
 // region ids in LDS)
-ScanPlan plan_scan(const wf_params& p, bool select, bool fine);
-AttnPlan plan_attn(const wf_params& p, long nrows, bool fine);
+ScanPlan plan_scan(const wf_params& p, bool select, int fine);
+AttnPlan plan_attn(const wf_params& p, long nrows, int fine);
 // Most splits that the coarse plan of any row count up to nrows takes (fewer rows
 // can take more splits: 9 chunks in 5 splits of two, 8 in 8 of one).
 long most_attn_splits(const wf_params& p, long nrows);
@@ -182,7 +184,7 @@ hipError_t launch_dwt(const wf_params& p, const void* K, float* approx,
                       float* details, hipStream_t s);
 hipError_t launch_skim_tiles(const wf_params& p, bool fused, const void* Q,
                              const void* K, const float* approx, float* logits,
-                             float* stats, bool fine, hipStream_t s);
+                             float* stats, int fine, hipStream_t s);
 // One scale b of the multi-scale recursion (Haar).  Tiles: the coarse
 // logits of its n candidates (all 2^b-blocks when parent is null, else the
 // two halves of each block in parent [U][npar]).  Select: the eq. 8 weights
@@ -223,7 +225,7 @@ hipError_t launch_skim_weights(const wf_params& p, int ntiles, const float* logi
 // share: units per selection (seg indexed by u / share).
 hipError_t launch_scan_chunks(const wf_params& p, int weights, const void* Q,
                               const void* K, const int32_t* seg, float* stats,
-                              float* wpool, bool fine, hipStream_t s, int stat_slices = 0,
+                              float* wpool, int fine, hipStream_t s, int stat_slices = 0,
                               int share = 1);
 // Token-level path: the weights pass that first takes the unit's top-S
 // regions of W itself (seg_out [U][S] receives them) and forms the pool
@@ -241,7 +243,7 @@ bool scan_can_select(const wf_params& p);
 // writes one (max, sum) slice per workgroup into stats.
 hipError_t launch_scan_select_stats(const wf_params& p, const void* Q, const void* K,
                                     const float* W, int32_t* seg_out, float* stats,
-                                    bool fine, hipStream_t s);
+                                    int fine, hipStream_t s);
 hipError_t launch_scan_select(const wf_params& p, const float* wpool,
                               const int32_t* seg, int32_t* tok,
                               hipStream_t s);
@@ -252,7 +254,7 @@ hipError_t launch_gather(const wf_params& p, const void* K, const void* V,
 hipError_t launch_attn(const wf_params& p, const void* Q, const void* K,
                        const void* V, const int32_t* tok, int nsel,
                        const void* Kg, const void* Vg, int G, long nrows,
-                       float* part, float* pstat, bool fine, hipStream_t s, int share = 1);
+                       float* part, float* pstat, int fine, hipStream_t s, int share = 1);
 // The top-S regions (eq. 9) of given weights W [groups][L >> J], one
 // workgroup per group, into seg [groups][S].
 hipError_t launch_select_w(const wf_params& p, long groups, const float* W, int32_t* seg,
@@ -265,7 +267,7 @@ bool attn_can_select(const wf_params& p, long nrows);
 hipError_t launch_attn_select(const wf_params& p, const void* Q, const void* K, const void* V,
                               const float* wpool, const int32_t* seg, int32_t* tok_out,
                               const void* Kg, const void* Vg, long nrows, float* part,
-                              float* pstat, bool fine, hipStream_t s, int share = 1);
+                              float* pstat, int fine, hipStream_t s, int share = 1);
 // out [groups][n] = sum over h < H of in [groups H + h][n], in order of h
 // (the selection weights of a sequence's heads added up).
 hipError_t launch_head_sum(const float* in, float* out, long n, int H, int groups,
@@ -280,6 +282,6 @@ hipError_t load_skim_kernels();
 hipError_t load_dwt_kernels();
 hipError_t launch_attn_combine(const wf_params& p, long nrows,
                                const float* part, const float* pstat, void* O,
-                               bool fine, hipStream_t s);
+                               int fine, hipStream_t s);
 
 }  // namespace wf

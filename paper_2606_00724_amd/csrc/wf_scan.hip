@@ -545,13 +545,13 @@ constexpr size_t kLdsBudget = 160 * 1024 - 1024;
 
 // Most fp32 ranges of a unit: those of 1 to 8 chunks of 128 positions, about
 // 1024 in all (the coarse statistics), at most twice as many where fine.
-static long most_fp32_ranges(long U, long P, bool fine) {
+static long most_fp32_ranges(long U, long P, int fine) {
   const long chunks = (P + 127) / 128;
   const long cpw = std::max(1L, std::min(8L, U * chunks / 1024));
-  return (chunks + cpw - 1) / cpw * (fine ? 2 : 1);
+  return (chunks + cpw - 1) / cpw * (fine & kFineSplits ? 2 : 1);
 }
 
-ScanPlan plan_scan(const wf_params& p, bool select, bool fine) {
+ScanPlan plan_scan(const wf_params& p, bool select, int fine) {
   ScanPlan s{};
   const long P = (long)p.segments << p.levels;
   const long U = (long)p.batch * p.heads;
@@ -642,7 +642,7 @@ static int scan_streams(const wf_params& p) {
 // the scan's arguments when its workgroups take the top-S regions from W
 // themselves; false when the shape does not allow it
 static bool scan_select_args(const wf_params& p, const void* Q, const void* K, const float* W,
-                             int32_t* seg_out, int share, bool fine, ScanArgs& a, ScanPlan& pl) {
+                             int32_t* seg_out, int share, int fine, ScanArgs& a, ScanPlan& pl) {
   if (p.segments > kSelectLdsSegs || share < 1 ||
       (p.batch * p.heads) % share != 0)
     return false;
@@ -678,8 +678,8 @@ static bool scan_select_args(const wf_params& p, const void* Q, const void* K, c
 bool scan_can_select(const wf_params& p) {
   ScanArgs a;
   ScanPlan pl;
-  return scan_select_args(p, nullptr, nullptr, nullptr, nullptr, 1, true, a, pl) &&
-         scan_select_args(p, nullptr, nullptr, nullptr, nullptr, 1, false, a, pl);
+  return scan_select_args(p, nullptr, nullptr, nullptr, nullptr, 1, kFineSplits, a, pl) &&
+         scan_select_args(p, nullptr, nullptr, nullptr, nullptr, 1, 0, a, pl);
 }
 
 hipError_t launch_scan_select_weights(const wf_params& p, const void* Q, const void* K,
@@ -688,7 +688,7 @@ hipError_t launch_scan_select_weights(const wf_params& p, const void* Q, const v
   ScanArgs a;
   ScanPlan pl;
   // (the pool normalisers take a thread per query row, 64 rows at most)
-  if (p.dtype != WF_BF16 || p.q_len > 64 || !scan_select_args(p, Q, K, W, seg_out, share, true, a, pl))
+  if (p.dtype != WF_BF16 || p.q_len > 64 || !scan_select_args(p, Q, K, W, seg_out, share, 0, a, pl))
     return hipErrorInvalidValue;
   a.blocks = blocks;
   a.wpool = wpool;
@@ -701,7 +701,7 @@ hipError_t launch_scan_select_weights(const wf_params& p, const void* Q, const v
 
 hipError_t launch_scan_select_stats(const wf_params& p, const void* Q, const void* K,
                                     const float* W, int32_t* seg_out, float* stats,
-                                    bool fine, hipStream_t s) {
+                                    int fine, hipStream_t s) {
   ScanArgs a;
   ScanPlan pl;
   if (!fp32_rows_fit(p) || !scan_select_args(p, Q, K, W, seg_out, 1, fine, a, pl))
@@ -721,7 +721,7 @@ hipError_t launch_scan_select_stats(const wf_params& p, const void* Q, const voi
 
 hipError_t launch_scan_chunks(const wf_params& p, int weights, const void* Q,
                               const void* K, const int32_t* seg, float* stats,
-                              float* wpool, bool fine, hipStream_t s, int stat_slices, int share) {
+                              float* wpool, int fine, hipStream_t s, int stat_slices, int share) {
   if (share < 1 || (p.batch * p.heads) % share != 0 || !fp32_rows_fit(p))
     return hipErrorInvalidValue;
   const ScanPlan pl = plan_scan(p, false, fine);

@@ -595,7 +595,7 @@ static int rec_cpt(const wf_params& p, int b) {
   return p.wavelet == WF_HAAR ? haar_cpt(b) : kMaxCoefTile;
 }
 
-SkimPlan plan_skim(const wf_params& p, bool fused, bool fine) {
+SkimPlan plan_skim(const wf_params& p, bool fused, int fine) {
   SkimPlan k;
   const int J = p.levels;
   if (!fused) {
@@ -603,7 +603,7 @@ SkimPlan plan_skim(const wf_params& p, bool fused, bool fine) {
     k.cpt = kMaxCoefTile;
   } else if (p.wavelet == WF_HAAR) {
     k.source = keys_stream(p) ? kHaarStream : kHaarSum;
-    k.cpt = fine ? haar_cpt(J, (long)p.batch * p.heads, (long)p.ctx_len >> J) : haar_cpt(J);
+    k.cpt = fine & kFineTiles ? haar_cpt(J, (long)p.batch * p.heads, (long)p.ctx_len >> J) : haar_cpt(J);
   } else {
     k.source = kCascade;
     k.cpt = kMaxCoefTile;  // 4 (d=128) or 8 (d=64) streams of 16 or 8
@@ -696,7 +696,7 @@ static hipError_t skim_tiles_common(const wf_params& p, int source, int cpt, int
 
 hipError_t launch_skim_tiles(const wf_params& p, bool fused, const void* Q,
                              const void* K, const float* approx, float* logits,
-                             float* stats, bool fine, hipStream_t s) {
+                             float* stats, int fine, hipStream_t s) {
   const SkimPlan pl = plan_skim(p, fused, fine);
   return skim_tiles_common(p, pl.source, pl.cpt, p.levels, (long)p.ctx_len >> p.levels,
                            nullptr, 0, Q, K, approx, logits, stats, s);
