@@ -930,7 +930,8 @@ static FastPlan plan_token(const wf_params& p, int J, long Lf, bool lse, bool ga
     const long most = std::min(chunks, std::max(1L, (slots + U - 1) / U));
     const long cpr = (chunks + most - 1) / most;
     const long max_cpr = gather ? cpr : cpr <= kHeldChunks ? kHeldChunks : chunks;
-    return ranges_per_unit(U, chunks, slots, max_cpr);
+    const long cus = device_cu_count();
+    return ranges_per_unit(U, chunks, slots, max_cpr, p.head_dim == 64 && slots > cus ? cus : 0);
   };
   const long R0 = ranges(2L * device_cu_count());
   const long cpr0 = (chunks + R0 - 1) / R0;

@@ -79,13 +79,20 @@ inline long remainder_len(const wf_params& p) { return (long)p.ctx_len - filtere
 // selection, its first loads: about six chunks) is paid once.  28 units of 61K
 // keys, 32-token blocks: 216.8 us a call with 10 ranges a unit, 147.5 with 9; 100 units
 // of 32K: 317.6 and 224.6.  Never more ranges than ceil(slots / U) except for max_cpw.
-inline long ranges_per_unit(long U, long chunks, long slots, long max_cpw) {
+//
+// cu_slots: CUs, for workgroups that a CU rather than the memory bounds, two of
+// which are resident per CU (the token skims of 64 channels): a CU that has one more
+// than the others ends last (fixed part: four chunks).  Skim of 300 units of 6000
+// keys, 8-token blocks: 77.3 us with one range a unit, 70.0 with two; 400 of 1734:
+// 0.95 of two ranges' time with one.
+inline long ranges_per_unit(long U, long chunks, long slots, long max_cpw, long cu_slots = 0) {
   const long up = std::min(chunks, std::max(1L, (slots + U - 1) / U));
   const long down = std::min(chunks, std::max(1L, slots / U));
   const long least = (chunks + max_cpw - 1) / max_cpw;
   auto cost = [&](long C) {
     const double cpw = (double)((chunks + C - 1) / C), fixed = 6.0;
     const long n = U * ((chunks + (long)cpw - 1) / (long)cpw), rest = n % slots;
+    if (cu_slots) return (double)((n + cu_slots - 1) / cu_slots) * (cpw + 4.0);
     return (double)(n / slots) * (cpw + fixed) +
            (rest ? cpw * std::max(0.7, (double)rest / (double)slots) + fixed : 0.0);
   };
