@@ -301,7 +301,8 @@ static bool general_wide(const wf_params& p) {
   return !fast_path(p) && scan_selects(p);
 }
 static bool general_attn_selects(const wf_params& p) {
-  return general_wide(p) && attn_can_select(p, fused_rows(p));
+  const bool small = p.dtype == WF_BF16 && p.q_len <= 64 && ((p.ctx_len >> p.levels) & 3) == 0;
+  return general_wide(p) && attn_can_select(p, fused_rows(p)) && (small || pool_on_chip(p));
 }
 static int fused_kernels(const wf_params& p) {
   return fast_path(p) ? 5 : general_attn_selects(p) ? 6 : 7;

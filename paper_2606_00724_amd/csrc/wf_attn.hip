@@ -719,11 +719,16 @@ hipError_t launch_attn(const wf_params& p, const void* Q, const void* K,
               : attn_launch<float, 64>(a, pl.lds_bytes, s);
 }
 
+bool pool_on_chip(const wf_params& p) {
+  return ((long)p.segments << p.levels) <= 2L * 16 * kAttnRingBlock;
+}
+
 bool attn_can_select(const wf_params& p, long nrows) {
   if (p.segments > kSelectLdsSegs || (p.dtype != WF_BF16 && !wide_weights(p))) return false;
   // (the coarse plan's splits are the longest, its ring is no deeper)
   const AttnPlan pl = plan_attn(p, nrows, 0);
   if (pl.nbuf < 2 || pl.rps > pl.tcap) return false;
+  if (p.dtype != WF_BF16 && !pool_on_chip(p)) return false;
   const size_t ring = (size_t)pl.nbuf * 2 * kRingRows * (p.dtype == WF_BF16 ? 2 : 4) * p.head_dim;
   return sizeof(SelectShared<kAttnRingBlock>) + (size_t)p.segments * sizeof(int32_t) <= ring;
 }

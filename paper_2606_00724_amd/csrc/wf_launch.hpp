@@ -270,6 +270,12 @@ hipError_t launch_select_w(const wf_params& p, long groups, const float* W, int3
 // tokens of the scan weights wpool [U][S 2^J] itself (the pool of the
 // regions seg [U][S]); tok_out [U][k_eff] (nullable) receives them.
 bool attn_can_select(const wf_params& p, long nrows);
+// Whether the selecting attention holds a unit's scan weights in registers (16384).
+// Past that each of a unit's workgroups reads them from memory several times, and
+// the general path with fp32 keys, more than 64 query rows or coefficients that
+// are no multiple of four selects in a kernel of its own (5 units, 45412 of
+// 120288 positions: 178.6 + 26.5 us apart, 225.1 in one).
+bool pool_on_chip(const wf_params& p);
 // share: units per selection (wpool, seg and tok_out indexed by u / share).
 hipError_t launch_attn_select(const wf_params& p, const void* Q, const void* K, const void* V,
                               const float* wpool, const int32_t* seg, int32_t* tok_out,

@@ -48,3 +48,18 @@ def test_fp32_rounds_leave_few_cus_idle(units, rows):
         per = -(-chunks // c)
         return -(-units * -(-chunks // per) // 256) * (per + 1)
     assert cost(_ranges(wf, units, rows, 64)) <= 0.85 * cost(1)
+
+
+@pytest.mark.parametrize("dtype,B,L,apart", [
+    ("bf16", 16, 7933 * 16, True),    # coefficients no multiple of four
+    ("bf16", 100, 8192 * 16, True), ("f32", 16, 8192 * 16, True),
+    ("bf16", 16, 8192 * 16, False),
+    ("f32", 16, 1024 * 16, False), ("bf16", 100, 1024 * 16, False)])
+def test_large_pools_are_selected_apart(dtype, B, L, apart):
+    """Pools past 16384 positions are not selected by every workgroup of the
+    attention where a kernel of its own used to do it."""
+    import paper_2606_00724_amd as wf
+    S = (L >> 4) * 7 // 8
+    p = wf.make_params(batch=1, heads=5, ctx_len=L, head_dim=128, q_len=B, levels=4, segments=S,
+                       budget=4 * S, dtype=dtype, wavelet="db2")
+    assert ("scan_select" in wf.fused_kernel_names(p)) == apart
