@@ -21,9 +21,10 @@ def cascade(x, levels, boundary):
     return x
 
 
-# (levels, coefficients per unit): one, two and three coefficients are all
-# edge; 5 has two interior ones; 70 crosses a wave's run and a workgroup;
-# past it several workgroups a unit.  Every block length in loads.
+# (levels, coefficients per unit): the last coefficient (J = 1) or two are edge
+# ones, so one and two coefficients are all edge from J = 2 on and 3 has one
+# interior one; 70 crosses a wave's run and a workgroup; past it several workgroups
+# a unit.  Every block length in loads.
 SHAPES = [(1, 1), (1, 2), (1, 333), (2, 1), (2, 5), (2, 300), (3, 3), (3, 70), (4, 2),
           (4, 131), (5, 4), (5, 67), (6, 1), (6, 3), (6, 35), (7, 2), (7, 19)]
 

@@ -1,5 +1,9 @@
 """Which parameters the fused calls take does not depend on how a plan splits
-the work (no GPU needed: plans are host arithmetic over 256 CUs)."""
+the work, and which splits are taken (no GPU needed: plans are host arithmetic
+over 256 CUs)."""
+import os
+import subprocess
+
 import pytest
 
 
@@ -63,3 +67,36 @@ def test_large_pools_are_selected_apart(dtype, B, L, apart):
     p = wf.make_params(batch=1, heads=5, ctx_len=L, head_dim=128, q_len=B, levels=4, segments=S,
                        budget=4 * S, dtype=dtype, wavelet="db2")
     assert ("scan_select" in wf.fused_kernel_names(p)) == apart
+
+
+# (kernel, units, chunks, workgroups resident at once, most chunks a range) of
+# the longer-range cases of test_gpu_dispatch_edges.py: 16384 keys and 11520 pool
+# positions in chunks of 128, 5760 rows in chunks of 64; fp32: 2560 in chunks of 64
+LONGER = [("token skim", 28, 128, 512, 128), ("held and db2 skims", 28, 128, 256, 128),
+          ("bf16 scan", 28, 90, 256, 32), ("bf16 attention", 28, 90, 256, 64),
+          ("fp32 scan", 40, 40, 256, 0), ("fp32 attention", 40, 40, 256, 0)]
+
+
+def test_odd_unit_counts_take_fewer_longer_ranges(tmp_path):
+    """Each kernel's plan takes less than ceil(resident / units) ranges a unit, and
+    ranges of more chunks than that count would give."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    src = tmp_path / "ranges.cpp"
+    body = "".join(
+        f'  std::printf("%ld\\n", ' + (
+            f"wf::ranges_per_unit({u}, {c}, {slots}, {most})" if most else
+            f"wf::fp32_ranges_per_unit({u}, {c}, {slots}, {c}, 1)") + ");\n"
+        for _, u, c, slots, most in LONGER)
+    src.write_text('#include <cstdio>\nnamespace wf { struct Db2TokenTaps; }\n#include "wf_launch.hpp"\n'
+                   "namespace wf { int device_cu_count() { return 256; } }\n"
+                   "int main() {\n" + body + "}\n")
+    exe = tmp_path / "ranges"
+    subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    f"-I{root}/include", f"-I{root}/paper_2606_00724_amd/csrc", str(src), "-o",
+                    str(exe)], check=True)
+    got = [int(x) for x in subprocess.run([str(exe)], capture_output=True, text=True,
+                                          check=True).stdout.split()]
+    for (name, units, chunks, slots, _), ranges in zip(LONGER, got):
+        up = -(-slots // units)
+        assert ranges < up, name
+        assert -(-chunks // ranges) > -(-chunks // up), name
