@@ -276,7 +276,7 @@ static const char* const kGeneralNames[] = {
 // W over all CUs, the top-S in the statistics pass, and when the attention's
 // rows allow it the top-k in the attention (scan_selects).  One workgroup per
 // unit for W and the top-S took 30.6 us of 107.9 with 16 units of 128 query
-// rows and 1024 coefficients; W over all CUs takes 11.2.
+// rows and 1024 coefficients; W over all CUs takes 8.1.
 static const char* const kGeneralWideNames[] = {
     "skim_tile", "skim_weights", "scan_stats", "scan_weights",
     "scan_select", "sparse_attn", "attn_combine"};
@@ -657,8 +657,8 @@ static wf_status shared_impl(const wf_params* p, const void* Q, const void* K,
       WF_TRY(step(launch_skim_select(*p, sp.ntiles, logits, sstats, W, unit_seg, s)));
     WF_TRY(step(launch_head_sum(W, wsum, nJ, H, p->batch, s)));
     WF_TRY(step(launch_select_w(pg, p->batch, wsum, seg, s)));
-    WF_TRY(step(launch_scan_chunks(*p, 0, Q, K, seg, cstats, wpool, fine, s, 0, H)));
-    WF_TRY(step(launch_scan_chunks(*p, 1, Q, K, seg, cstats, wpool, fine, s, 0, H)));
+    WF_TRY(step(launch_scan_chunks(*p, 0, Q, K, seg, cstats, wpool, fine, s, H)));
+    WF_TRY(step(launch_scan_chunks(*p, 1, Q, K, seg, cstats, wpool, fine, s, H)));
     WF_TRY(step(launch_head_sum(wpool, wpsum, P, H, p->batch, s)));
     WF_TRY(step(launch_scan_select(pg, wpsum, seg, tok, s)));
     WF_TRY(step(launch_attn(*p, Q, K, V, tok, (int)keff, Kg, Vg, p->gen_len, nrows, part,

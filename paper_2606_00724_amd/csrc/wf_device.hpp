@@ -182,14 +182,6 @@ __device__ __forceinline__ void unit_block_weights(const float* lg, const float*
   }
 }
 
-// Sums of v over lane pairs (l, l ^ 1) and (l, l ^ 2), DPP quad_perm.
-__device__ __forceinline__ float add_xor1(float v) {
-  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xf, 0xf, false));
-}
-__device__ __forceinline__ float add_xor2(float v) {
-  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xf, 0xf, false));
-}
-
 // Reductions over the lane pairs (l, l ^ 16) and (l, l ^ 32) on the VALU:
 // v_permlane16_swap / v_permlane32_swap of a value with itself leave the
 // two partners' values in the two results (lane l gets {v[l], v[l ^ 16]} and
@@ -640,17 +632,6 @@ __device__ __forceinline__ void block_select_topk_regs(const float* score, int n
     gt_base += total >> 16;
     eq_base += total & 0xffffu;
   }
-}
-
-// Top-k by whichever form fits: registers for n <= EPT * NT, else the
-// general loop over `score`.
-template <int NT, int EPT, typename Emit>
-__device__ __forceinline__ void block_select_topk_any(const float* score, int n, int k, Emit emit,
-                                                      SelectShared<NT>& sh) {
-  if (n <= EPT * NT)
-    block_select_topk_regs<NT, EPT>(score, n, k, emit, sh);
-  else
-    block_select_topk<NT>(score, n, k, emit, sh);
 }
 
 // ------------------------------------------------------------ LDS staging

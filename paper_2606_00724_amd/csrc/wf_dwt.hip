@@ -133,7 +133,7 @@ __global__ __launch_bounds__(kBlock, 2) void band_approx_kernel(DwtArgs a, Taps 
   if (sym && tile == a.ntiles - 1) {
     for (int i = threadIdx.x; i < (6 << J); i += kBlock) edge_lds[i] = edge.e[i];
     __syncthreads();
-    const long n = n_end + wave;  // at most three
+    const long n = n_end + wave;  // at most two
     if (n < a.nJ) edge_coef<T, D, J>(Kunit, n, a.nJ, edge_lds, RowsIdentity{}, put);
     return;
   }

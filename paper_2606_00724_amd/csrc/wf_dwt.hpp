@@ -532,7 +532,10 @@ __device__ void band_tile(const T* Kunit, long L, long n0, int ncoef, long n_end
 // extensions make E_m differ from f_J, but E_m depends only on m (lengths
 // are multiples of 2^J), so the host builds the three filters once per J by
 // pushing impulses through the extended cascade.  Filter m starts at
-// 2^J m (m + 1) / 2.  The banded path with edges covers J <= kBandMaxJ.
+// 2^J m (m + 1) / 2.  A window of 3 2^J - 2 rows from coefficient nJ - 3 ends inside
+// the sequence, so the skim tiles and the staged transform reach m < 2 only; the
+// token skim's last three blocks take all three.  The banded path with edges covers
+// J <= kBandMaxJ.
 constexpr int kBandMaxJ = 7;
 struct EdgeTaps {
   float e[6 << kBandMaxJ];

@@ -68,15 +68,15 @@ struct ScanArgs {
   int32_t* seg_out;
   int nJ;
   int w_in_lds;         // W staged in LDS for the selection
-  float* stats;         // [U][C][2][B]
+  float* stats;         // [U][C][2][B]: reference (log2 units), sum of 2^(logit - reference)
   float* wpool;         // [U][P]  (weights mode)
   long Ls;              // rows per unit in K
   int U, L, B, J, S, P, C;
-  int Cs;               // (max, sum) slices in `stats`: C, or 1 when precomputed
+  int Cs;               // slices in `stats`
   int span;             // pool positions per workgroup (multiple of the chunk)
-  int nbuf;             // LDS ring depth (bf16 path)
-  int seg_cap;          // region ids staged per workgroup (bf16 path)
-  int stream;           // statistics pass: pool rows read with the nt policy (bf16 path)
+  int nbuf;             // LDS ring depth
+  int seg_cap;          // region ids staged per workgroup
+  int stream;           // statistics pass: pool rows read with the nt policy
   float scale;
   // units per selection: the selecting scan of unit u reads W and writes
   // seg_out of selection u / share (seg_out by the group's first unit only)

@@ -33,8 +33,8 @@ struct SkimPlan {
 struct ScanPlan {
   int chunks;        // workgroups per unit
   int span;          // pool positions per workgroup
-  int nbuf;          // LDS ring depth (bf16)
-  int seg_cap;       // region ids staged per workgroup (bf16)
+  int nbuf;          // LDS ring depth
+  int seg_cap;       // region ids staged per workgroup
   size_t lds_bytes;  // dynamic LDS of the chunk kernels
 };
 
@@ -78,7 +78,9 @@ inline long remainder_len(const wf_params& p) { return (long)p.ctx_len - filtere
 // (about 0.7 of the CUs reach it) and the fixed part of a workgroup (its
 // selection, its first loads: about six chunks) is paid once.  28 units of 61K
 // keys, 32-token blocks: 216.8 us a call with 10 ranges a unit, 147.5 with 9; 100 units
-// of 32K: 317.6 and 224.6.  Never more ranges than ceil(slots / U) except for max_cpw.
+// of 32K: 317.6 and 224.6.  Kernel by kernel over 34 to 700 units of 1K to 12K keys
+// (648 calls), against ceil(slots / U) ranges: the scan's weights pass 0.93 of the
+// time (at most 1.02), the attention 0.93 (1.04), the skims 0.93.  Never more ranges than ceil(slots / U) except for max_cpw.
 //
 // cu_slots: CUs, for workgroups that a CU rather than the memory bounds, two of
 // which are resident per CU (the token skims of 64 channels): a CU that has one more
@@ -134,7 +136,8 @@ inline long fp32_ranges_per_unit(long U, long chunks, long slots, long most, lon
 // instead of 80.0; 32 fp32 units of 128 coefficients 63.8 instead of 70.0.
 // The line is drawn at 1024 in all: calls below it (two fp32 units of 128
 // coefficients would take 49.1 us instead of 54.2) keep the sequence of
-// kernels that the timed entry points have always named for them.
+// kernels that the timed entry points have always named for them.  The names draw
+// this line, not the times.
 inline bool wide_weights(const wf_params& p) {
   return (long)p.batch * p.heads * ((long)p.ctx_len >> p.levels) >= 1024;
 }
@@ -227,13 +230,12 @@ hipError_t launch_skim_select(const wf_params& p, int ntiles,
 // selection).
 hipError_t launch_skim_weights(const wf_params& p, int ntiles, const float* logits,
                                const float* stats, float* W, hipStream_t s);
-// stat_slices: 0 when `stats` holds one (max, sum) slice per scan workgroup
-// (written by the stats pass), 1 when it holds the pool's final pair.
+// stats: one (reference, sum) slice per scan workgroup, the reference in log2
+// units, written by the statistics pass and read by the weights pass.
 // share: units per selection (seg indexed by u / share).
 hipError_t launch_scan_chunks(const wf_params& p, int weights, const void* Q,
                               const void* K, const int32_t* seg, float* stats,
-                              float* wpool, int fine, hipStream_t s, int stat_slices = 0,
-                              int share = 1);
+                              float* wpool, int fine, hipStream_t s, int share = 1);
 // Token-level path: the weights pass that first takes the unit's top-S
 // regions of W itself (seg_out [U][S] receives them) and forms the pool
 // normalisers from the selected blocks' log-sum-exps (blocks [U][nJ][2][B]).
@@ -242,8 +244,8 @@ hipError_t launch_scan_chunks(const wf_params& p, int weights, const void* Q,
 hipError_t launch_scan_select_weights(const wf_params& p, const void* Q, const void* K,
                                       const float* W, const float* blocks, int32_t* seg_out,
                                       float* wpool, hipStream_t s, int share = 1);
-// Whether the scan's workgroups can take the top-S regions themselves (bf16,
-// the region ids and the selection fit in LDS).
+// Whether the scan's workgroups can take the top-S regions themselves (the region
+// ids and the selection fit in LDS).
 bool scan_can_select(const wf_params& p);
 // The statistics pass that first takes the unit's top-S regions of W itself
 // (seg_out [U][S] receives them, for the weights pass that follows) and

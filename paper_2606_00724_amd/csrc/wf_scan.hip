@@ -112,11 +112,11 @@ __device__ __forceinline__ f32x4 granule_dot(u32x4 q, u32x4 k, f32x4 acc) {
   }
 }
 
-// SEL: the workgroup first takes the unit's top-S
-// regions from W (eq. 9) itself, then queues its first pool chunks.  In the
+// SEL: the workgroup first takes the unit's top-S regions from W (eq. 9) itself,
+// then queues its first pool chunks.  In the
 // weights pass of the token-level path it forms the pool normalisers from
 // the selected blocks' log-sum-exps while they load; in the statistics pass
-// (the step from cached coefficients) the selection is all it adds, and the
+// (the coefficient-tile path and the step from cached coefficients) the selection is all it adds, and the
 // weights pass that follows reads the region ids the unit's first range
 // wrote.
 template <int WEIGHTS, typename T, int D, bool SEL = false>
@@ -620,7 +620,7 @@ static hipError_t scan_launch(const ScanArgs& a, size_t lds, hipStream_t s) {
 }
 
 // The two-pass scan takes fp32 query blocks up to the size whose rows, beside
-// 128 pool rows, fit the LDS (174 rows of 128 channels): callers see the same
+// 128 pool rows, fit the LDS (169 rows of 128 channels): callers see the same
 // limit whatever a kernel stages.
 static bool fp32_rows_fit(const wf_params& p) {
   const size_t stride = (size_t)p.head_dim * 4 + 16, nqb = (size_t)(p.q_len + 15) / 16;
@@ -721,7 +721,7 @@ hipError_t launch_scan_select_stats(const wf_params& p, const void* Q, const voi
 
 hipError_t launch_scan_chunks(const wf_params& p, int weights, const void* Q,
                               const void* K, const int32_t* seg, float* stats,
-                              float* wpool, int fine, hipStream_t s, int stat_slices, int share) {
+                              float* wpool, int fine, hipStream_t s, int share) {
   if (share < 1 || (p.batch * p.heads) % share != 0 || !fp32_rows_fit(p))
     return hipErrorInvalidValue;
   const ScanPlan pl = plan_scan(p, false, fine);
@@ -740,7 +740,7 @@ hipError_t launch_scan_chunks(const wf_params& p, int weights, const void* Q,
   a.S = p.segments;
   a.P = p.segments << p.levels;
   a.C = pl.chunks;
-  a.Cs = stat_slices > 0 ? stat_slices : pl.chunks;
+  a.Cs = pl.chunks;
   a.span = pl.span;
   a.nbuf = pl.nbuf;
   a.seg_cap = pl.seg_cap;

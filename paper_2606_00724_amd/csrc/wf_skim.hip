@@ -220,7 +220,7 @@ skim_tile_kernel(SkimTileArgs a, Taps taps, EdgeTaps edge) {
           const long n_end =
               sym ? (a.L >= band_len(J) ? min((a.L - band_len(J)) / (1L << J) + 1, nJf) : 0L) : nJf;
           band_tile<T, D, J>(Kunit, a.L, n0, ncoef, n_end, !sym, band, coef, map);
-          // at most three edge coefficients: wave w takes the w-th of the tile
+          // at most two edge coefficients: wave w takes the w-th of the tile
           const long n = max(n0, n_end) + (threadIdx.x >> 6);
           if (n < n0 + ncoef) {
             using BS = BandShape<T, D, J>;
@@ -284,8 +284,6 @@ skim_tile_kernel(SkimTileArgs a, Taps taps, EdgeTaps edge) {
   }
 }
 
-// One workgroup per unit: merge the tiles' row statistics, form W (eq. 8) and
-// select the top-S regions (eq. 9).
 // W_j (eq. 8) of unit u for the columns 4 j4 .. 4 j4 + 3, j4 in [j4_lo,
 // j4_hi) (nJ a multiple of 4), from the query-major logits and the row
 // normalisers c_q = M_q log2(e) + log2(Z_q); also into wsh when given.
@@ -460,6 +458,8 @@ __global__ __launch_bounds__(kBlock) void skim_weights_rows_kernel(SkimSelectArg
   }
 }
 
+// One workgroup per unit: merge the tiles' row statistics and form W (eq. 8),
+// unless w_ready, and select the top-S regions (eq. 9).
 constexpr int kSelectBlock = 1024;
 
 __global__ __launch_bounds__(kSelectBlock) void skim_select_kernel(SkimSelectArgs a,
