@@ -751,7 +751,7 @@ static hipError_t skim_select_common(const wf_params& p, bool two_stage, long nJ
   // W over all CUs first: on the two-stage path where the call has the
   // coefficients to fill the chip with it (28 units of 1914: 24.2 us in one
   // kernel, 11.7 + 7.8 in two; 32 of 512: 14.5 and 7.1 + 6.4), on the
-  // recursion's scales from 4096 candidates on (1024 columns a workgroup)
+  // recursion's scales from 4096 candidates on (1024 columns a workgroup).
   // So few rows and columns that one workgroup per unit is done with W before a
   // second kernel starts stay in one kernel, where the units fit the CUs at once
   // (the staged skim of 64 units of 256 columns, 8 rows: 15.8 us, in two kernels
