@@ -310,6 +310,13 @@ __global__ __launch_bounds__(kAttnRingBlock) void attn_ring_kernel(AttnArgs a) {
             } else {
               l_run += ps;
             }
+            // rows past the range repeat its last one: 0 there, as 0 times an
+            // infinite value is NaN (every wave that reads the block does it)
+            if (sb + 16 > re) {
+              f32x4* pad = reinterpret_cast<f32x4*>(const_cast<unsigned char*>(vblk));
+              for (int i = (re - sb) * G + lane; i < 16 * G; i += 64)
+                pad[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
             // P is the A operand in place; V row 4g + i, channel 16 cb + col
 #pragma unroll
             for (int i = 0; i < 4; ++i) {

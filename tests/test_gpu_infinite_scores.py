@@ -69,3 +69,24 @@ def test_scan(spans, dtype, d, B):
     ref = torch.softmax(s, -1).sum(1)
     assert (W[:, bad] == 0).all()
     assert ((W[pick][:, ~bad] - ref).abs() / ref).max().item() <= SEL_REL
+
+
+# rows that fill no last block of 16 or chunk of 64, in one split and in several;
+# the row parts of two (50 rows) and four waves (16)
+@pytest.mark.parametrize("units,n", [(3, 1), (3, 17), (3, 200), (300, 95), (600, 4099)])
+@pytest.mark.parametrize("d,B", [(64, 16), (128, 50)])
+def test_fp32_infinite_value_in_the_last_row(units, n, d, B):
+    """Channels of V that are infinite in the last row: infinite there for every
+    query, as each weight is positive, and the other channels as without them."""
+    import paper_2606_00724_amd as wf
+    p = wf.make_params(batch=1, heads=units, ctx_len=8192, head_dim=d, q_len=B, levels=1,
+                       segments=4096, budget=n, dtype="f32")
+    Q, K, V = inputs(units, B, n, d, torch.float32, rows_of(n, []))
+    ref = torch.softmax(Q[0].double() @ K[0].double().transpose(1, 2).contiguous() / d ** 0.5,
+                        -1) @ V[0].double()
+    V[:, :, -1, 0], V[:, :, -1, d - 1] = float("inf"), float("-inf")
+    O = torch.empty_like(Q)
+    wf.wf_sparse_attn(p, Q, K, V, n, O, wf.alloc_workspace(p, wf.OP_ATTN, Q.device))
+    torch.cuda.synchronize()
+    assert (O[..., 0] == float("inf")).all() and (O[..., d - 1] == float("-inf")).all()
+    assert (O[0] - ref)[..., 1:d - 1].abs().max().item() <= O_TOL["f32"]
